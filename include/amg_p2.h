@@ -219,7 +219,7 @@ typedef struct {
                                       (0 on the coarsest level)               */
     int32_t n_colors;              /* Gauss-Seidel colours (0 if not built)    */
     int32_t is_coarsest;
-    int32_t lanes_A, lanes_gs;     /* lanes per row chosen for the level's
+    int32_t lanes_A, lanes_gs;     /* lanes per row of the level's
                                       natural-order and colour-sweep kernels
                                       (of the reduced-precision copies when
                                       precision is not FP64)                 */
@@ -339,7 +339,9 @@ int amg_get_level_colors(amg_handle h, int32_t level, int32_t *colors);
  * kernels: AMG_SHAPE_NATURAL the FP64 natural-order kernels (residual,
  * Jacobi, operator, the outer Krylov operator on level 0), AMG_SHAPE_SWEEP
  * the FP64 colour sweeps, AMG_SHAPE_NATURAL_RP / AMG_SHAPE_SWEEP_RP the same
- * kernels of the reduced-precision copies. lanes: lanes of the 64-wide
+ * kernels of the reduced-precision copies. (All colours of a sweep run in
+ * one launch by default; a level whose sweep shape is set here runs one
+ * launch of that shape per colour, followed by a natural-order residual.) lanes: lanes of the 64-wide
  * wavefront per row, one of 4, 8, 16, 32, 64. trip: entries per lane and
  * loop trip, 1, 2 or 4 (a lane's entries of one trip have their loads in
  * flight together; the sums do not depend on it; the prolongation kernels

@@ -425,7 +425,8 @@ int amg_get_level_info(amg_handle h, int32_t level, amg_level_info *info) {
         info->n_colors = L.cptr.empty() ? 0 : static_cast<int>(L.cptr.size()) - 1;
         info->is_coarsest = L.coarsest ? 1 : 0;
         info->lanes_A = h->mixed ? L.mp.G : L.G;
-        info->lanes_gs = h->mixed ? L.mp.Gg : L.Gg;
+        const bool one = L.sweep.usable() && !(h->mixed ? L.mp.by_colour : L.by_colour);
+        info->lanes_gs = one ? (h->mixed ? L.mp.shape.G : L.shape.G) : (h->mixed ? L.mp.Gg : L.Gg);
         info->trip_A = h->mixed ? L.mp.trip : L.trip;
         info->trip_gs = h->mixed ? L.mp.tripg : L.tripg;
         info->lanes64_A = L.G;
@@ -628,7 +629,12 @@ int amg_set_launch_shape(amg_handle h, int32_t level, int32_t kernels, int32_t l
         AMG_REQUIRE(sweep || xcd == 0, AMG_EINVAL, "amg_set_launch_shape: xcd applies to colour sweeps only");
         switch (kernels) {
             case AMG_SHAPE_NATURAL: L.G = lanes; L.trip = trip; break;
-            case AMG_SHAPE_SWEEP: L.Gg = lanes; L.tripg = trip; L.gs_xcd = xcd; break;
+            case AMG_SHAPE_SWEEP:
+                L.Gg = lanes;
+                L.tripg = trip;
+                L.gs_xcd = xcd;
+                L.by_colour = true;
+                break;
             case AMG_SHAPE_NATURAL_RP:
             case AMG_SHAPE_SWEEP_RP:
                 AMG_REQUIRE(h->mixed, AMG_EINVAL, "amg_set_launch_shape: no reduced-precision copy (FP64 hierarchy)");
@@ -639,6 +645,7 @@ int amg_set_launch_shape(amg_handle h, int32_t level, int32_t kernels, int32_t l
                     L.mp.Gg = lanes;
                     L.mp.tripg = trip;
                     L.mp.xcd = xcd;
+                    L.mp.by_colour = true;
                 }
                 break;
             case AMG_SHAPE_VANKA:

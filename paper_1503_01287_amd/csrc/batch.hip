@@ -414,7 +414,8 @@ void build_batch(amg_ctx *h, int nsys, const amg_system *sys) {
         SetupPhase ph(h, "autotune");
         const bool reduced = p.precision != AMG_PREC_FP64;
         for (size_t l = 0; l < merged.size(); ++l)
-            if (merged[l].nA > 0 && (!reduced || l == 0)) autotune_level(h, merged[l], reduced);
+            if (merged[l].nA > 0 && (l == 0 || (!reduced && !sweeps_give_residual(h, merged[l]))))
+                autotune_level(h, merged[l]);
     }
 
     // level-0 layout of every system, chunk tables
@@ -641,9 +642,16 @@ void build_batch_spd(amg_ctx *h, int nsys, const amg_system *sys) {
                 if (rows.empty()) rows.push_back(0);
                 M.g_rowid.upload(rows, s);
                 M.d_cptr.upload(M.cptr, s);
-                if (M.Ag.nrows > 0)
-                    launch_gather_rows(M.A.np, M.Ag.nrows, M.g_rowid.p, M.A.rowptr.p, M.A.col.p, M.A.val.p,
-                                       M.A.nnz, M.Ag.rowptr.p, M.Ag.col.p, M.Ag.val.p, M.Ag.nnz, s);
+                if (M.Ag.nrows > 0) {
+                    M.sweep.build(M.cptr, rows, M.n, 4, s);
+                    M.sweep.rows.alloc(static_cast<size_t>(M.Ag.nrows));
+                    M.sweep.gcol.alloc(static_cast<size_t>(std::max<int64_t>(1, M.Ag.nnz)));
+                    launch_split_rows(M.A.np, M.Ag.nrows, M.g_rowid.p, M.sweep.place.p, M.A.rowptr.p, M.A.col.p,
+                                      M.A.val.p, M.A.nnz, M.Ag.rowptr.p, M.Ag.col.p, M.Ag.val.p, M.Ag.nnz,
+                                      M.sweep.rows.p, M.sweep.gcol.p, s);
+                    M.shape = sweep_shape(M.Ag.nnz, M.Ag.nrows, ncol, M.mode == 3);
+                    M.mp.shape = sweep_shape(M.Ag.nnz, M.Ag.nrows, ncol, false);
+                }
             }
         }
         // systems ending on this level: their coarsest inverses, as 3 n x 3 n
@@ -697,7 +705,8 @@ void build_batch_spd(amg_ctx *h, int nsys, const amg_system *sys) {
         SetupPhase ph(h, "autotune");
         const bool reduced = p.precision != AMG_PREC_FP64;
         for (size_t l = 0; l < merged.size(); ++l)
-            if (merged[l].nA > 0 && (!reduced || l == 0)) autotune_level(h, merged[l], reduced);
+            if (merged[l].nA > 0 && (l == 0 || (!reduced && !sweeps_give_residual(h, merged[l]))))
+                autotune_level(h, merged[l]);
     }
     // level-0 layout of every system (velocity ranges only), chunk tables
     h->nsys = nsys;

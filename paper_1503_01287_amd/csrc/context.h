@@ -13,6 +13,7 @@
 #include "learn.h"
 #include "mixed.h"
 #include "saddle.h"
+#include "sweep.h"
 #include "tail.h"
 #include "vanka.h"
 
@@ -33,6 +34,8 @@ struct LevelMP {
     int G = 16, Gg = 16;           // lanes per row of the reduced-precision A / grouped-A kernels
     int trip = 1, tripg = 1;       // their entries per lane and loop trip (1, 2, 4), chosen by the tuner
     int xcd = 0;                   // per-XCD contiguous rows in the colour sweeps (as Level::gs_xcd)
+    SweepShape shape;              // of its one-launch sweeps
+    bool by_colour = false;        // as Level::by_colour
     DevBuf<float> a32, ag32;       // FP32 planes
     DevBuf<uint16_t> a16, ag16;    // BF16 planes (values / row scale)
     DevBuf<float> scale;           // BF16: scale of every scalar row
@@ -82,6 +85,33 @@ struct DenseSegs {
     }
 };
 
+// Buffers of a level's one-launch sweeps in one precision (k_sweep.hip).
+struct SweepBuf {
+    DevBuf<int> ctl;
+    DevBuf<char> xg;
+    int64_t half = 0;
+    // nodes: places in xg; stride: values per place
+    void build(int kind, int64_t nodes, int stride, hipStream_t s);
+};
+
+// What the one-launch sweeps need beside a level's grouped rows.
+struct SweepData {
+    int ncolors = 0;                   // 0: none
+    int64_t places = 0;                // places in xg
+    DevBuf<int> place;                 // per node: its place in xg (-1: not swept)
+    DevBuf<int> cptr, base;            // grouped rows of a colour; its first place in xg
+    DevBuf<int4> rows;                 // grouped rows' descriptors (SweepArgs::rows)
+    DevBuf<int> gcol;                  // places of the entries' columns
+    DevBuf<int> tpre;                  // first tile of a colour, for every tile size
+    int ntiles[SWEEP_TILE_SIZES] = {};
+    SweepBuf f64, f32;
+    // tables of the colours cptr over the nodes rowid[0 .. cptr.back()) of n,
+    // and the FP64 buffers; stride: values per place
+    void build(const std::vector<int> &cptr, const std::vector<int> &rowid, int n, int stride, hipStream_t s);
+    bool usable() const { return ncolors > 0 && ncolors <= SWEEP_MAX_COLOURS; }
+    void fill(SweepArgs &a, const SweepShape &q, const SweepBuf &buf) const;
+};
+
 // One level of the scalar hierarchy of a Braess-Sarazin Schur complement
 // S = C + B A_hat^{-1} B^T (natural row order, rows grouped by colour
 // through `rowid`).
@@ -93,6 +123,8 @@ struct SchurLevel {
     DevBuf<double> dinv;         // 1 / S_ii
     std::vector<int> cptr;       // rows of colour c: rowid[cptr[c] .. cptr[c+1])
     DevBuf<int> rowid;
+    SweepData sweep;
+    SweepShape shape;            // of its sweeps
     DMat Sg;                     // the smoothed rows of S in the order rowid (colour sweeps)
     DevBuf<double> x, b, r;
     DevBuf<float> s32, sg32, dinv32, x32, b32, r32;  // reduced-precision cycle
@@ -157,6 +189,9 @@ struct Level {
     std::vector<int64_t> colour_nnz;  // stored entries in the rows of colour c
     DMat Ag;                  // rows of A grouped by colour
     DevBuf<int> g_rowid;      // node of grouped row g
+    SweepData sweep;
+    SweepShape shape;         // of its one-launch sweeps
+    bool by_colour = false;   // one launch per colour instead (a forced launch shape)
     DevBuf<int> d_cptr;       // cptr on the device (tail kernel)
     // transfer between this level and the next coarser one
     DMat P, R;                // P: n x n_c scalar, R = P^T
@@ -377,15 +412,21 @@ double jacobi_omega(const amg_ctx *h, int l);
 void setup_tail(amg_ctx *h);
 // lanes per row for a row kernel from the mean entries per row (4..64)
 int lanes_for(int64_t nnz, int nrows);
-// setup-time tuner of a level's FP64 kernels (lanes, loop form, XCD placement)
-// natural_only: the natural-order kernels only (not the colour sweeps)
-void autotune_level(amg_ctx *h, Level &L, bool natural_only = false);
+// setup-time tuner of a level's FP64 natural-order kernels (lanes, loop form)
+void autotune_level(amg_ctx *h, Level &L);
+// the level's cycle runs no natural-order residual: its one-launch
+// pre-smoothing sweeps leave all of it but the entries of later colours
+inline bool sweeps_give_residual(const amg_ctx *h, const Level &L) {
+    return h->prm.smoother == AMG_SMOOTH_GS && h->prm.pre > 0 && L.sweep.usable();
+}
 // first level covered by the SPD hierarchy's assembled coarse end, or -1
 int dense_tail_level(const amg_ctx *h);
 // evict the GPU caches before a tuner's timed run: inside a cycle a level's
 // operator is read after the finer levels' passes have replaced it in the
 // caches, so the tuners time kernels on cold data
 void evict_caches(amg_ctx *h);
+// the shape of a level's sweeps: rows of `nnz / nrows` entries, half of which a sweep has changed
+SweepShape sweep_shape(int64_t nnz, int nrows, int ncolors, bool fp64_blocks);
 // q.Sg from q.S, q.rowid and q.cptr
 void group_schur_rows(SchurLevel &q, hipStream_t s);
 // FP32 copy of the assembled coarse-end operator (reduced-precision cycle)

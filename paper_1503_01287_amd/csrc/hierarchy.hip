@@ -237,6 +237,71 @@ static void check_system(const amg_system *sys) {
     }
 }
 
+void SweepBuf::build(int kind, int64_t nodes, int stride, hipStream_t s) {
+    half = std::max<int64_t>(SWEEP_PAD, nodes) * stride;
+    const std::vector<int> z(SWEEP_CTL_INTS, 0);
+    ctl.upload(z, s);
+    xg.alloc(static_cast<size_t>(2 * half) * (kind == SWEEP_F64 ? 8 : 4));
+    launch_sweep_absent(kind, xg.p, 2 * half, s);
+}
+
+void SweepData::build(const std::vector<int> &cp, const std::vector<int> &rowid, int n, int stride, hipStream_t s) {
+    const int nc = static_cast<int>(cp.size()) - 1;
+    ncolors = nc;
+    std::vector<int> bs(nc + 1, 0), pl(std::max(1, n), -1), tp;
+    for (int c = 0; c < nc; ++c) {
+        const int rows = cp[c + 1] - cp[c];
+        bs[c + 1] = bs[c] + (rows + SWEEP_PAD - 1) / SWEEP_PAD * SWEEP_PAD;
+        for (int g = cp[c]; g < cp[c + 1]; ++g) pl[rowid[g]] = bs[c] + g - cp[c];
+    }
+    places = bs[nc];
+    for (int t = 0; t < SWEEP_TILE_SIZES; ++t) {
+        const int tr = (SWEEP_THREADS / 64) << t;
+        int at = 0;
+        for (int c = 0; c <= nc; ++c) {
+            tp.push_back(at);
+            if (c < nc) at += (cp[c + 1] - cp[c] + tr - 1) / tr;
+        }
+        ntiles[t] = at;
+    }
+    place.upload(pl, s);
+    cptr.upload(cp, s);
+    base.upload(bs, s);
+    tpre.upload(tp, s);
+    f64.build(SWEEP_F64, places, stride, s);
+}
+
+void SweepData::fill(SweepArgs &a, const SweepShape &q, const SweepBuf &buf) const {
+    int t = 0;
+    while (t < SWEEP_TILE_SIZES && (SWEEP_THREADS / 64) << t != q.tile_rows()) ++t;
+    AMG_REQUIRE(t < SWEEP_TILE_SIZES && buf.ctl.n > 0, AMG_EINVAL, "sweep: bad tile size or no buffers");
+    a.ncolors = ncolors;
+    a.ntiles = ntiles[t];
+    a.tpre = tpre.p + static_cast<int64_t>(t) * (ncolors + 1);
+    a.cptr = cptr.p;
+    a.base = base.p;
+    a.rows = rows.p;
+    a.gcol = gcol.p;
+    a.xg = buf.xg.p;
+    a.xg_half = buf.half;
+    a.ctl = buf.ctl.p;
+}
+
+// Lanes: a row's entries of the swept side in one trip of its lanes, which
+// take two entries each before the wait (FP64 blocks one: registers), so the
+// mean row sets G for FP64 blocks and half of it otherwise. us per sweep at
+// G / the next smaller or larger: elasticity 16^3 level 1 FP64 79 (64) / 103
+// (32), 32^3 level 0 FP32 141 (16) / 147 (32). Workgroups: enough for five
+// colours, since those further ahead only poll (16^3 level 1 BF16: 60 us with
+// 5 colours' worth, 64 with 3, 70 with 256 workgroups), at most one to a CU.
+SweepShape sweep_shape(int64_t nnz, int nrows, int ncolors, bool fp64_blocks) {
+    SweepShape q;
+    q.G = std::max(8, lanes_for(fp64_blocks ? nnz : nnz / 2, nrows));
+    const int per_colour = nrows / std::max(1, ncolors) / q.tile_rows() + 1;
+    q.grid = std::min(256, std::max(24, 5 * per_colour));
+    return q;
+}
+
 static void setup_smoother(amg_ctx *h, Level &L) {
     hipStream_t s = h->stream;
     const int nb = L.mode == 3 ? 9 : 1;
@@ -273,10 +338,15 @@ static void setup_smoother(amg_ctx *h, Level &L) {
     L.Ag.val.alloc(static_cast<size_t>(L.A.nnz) * L.A.np);
     L.g_rowid.upload(order, s);
     L.d_cptr.upload(L.cptr, s);
-    launch_gather_rows(L.A.np, L.n, L.g_rowid.p, L.A.rowptr.p, L.A.col.p, L.A.val.p, L.A.nnz, L.Ag.rowptr.p,
-                       L.Ag.col.p, L.Ag.val.p, L.Ag.nnz, s);
+    L.sweep.build(L.cptr, order, L.n, 4, s);
+    L.sweep.rows.alloc(static_cast<size_t>(L.n));
+    L.sweep.gcol.alloc(static_cast<size_t>(L.A.nnz));
+    launch_split_rows(L.A.np, L.n, L.g_rowid.p, L.sweep.place.p, L.A.rowptr.p, L.A.col.p, L.A.val.p, L.A.nnz,
+                      L.Ag.rowptr.p, L.Ag.col.p, L.Ag.val.p, L.Ag.nnz, L.sweep.rows.p, L.sweep.gcol.p, s);
     AMG_HIP(hipStreamSynchronize(s));
     L.Gg = L.G;
+    L.shape = sweep_shape(L.Ag.nnz, L.Ag.nrows, ncol, L.mode == 3);
+    L.mp.shape = sweep_shape(L.Ag.nnz, L.Ag.nrows, ncol, false);
 }
 
 // Autotuner: lanes per row for the level's row kernels, measured with HIP
@@ -305,12 +375,16 @@ void group_schur_rows(SchurLevel &q, hipStream_t s) {
     q.Sg.rowptr.upload(grp, s);
     q.Sg.col.alloc(std::max<int64_t>(1, q.Sg.nnz));
     q.Sg.val.alloc(std::max<int64_t>(1, q.Sg.nnz));
-    launch_gather_rows(1, m, q.rowid.p, q.S.rowptr.p, q.S.col.p, q.S.val.p, q.S.nnz, q.Sg.rowptr.p, q.Sg.col.p,
-                       q.Sg.val.p, q.Sg.nnz, s);
+    q.sweep.build(q.cptr, order, q.S.nrows, 1, s);
+    q.sweep.rows.alloc(static_cast<size_t>(m));
+    q.sweep.gcol.alloc(static_cast<size_t>(std::max<int64_t>(1, q.Sg.nnz)));
+    launch_split_rows(1, m, q.rowid.p, q.sweep.place.p, q.S.rowptr.p, q.S.col.p, q.S.val.p, q.S.nnz, q.Sg.rowptr.p,
+                      q.Sg.col.p, q.Sg.val.p, q.Sg.nnz, q.sweep.rows.p, q.sweep.gcol.p, s);
     AMG_HIP(hipStreamSynchronize(s));
+    q.shape = sweep_shape(q.Sg.nnz, m, static_cast<int>(q.cptr.size()) - 1, false);
 }
 
-void autotune_level(amg_ctx *h, Level &L, bool natural_only) {
+void autotune_level(amg_ctx *h, Level &L) {
     hipStream_t s = h->stream;
     const int cand[] = {8, 16, 32, 64};
     hipEvent_t e0, e1;
@@ -355,9 +429,9 @@ void autotune_level(amg_ctx *h, Level &L, bool natural_only) {
                     bestT = T;
                 }
             }
-        return std::make_tuple(bestG, bestT, best);
+        return std::make_pair(bestG, bestT);
     };
-    std::tie(L.G, L.trip, std::ignore) = pick(L.G, [&](int G, int P) {
+    std::tie(L.G, L.trip) = pick(L.G, [&](int G, int P) {
         RowArgs a;
         a.nrows = L.n;
         a.rowptr = L.A.rowptr.p;
@@ -370,35 +444,6 @@ void autotune_level(amg_ctx *h, Level &L, bool natural_only) {
         a.trip = P;
         return time_it([&] { launch_row(L.mode, OP_RESID, G, a, s); });
     });
-    if (!L.cptr.empty() && !natural_only) {
-        // a whole forward sweep, colour by colour, as the smoother runs it,
-        // with round-robin or per-XCD contiguous workgroup placement
-        auto sweep_time = [&](int G, int P, int xcd) {
-            return time_it([&] {
-                for (size_t c = 0; c + 1 < L.cptr.size(); ++c) {
-                    if (L.cptr[c + 1] == L.cptr[c]) continue;
-                    RowArgs a;
-                    a.nrows = L.cptr[c + 1] - L.cptr[c];
-                    a.rowptr = L.Ag.rowptr.p + L.cptr[c];
-                    a.col = L.Ag.col.p;
-                    a.val = L.Ag.val.p;
-                    a.nnz = L.Ag.nnz;
-                    a.rowid = L.g_rowid.p + L.cptr[c];
-                    a.x = L.t.p;
-                    a.b = L.b.p;
-                    a.y = L.t.p;
-                    a.dinv = L.dinv.p;
-                    a.dinv_n = L.n;
-                    a.xcd_chunks = xcd;
-                    a.trip = P;
-                    launch_row(L.mode, OP_GS, G, a, s);
-                }
-            });
-        };
-        float rr_ms = 0.f;
-        std::tie(L.Gg, L.tripg, rr_ms) = pick(L.Gg, [&](int G, int P) { return sweep_time(G, P, 0); });
-        L.gs_xcd = sweep_time(L.Gg, L.tripg, 1) < 0.95f * rr_ms ? 1 : 0;
-    }
     if (L.n_pres > 0 && L.B.nnz > 0) {
         // saddle levels: lanes of the B (1x3, pressure rows) and B^T (3x1,
         // velocity rows) kernels, same rule (heuristic kept unless >= 5% slower)
@@ -1234,10 +1279,12 @@ void build_hierarchy(amg_ctx *h, const amg_system *sys) {
                 setup_smoother(h, L);
                 if (h->saddle) saddle_setup_level(h, L);
             }
-            const bool used = reduced ? l == 0 : (tail_from < 0 || static_cast<int>(l) < tail_from);
+            const bool used =
+                reduced ? l == 0
+                        : ((tail_from < 0 || static_cast<int>(l) < tail_from) && (l == 0 || !sweeps_give_residual(h, L)));
             if (p.autotune && used) {
                 SetupPhase ph(h, "autotune");
-                autotune_level(h, L, reduced);
+                autotune_level(h, L);
             }
         }
     }

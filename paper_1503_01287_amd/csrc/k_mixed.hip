@@ -99,7 +99,8 @@ __global__ void __launch_bounds__(MBLOCK) k_row_mp(const RowArgsMP a) {
                 d0 = a.dinv[i];
             }
         }
-        if constexpr (NEEDS_OWN) own = OP == OP_JACOBI ? a.x[3 * i + c] : a.y[3 * i + c];
+        if constexpr (NEEDS_OWN) 
+            own = OP == OP_JACOBI ? a.x[3 * i + c] : (OP == OP_SPMV_ADD ? a.base[3 * i + c] : a.y[3 * i + c]);
         if constexpr (KIND == VAL_BF16) {
             if constexpr (MODE == 3) {
                 q0 = a.rscale[3 * i];

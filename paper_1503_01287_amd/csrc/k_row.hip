@@ -103,7 +103,8 @@ __global__ void __launch_bounds__(BLOCK) k_row(const RowArgs a) {
                 d0 = a.dinv[i];
             }
         }
-        if constexpr (NEEDS_OWN) own = (OP == OP_SPMV_ADD || OP == OP_GS) ? a.y[3 * i + c] : a.x[3 * i + c];
+        if constexpr (NEEDS_OWN)
+            own = OP == OP_SPMV_ADD ? a.base[3 * i + c] : (OP == OP_GS ? a.y[3 * i + c] : a.x[3 * i + c]);
     }
     double s0 = 0.0, s1 = 0.0, s2 = 0.0;
     if (active) {

@@ -31,7 +31,8 @@ __global__ void __launch_bounds__(SB) k_blk(const BlkArgsT<T> a) {
     T bo = T(0), yo = T(0), ds = T(0);
     if (ep) {
         if constexpr (OP == BLK_RESID || OP == BLK_SGS_P) bo = a.b[o];
-        if constexpr (OP == BLK_ADD || OP == BLK_SUB) yo = a.y[o];
+        if constexpr (OP == BLK_ADD) yo = a.base ? a.base[o] : a.y[o];
+        if constexpr (OP == BLK_SUB) yo = a.y[o];
         if constexpr (OP == BLK_SGS_P) yo = a.y_zero ? T(0) : a.y[o];
         if constexpr (OP == BLK_SGS_P) ds = a.dscale[i];
         if constexpr (OP == BLK_ADD_SCALED) {

@@ -17,7 +17,7 @@ namespace amgp2 {
 // group have reduced s = (A x)_i (3 components).
 enum RowOp : int {
     OP_SPMV = 0,      // y_i = s
-    OP_SPMV_ADD = 1,  // y_i += s                         (prolongation x += P e)
+    OP_SPMV_ADD = 1,  // y_i = base_i + s                 (prolongation x + P e)
     OP_RESID = 2,     // y_i = b_i - s                    (residual)
     OP_JACOBI = 3,    // y_i = x_i + omega D_i^{-1}(b_i - s)   (damped block Jacobi)
     OP_GS = 4,        // x_i += D_i^{-1}(b_i - s), in place   (Gauss-Seidel, one colour)
@@ -34,6 +34,7 @@ struct RowArgs {
     const double *x = nullptr;      // vector the operator multiplies
     const double *b = nullptr;      // right-hand side (RESID, JACOBI, GS)
     double *y = nullptr;            // output (for GS: the vector updated in place)
+    const double *base = nullptr;   // SPMV_ADD: what s is added to (may be y)
     const double *dinv = nullptr;   // inverted diagonal blocks, planes of stride dinv_n
     int64_t dinv_n = 0;
     double omega = 1.0;

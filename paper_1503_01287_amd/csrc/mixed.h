@@ -23,6 +23,7 @@ struct RowArgsMP {
     const float *x = nullptr;
     const float *b = nullptr;
     float *y = nullptr;
+    const float *base = nullptr;    // OP_SPMV_ADD: what the product is added to (may be y)
     const float *dinv = nullptr;
     int64_t dinv_n = 0;
     float omega = 1.f;

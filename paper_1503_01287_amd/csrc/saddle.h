@@ -12,7 +12,7 @@ namespace amgp2 {
 
 enum BlkOp : int {
     BLK_SPMV = 0,   // y = s
-    BLK_ADD = 1,    // y += s
+    BLK_ADD = 1,    // y = base + s (y += s without a base)
     BLK_SUB = 2,    // y -= s
     BLK_RESID = 3,  // y = b - s
     BLK_SGS_P = 4,  // (1x3 rows of B) y_p += omega * dscale_p * (s - b_p)
@@ -30,6 +30,7 @@ struct BlkArgsT {
     const T *x = nullptr;     // bc components per column node
     const T *b = nullptr;     // br components per row
     T *y = nullptr;
+    const T *base = nullptr;  // BLK_ADD
     const T *dscale = nullptr;
     T omega = 1;
     // optional scalar operator on the same rows (1x3 B rows only, with

@@ -127,11 +127,43 @@ static void jacobi_step(amg_ctx *h, int l, const double *b, double *x, bool zero
     launch_copy(x, L.t.p, 3 * static_cast<int64_t>(L.nA), h->stream);
 }
 
+static bool one_launch_sweeps(const amg_ctx *h, const Level &L) {
+    return h->prm.smoother == AMG_SMOOTH_GS && L.sweep.usable() && !L.by_colour;
+}
+
 // One block Gauss-Seidel sweep by colours. x_zero: x is zero on entry (and
 // its buffer holds the zeros), so the first colour's rows see only zero
 // neighbours: x_i = D_i^{-1} b_i without reading their matrix rows.
-static void gs_sweep(amg_ctx *h, int l, const double *b, double *x, bool forward, bool x_zero) {
+// in_t: the iterate on entry is in L.t (one-launch sweeps read it there).
+// part: see SweepArgs::part (one-launch forward sweeps).
+static SweepArgs sweep_args(Level &L, const double *b, double *x, bool forward, bool x_zero, double *part) {
+    SweepArgs a;
+    L.sweep.fill(a, L.shape, L.sweep.f64);
+    a.col = L.Ag.col.p;
+    a.val = L.Ag.val.p;
+    a.nnz = L.Ag.nnz;
+    a.dinv = L.dinv.p;
+    a.dinv_n = L.n;
+    a.b = b;
+    a.x_old = L.t.p;
+    a.x = x;
+    a.part = part;
+    a.forward = forward ? 1 : 0;
+    a.x_zero = x_zero ? 1 : 0;
+    return a;
+}
+
+static void gs_sweep(amg_ctx *h, int l, const double *b, double *x, bool forward, bool x_zero, bool in_t,
+                     double *part) {
     Level &L = h->lv[l];
+    if (one_launch_sweeps(h, L)) {
+        if (!x_zero && !in_t) launch_copy(L.t.p, x, 3 * static_cast<int64_t>(L.nA), h->stream);
+        const double rows = L.Ag.nrows;
+        ProfScope ps(h, tag("gs", l), row_bytes(L.Ag, x_zero ? L.Ag.nnz / 2 : L.Ag.nnz, L.Ag.nrows) +
+                                          rows * (8.0 + 24.0 + 48.0 + (L.mode == 3 ? 72.0 : 8.0)));
+        launch_sweep(L.mode, SWEEP_F64, L.shape, sweep_args(L, b, x, forward, x_zero, part), h->stream);
+        return;
+    }
     const int ncol = static_cast<int>(L.cptr.size()) - 1;
     const int nb = L.mode == 3 ? 9 : 1;
     for (int q = 0; q < ncol; ++q) {
@@ -166,19 +198,27 @@ static void gs_sweep(amg_ctx *h, int l, const double *b, double *x, bool forward
     }
 }
 
-// zero_init: x is zero on entry; filled: its buffer already holds the zeros
-void smooth(amg_ctx *h, int l, const double *b, double *x, bool pre, bool zero_init, bool filled) {
+// zero_init: x is zero on entry; filled: its buffer already holds the zeros;
+// in_t: the iterate on entry is in L.t; part: written by the last sweep
+static void smooth_from(amg_ctx *h, int l, const double *b, double *x, bool pre, bool zero_init, bool filled,
+                        bool in_t, double *part) {
     const amg_params &p = h->prm;
     const int steps = pre ? p.pre : p.post;
     Level &L = h->lv[l];
-    const bool need_fill = zero_init && !filled && (steps == 0 || p.smoother != AMG_SMOOTH_JA);
+    const bool need_fill =
+        zero_init && !filled && (steps == 0 || (p.smoother != AMG_SMOOTH_JA && !(pre && one_launch_sweeps(h, L))));
     if (need_fill) launch_fill(x, 0.0, 3 * static_cast<int64_t>(L.nA), h->stream);
     for (int k = 0; k < steps; ++k) {
         if (p.smoother == AMG_SMOOTH_JA)
             jacobi_step(h, l, b, x, zero_init && k == 0);
         else
-            gs_sweep(h, l, b, x, pre || h->post_forward, pre && zero_init && k == 0);
+            gs_sweep(h, l, b, x, pre || h->post_forward, pre && zero_init && k == 0, in_t && k == 0,
+                     k == steps - 1 ? part : nullptr);
     }
+}
+
+void smooth(amg_ctx *h, int l, const double *b, double *x, bool pre, bool zero_init, bool filled) {
+    smooth_from(h, l, b, x, pre, zero_init, filled, false, nullptr);
 }
 
 static void coarse_solve(amg_ctx *h, const double *b, double *x) {
@@ -226,8 +266,16 @@ static void cycle(amg_ctx *h, int l, const double *b, double *x, bool x_zero, bo
         run_dense_tail(h, b, x);
         return;
     }
-    smooth(h, l, b, x, true, x_zero, filled);
-    residual(h, l, b, x, L.r.p, L.nA);
+    if (h->prm.pre > 0 && one_launch_sweeps(h, L)) {
+        // the last pre-smoothing sweep leaves all of the residual but the
+        // entries of later colours
+        smooth_from(h, l, b, x, true, x_zero, filled, false, L.r.p);
+        ProfScope ps(h, tag("resid", l), row_bytes(L.Ag, L.Ag.nnz / 2, L.Ag.nrows) + 3.0 * L.Ag.nrows * 24.0);
+        launch_later(L.mode, SWEEP_F64, L.Ag.nrows, L.shape, sweep_args(L, b, x, true, x_zero, L.r.p), h->stream);
+    } else {
+        smooth_from(h, l, b, x, true, x_zero, filled, false, nullptr);
+        residual(h, l, b, x, L.r.p, L.nA);
+    }
     Level &C = h->lv[l + 1];
     {
         // b_{l+1} = P^T r; the same pass zeroes x_{l+1} for the recursion
@@ -246,14 +294,17 @@ static void cycle(amg_ctx *h, int l, const double *b, double *x, bool x_zero, bo
         const int nu = std::max(1, h->prm.nu);
         for (int k = 0; k < nu; ++k) cycle(h, l + 1, C.b.p, C.x.p, k == 0, k == 0);
     }
+    // one-launch sweeps read their iterate from L.t: the prolongation puts it there
+    const bool to_t = h->prm.post > 0 && one_launch_sweeps(h, L);
     {
         RowArgs a = row_args(L.P);
         a.x = C.x.p;
-        a.y = x;
+        a.base = x;
+        a.y = to_t ? L.t.p : x;
         ProfScope ps(h, tag("prolong", l), row_bytes(L.P, L.P.nnz, L.P.nrows) + 3.0 * (2.0 * L.n + C.n) * 8.0);
         launch_row(1, OP_SPMV_ADD, L.Gp, a, h->stream);
     }
-    smooth(h, l, b, x, false, false, false);
+    smooth_from(h, l, b, x, false, false, false, to_t, nullptr);
 }
 
 void vcycle(amg_ctx *h, int l, const double *b, double *x) { cycle(h, l, b, x, true, false); }

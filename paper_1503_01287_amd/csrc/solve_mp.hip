@@ -79,35 +79,6 @@ static void autotune_mp(amg_ctx *h, Level &L) {
         a.trip = P;
         return time_it([&] { launch_row_mp(L.mode, OP_RESID, G, M.kind, a, s); });
     });
-    if (!L.cptr.empty()) {
-        // a whole forward sweep, colour by colour, as the smoother runs it;
-        // then per-XCD contiguous rows for the chosen kernel
-        auto sweep_time = [&](int G, int P, int xcd) {
-            return time_it([&] {
-                for (size_t c = 0; c + 1 < L.cptr.size(); ++c) {
-                    if (L.cptr[c + 1] == L.cptr[c]) continue;
-                    RowArgsMP a;
-                    a.nrows = L.cptr[c + 1] - L.cptr[c];
-                    a.rowptr = L.Ag.rowptr.p + L.cptr[c];
-                    a.col = L.Ag.col.p;
-                    a.val = M.agval();
-                    a.rscale = M.scale.p;
-                    a.nnz = L.Ag.nnz;
-                    a.rowid = L.g_rowid.p + L.cptr[c];
-                    a.x = M.t.p;
-                    a.b = M.b.p;
-                    a.y = M.t.p;
-                    a.dinv = M.dinv.p;
-                    a.dinv_n = L.n;
-                    a.xcd_chunks = xcd;
-                    a.trip = P;
-                    launch_row_mp(L.mode, OP_GS, G, M.kind, a, s);
-                }
-            });
-        };
-        M.Gg = pick(M.Gg, M.tripg, [&](int G, int P) { return sweep_time(G, P, 0); });
-        M.xcd = sweep_time(M.Gg, M.tripg, 1) < 0.95f * sweep_time(M.Gg, M.tripg, 0) ? 1 : 0;
-    }
     AMG_HIP(hipEventDestroy(e0));
     AMG_HIP(hipEventDestroy(e1));
 }
@@ -146,6 +117,7 @@ void build_mixed(amg_ctx *h) {
                                    M.ag16.p, s);
             }
         }
+        if (L.sweep.usable()) L.sweep.f32.build(SWEEP_F32, L.sweep.places, 4, s);
         M.dinv.alloc(L.dinv.n);
         launch_to_f32(L.dinv.p, M.dinv.p, static_cast<int64_t>(L.dinv.n), s);
         M.pval.alloc(L.P.nnz);
@@ -156,9 +128,11 @@ void build_mixed(amg_ctx *h) {
         // kernels' tuned choice, so that its result does not inherit their
         // timing noise
         M.G = M.Gg = lanes_for(L.A.nnz, L.n);
-        // (not the levels inside the assembled coarse end: those kernels do
-        // not run in the cycle)
-        if (h->prm.autotune && (h->dense_start < 0 || static_cast<int>(l) < h->dense_start)) autotune_mp(h, L);
+        // (not the levels inside the assembled coarse end, nor those whose
+        // sweeps give the residual: those kernels do not run in the cycle)
+        if (h->prm.autotune && (h->dense_start < 0 || static_cast<int>(l) < h->dense_start) &&
+            !sweeps_give_residual(h, L))
+            autotune_mp(h, L);
     }
     refresh_tail_f32(h);
 }
@@ -193,6 +167,7 @@ void build_saddle_mp(amg_ctx *h) {
             q.x32.alloc(m);
             q.b32.alloc(m);
             q.r32.alloc(m);
+            if (q.sweep.usable()) q.sweep.f32.build(SWEEP_F32, q.sweep.places, 1, s);
         }
     }
     AMG_HIP(hipStreamSynchronize(s));
@@ -284,8 +259,40 @@ static float *jacobi_mp(amg_ctx *h, int l, const float *b, float *x, bool zero) 
     return x;
 }
 
-static void gs_mp(amg_ctx *h, int l, const float *b, float *x, bool forward, bool x_zero) {
+static bool one_launch_sweeps(const amg_ctx *h, const Level &L) {
+    return h->prm.smoother == AMG_SMOOTH_GS && L.sweep.usable() && !L.mp.by_colour;
+}
+
+static SweepArgs sweep_args(Level &L, const float *b, float *x, bool forward, bool x_zero, float *part) {
+    SweepArgs a;
+    L.sweep.fill(a, L.mp.shape, L.sweep.f32);
+    a.col = L.Ag.col.p;
+    a.val = L.mp.agval();
+    a.rscale = L.mp.scale.p;
+    a.nnz = L.Ag.nnz;
+    a.dinv = L.mp.dinv.p;
+    a.dinv_n = L.n;
+    a.b = b;
+    a.x_old = L.mp.t.p;
+    a.x = x;
+    a.part = part;
+    a.forward = forward ? 1 : 0;
+    a.x_zero = x_zero ? 1 : 0;
+    return a;
+}
+static int sweep_kind(const Level &L) { return L.mp.kind == VAL_F32 ? SWEEP_F32 : SWEEP_BF16; }
+
+// in_t: the iterate on entry is in mp.t (one-launch sweeps read it there);
+// part: see SweepArgs::part (one-launch forward sweeps)
+static void gs_mp(amg_ctx *h, int l, const float *b, float *x, bool forward, bool x_zero, bool in_t, float *part) {
     Level &L = h->lv[l];
+    if (one_launch_sweeps(h, L)) {
+        if (!x_zero && !in_t) launch_copy_f32(L.mp.t.p, x, 3 * static_cast<int64_t>(L.nA), h->stream);
+        ProfScope ps(h, tag("gs", l), mat_bytes(L, x_zero ? L.Ag.nnz / 2 : L.Ag.nnz, L.Ag.nrows) +
+                                          L.Ag.nrows * (4.0 + 12.0 + 24.0 + (L.mode == 3 ? 36.0 : 4.0)));
+        launch_sweep(L.mode, sweep_kind(L), L.mp.shape, sweep_args(L, b, x, forward, x_zero, part), h->stream);
+        return;
+    }
     const int ncol = static_cast<int>(L.cptr.size()) - 1;
     const int nb = L.mode == 3 ? 9 : 1;
     for (int q = 0; q < ncol; ++q) {
@@ -318,17 +325,20 @@ static void gs_mp(amg_ctx *h, int l, const float *b, float *x, bool forward, boo
 }
 
 // returns the buffer holding x_l afterwards (Jacobi steps alternate buffers)
-static float *smooth_mp(amg_ctx *h, int l, const float *b, float *x, bool pre, bool zero_init, bool filled) {
+static float *smooth_mp(amg_ctx *h, int l, const float *b, float *x, bool pre, bool zero_init, bool filled,
+                        bool in_t = false, float *part = nullptr) {
     const amg_params &p = h->prm;
     const int steps = pre ? p.pre : p.post;
     Level &L = h->lv[l];
-    if (zero_init && !filled && (steps == 0 || p.smoother != AMG_SMOOTH_JA))
+    if (zero_init && !filled &&
+        (steps == 0 || (p.smoother != AMG_SMOOTH_JA && !(pre && one_launch_sweeps(h, L)))))
         launch_fill_f32(x, 0.f, 3 * static_cast<int64_t>(L.nA), h->stream);
     for (int k = 0; k < steps; ++k) {
         if (p.smoother == AMG_SMOOTH_JA)
             x = jacobi_mp(h, l, b, x, zero_init && k == 0);
         else
-            gs_mp(h, l, b, x, pre || h->post_forward, pre && zero_init && k == 0);
+            gs_mp(h, l, b, x, pre || h->post_forward, pre && zero_init && k == 0, in_t && k == 0,
+                  k == steps - 1 ? part : nullptr);
     }
     return x;
 }
@@ -379,8 +389,17 @@ static float *cycle_mp(amg_ctx *h, int l, const float *b, float *x, bool x_zero,
             launch_dense_gemv_f32(h->tail_dense32.p, h->tail_m, h->tail_ld, h->tail_nc, b, x, h->stream);
         return x;
     }
-    x = smooth_mp(h, l, b, x, true, x_zero, filled);
-    residual_mp(h, l, b, x, L.mp.r.p);
+    if (h->prm.pre > 0 && one_launch_sweeps(h, L)) {
+        // the last pre-smoothing sweep leaves all of the residual but the
+        // entries of later colours
+        x = smooth_mp(h, l, b, x, true, x_zero, filled, false, L.mp.r.p);
+        ProfScope ps(h, tag("resid", l), mat_bytes(L, L.Ag.nnz / 2, L.Ag.nrows) + 3.0 * L.Ag.nrows * 12.0);
+        launch_later(L.mode, sweep_kind(L), L.Ag.nrows, L.mp.shape, sweep_args(L, b, x, true, x_zero, L.mp.r.p),
+                     h->stream);
+    } else {
+        x = smooth_mp(h, l, b, x, true, x_zero, filled);
+        residual_mp(h, l, b, x, L.mp.r.p);
+    }
     Level &C = h->lv[l + 1];
     {
         RowArgsMP a;
@@ -403,6 +422,8 @@ static float *cycle_mp(amg_ctx *h, int l, const float *b, float *x, bool x_zero,
         const int nu = std::max(1, h->prm.nu);
         for (int k = 0; k < nu; ++k) e = cycle_mp(h, l + 1, C.mp.b.p, e, k == 0, k == 0);
     }
+    // one-launch sweeps read their iterate from mp.t: the prolongation puts it there
+    const bool to_t = h->prm.post > 0 && one_launch_sweeps(h, L);
     {
         RowArgsMP a;
         a.nrows = L.P.nrows;
@@ -411,11 +432,12 @@ static float *cycle_mp(amg_ctx *h, int l, const float *b, float *x, bool x_zero,
         a.val = L.mp.pval.p;
         a.nnz = L.P.nnz;
         a.x = e;
-        a.y = x;
+        a.base = x;
+        a.y = to_t ? L.mp.t.p : x;
         ProfScope ps(h, tag("prolong", l), L.P.nnz * 8.0 + 3.0 * (2.0 * L.n + C.n) * 4.0);
         launch_row_mp(1, OP_SPMV_ADD, L.Gp, VAL_F32, a, h->stream);
     }
-    return smooth_mp(h, l, b, x, false, false, false);
+    return smooth_mp(h, l, b, x, false, false, false, to_t);
 }
 
 void precondition_mp(amg_ctx *h, const double *r, double *z) {

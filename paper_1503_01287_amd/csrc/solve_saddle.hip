@@ -179,6 +179,7 @@ static void prolong_u(amg_ctx *h, int l, const double *xc, double *x) {
     a.val = L.P.val.p;
     a.nnz = L.P.nnz;
     a.x = xc;
+    a.base = x;
     a.y = x;
     launch_row(1, OP_SPMV_ADD, L.Gp, a, h->stream);
 }
@@ -191,6 +192,7 @@ static void prolong_u(amg_ctx *h, int l, const float *xc, float *x) {
     a.val = L.mp.pval.p;
     a.nnz = L.P.nnz;
     a.x = xc;
+    a.base = x;
     a.y = x;
     launch_row_mp(1, OP_SPMV_ADD, L.Gp, VAL_F32, a, h->stream);
 }
@@ -290,6 +292,27 @@ static void sgs_step(amg_ctx *h, int l, const T *b, T *x, bool x_zero) {
     launch_blk<T>(1, 3, BLK_SGS_P, L.Gb, bb, h->stream);
 }
 
+// A Gauss-Seidel sweep of a Schur level from x_old (another buffer than x)
+// into x, backward; without x_old forward from zero, then the residual in sr.
+template <typename T>
+static void schur_sweep(amg_ctx *h, SchurLevel &q, const T *b, const T *x_old, T *x) {
+    const int kind = sizeof(T) == 8 ? SWEEP_F64 : SWEEP_F32;
+    SweepArgs a;
+    q.sweep.fill(a, q.shape, sizeof(T) == 8 ? q.sweep.f64 : q.sweep.f32);
+    a.col = q.Sg.col.p;
+    a.val = SV<T>::Sg(q);
+    a.nnz = q.Sg.nnz;
+    a.dinv = SV<T>::sdinv(q);
+    a.dinv_n = q.S.nrows;
+    a.b = b;
+    a.x_old = x_old;
+    a.x = x;
+    a.forward = a.x_zero = x_old ? 0 : 1;
+    if (!x_old) a.part = SV<T>::sr(q);
+    launch_sweep(SWEEP_SCALAR1, kind, q.shape, a, h->stream);
+    if (!x_old) launch_later(SWEEP_SCALAR1, kind, q.Sg.nrows, q.shape, a, h->stream);
+}
+
 // Scalar V(1,1) cycle on level k of the Schur hierarchy of saddle level l,
 // from a zero guess: Gauss-Seidel colour by colour on the smoothed rows
 // (forward before the coarse correction, backward after it), restriction
@@ -308,16 +331,21 @@ static void schur_vcycle(amg_ctx *h, int l, int k, const T *b, T *x) {
         launch_dense_segs<T>(q.dseg.view(), static_cast<const T *>(nullptr), b, static_cast<T *>(nullptr), x, s);
     if (q.nA == 0) return;
     const int nc = static_cast<int>(q.cptr.size()) - 1;
-    fillv(x, q.nA, s);
-    for (int c = 0; c < nc; ++c)
-        launch_scalar_gs<T>(q.cptr[c + 1] - q.cptr[c], q.Sg.rowptr.p + q.cptr[c], q.Sg.col.p, SV<T>::Sg(q),
-                            q.rowid.p + q.cptr[c], SV<T>::sdinv(q), b, x, q.G, s);
-    BlkArgsT<T> ra = blkT<T>(q.S, SV<T>::S(q));
-    ra.nrows = q.nA;
-    ra.x = x;
-    ra.b = b;
-    ra.y = SV<T>::sr(q);
-    launch_blk<T>(1, 1, BLK_RESID, q.G, ra, s);
+    const bool one = q.sweep.usable();
+    if (one) {
+        schur_sweep<T>(h, q, b, nullptr, x);
+    } else {
+        fillv(x, q.nA, s);
+        for (int c = 0; c < nc; ++c)
+            launch_scalar_gs<T>(q.cptr[c + 1] - q.cptr[c], q.Sg.rowptr.p + q.cptr[c], q.Sg.col.p, SV<T>::Sg(q),
+                                q.rowid.p + q.cptr[c], SV<T>::sdinv(q), b, x, q.G, s);
+        BlkArgsT<T> ra = blkT<T>(q.S, SV<T>::S(q));
+        ra.nrows = q.nA;
+        ra.x = x;
+        ra.b = b;
+        ra.y = SV<T>::sr(q);
+        launch_blk<T>(1, 1, BLK_RESID, q.G, ra, s);
+    }
     const Level &V = h->lv[l + k];
     SchurLevel &n = sh.lv[k + 1];
     BlkArgsT<T> ht = blkT<T>(V.Ht, SV<T>::Ht(V));
@@ -327,9 +355,12 @@ static void schur_vcycle(amg_ctx *h, int l, int k, const T *b, T *x) {
     schur_vcycle<T>(h, l, k + 1, SV<T>::sb(n), SV<T>::sx(n));
     BlkArgsT<T> hh = blkT<T>(V.H, SV<T>::H(V));
     hh.x = SV<T>::sx(n);
-    hh.y = x;
+    // (a one-launch sweep reads its iterate from the residual's buffer)
+    hh.base = x;
+    hh.y = one ? SV<T>::sr(q) : x;
     launch_blk<T>(1, 1, BLK_ADD, V.Gh, hh, s);
-    for (int c = nc - 1; c >= 0; --c)
+    if (one) schur_sweep<T>(h, q, b, SV<T>::sr(q), x);
+    for (int c = one ? -1 : nc - 1; c >= 0; --c)
         launch_scalar_gs<T>(q.cptr[c + 1] - q.cptr[c], q.Sg.rowptr.p + q.cptr[c], q.Sg.col.p, SV<T>::Sg(q),
                             q.rowid.p + q.cptr[c], SV<T>::sdinv(q), b, x, q.G, s);
 }

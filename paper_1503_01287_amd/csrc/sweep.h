@@ -1,0 +1,68 @@
+// Gauss-Seidel sweeps over all colours of a level in one launch (k_sweep.hip).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+namespace amgp2 {
+
+// What an entry is: a 3x3 block, a scalar applied to 3-component vectors, or
+// a scalar applied to a scalar vector (Schur complements).
+enum SweepMode : int { SWEEP_BLOCK = 3, SWEEP_SCALAR3 = 1, SWEEP_SCALAR1 = 0 };
+enum SweepKind : int { SWEEP_F64 = 0, SWEEP_F32 = 1, SWEEP_BF16 = 2 };
+
+constexpr int SWEEP_THREADS = 1024;    // threads of a workgroup
+constexpr int SWEEP_MAX_COLOURS = 1023;
+constexpr int SWEEP_PAD = 32;         // a colour's range of the swept vector starts at a multiple of this many nodes
+// control words of a level's sweeps: ticket, exits, buffer in turn, given up
+constexpr int SWEEP_CTL_INTS = 128;
+
+// Grouped rows: a row's entries with earlier colours come first, then the
+// diagonal, then those with later colours.
+struct SweepArgs {
+    int ncolors = 0, ntiles = 0;
+    const int *cptr = nullptr;      // grouped rows of colour c
+    const int *tpre = nullptr;      // first tile of colour c (ncolors + 1)
+    const int *base = nullptr;      // first node of colour c in xg
+    const int4 *rows = nullptr;     // of grouped row g: first entry, diagonal, end, node
+    const int *col = nullptr;       // node of an entry's column
+    const int *gcol = nullptr;      // its place in xg
+    const void *val = nullptr;      // planes nnz apart
+    int64_t nnz = 0;
+    const void *dinv = nullptr;     // inverted diagonal blocks, planes dinv_n apart
+    int64_t dinv_n = 0;
+    const float *rscale = nullptr;  // BF16: scale of a scalar row
+    const void *b = nullptr;
+    const void *x_old = nullptr;    // the iterate on entry, another buffer than x (not read if x_zero)
+    void *x = nullptr;              // the iterate on return
+    void *xg = nullptr;             // swept values by colour, 4 (scalar vectors: 1) per node: two buffers,
+    int64_t xg_half = 0;            // xg_half values apart, the first one filled with "absent" before the first sweep
+    void *part = nullptr;           // if set: b - (entries of earlier colours and the diagonal) x
+    int forward = 1;
+    int x_zero = 0;                 // x is zero on entry (its buffer need not hold the zeros; forward only)
+    int *ctl = nullptr;             // SWEEP_CTL_INTS words of this level, zero before the first launch
+};
+
+// G lanes per row (8, 16, 32, 64), at most `grid` workgroups
+struct SweepShape {
+    int G = 16, grid = 256;
+    int tile_rows() const { return SWEEP_THREADS / G; }
+};
+constexpr int SWEEP_TILE_SIZES = 4;  // tiles of (SWEEP_THREADS / 64) << t rows
+
+// "absent" into both buffers of xg (n values in all, of the sweep's precision)
+void launch_sweep_absent(int kind, void *xg, int64_t n, hipStream_t s);
+void launch_sweep(int mode, int kind, const SweepShape &q, const SweepArgs &a, hipStream_t s);
+// part -= (entries of later colours) x on the nrows grouped rows: the residual
+// after a forward sweep with the same arguments
+void launch_later(int mode, int kind, int nrows, const SweepShape &q, const SweepArgs &a, hipStream_t s);
+
+// place[i]: node i's place in xg. Rows order[g] gathered into the grouped
+// copy with their entries split as SweepArgs wants them (a stable partition
+// by the columns' places); rows, gcol written with it.
+void launch_split_rows(int np, int nrows, const int *order, const int *place, const int *rowptr, const int *col,
+                       const double *val, int64_t nnz, const int *g_rowptr, int *g_col, double *g_val,
+                       int64_t g_nnz, int4 *rows, int *gcol, hipStream_t s);
+
+}  // namespace amgp2
