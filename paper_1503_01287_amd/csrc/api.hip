@@ -431,8 +431,7 @@ int amg_get_level_info(amg_handle h, int32_t level, amg_level_info *info) {
         info->trip_gs = h->mixed ? L.mp.tripg : L.tripg;
         info->lanes64_A = L.G;
         info->trip64_A = L.trip;
-        const int fs = h->tail_start >= 0 ? h->tail_start
-                       : h->dense_start >= 0 ? h->dense_start
+        const int fs = h->dense_start >= 0 ? h->dense_start
                                              : h->saddle_tail_from;
         info->fused = (fs >= 0 && level >= fs) ? 1 : 0;
         info->schur_levels = static_cast<int>(L.schur.lv.size());

@@ -302,14 +302,9 @@ struct amg_ctx {
     // coarsest level: explicit dense inverse
     amgp2::DevBuf<double> coarse_inv;
     int coarse_m = 0, coarse_nc = 1;
-    // single-workgroup tail: levels tail_start.. run in one kernel (-1: none)
-    int tail_start = -1;
-    amgp2::TailArgs tail_args;
-    amgp2::DevBuf<amgp2::TailLevel> tail_levels;
-    int tail_lds = 0;
-    double tail_bytes = 0.0;
-    // the V-cycle from level dense_start (>= 1) down, as an explicit
-    // operator x = T b (tail_m x tail_m, applied to tail_nc components)
+    // the cycle from level dense_start down and from zero (below level 0: all
+    // nu visits that its parent makes), as an explicit operator x = T b
+    // (tail_m x tail_m, applied to tail_nc components)
     int dense_start = -1;
     amgp2::DevBuf<double> tail_dense;
     int tail_m = 0, tail_nc = 1;

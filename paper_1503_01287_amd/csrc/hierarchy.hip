@@ -561,12 +561,11 @@ static void setup_coarsest(amg_ctx *h, Level &L) {
 
 // Descriptors of levels t..L for the tail kernel; returns the doubles of
 // level vectors one workgroup needs (x, b, r: 9 per node).
-static int tail_descriptors(amg_ctx *h, int t, DevBuf<TailLevel> &buf, TailArgs &a, double &algo) {
+static int tail_descriptors(amg_ctx *h, int t, DevBuf<TailLevel> &buf, TailArgs &a) {
     const amg_params &p = h->prm;
     const int L = static_cast<int>(h->lv.size()) - 1;
     std::vector<TailLevel> d(L - t + 1);
     int off = 0;
-    algo = 0.0;
     for (int k = t; k <= L; ++k) {
         Level &V = h->lv[k];
         TailLevel &q = d[k - t];
@@ -597,10 +596,7 @@ static int tail_descriptors(amg_ctx *h, int t, DevBuf<TailLevel> &buf, TailArgs 
         q.p_val = V.P.val.p;
         q.omega = h->level_omega.empty() ? p.omega
                                          : h->level_omega[std::min<size_t>(k, h->level_omega.size() - 1)];
-        const double mat = static_cast<double>(V.A.nnz) * (V.A.np * 8.0 + 4.0);
-        algo += (p.pre + p.post + 1) * mat + 2.0 * V.P.nnz * 12.0;
     }
-    algo += static_cast<double>(h->coarse_m) * h->coarse_m * 8.0;
     buf.upload(d, h->stream);
     AMG_HIP(hipStreamSynchronize(h->stream));
     a = TailArgs();
@@ -629,9 +625,20 @@ static int tail_descriptors(amg_ctx *h, int t, DevBuf<TailLevel> &buf, TailArgs 
 int dense_tail_level(const amg_ctx *h) {
     const amg_params &p = h->prm;
     // (both forms implement the symmetric cycle: forward pre-, backward post-smoothing)
-    if (h->saddle || h->nsys > 0 || !p.fuse_coarse || p.nu != 1 || h->post_forward) return -1;
+    if (h->saddle || h->nsys > 0 || !p.fuse_coarse || h->post_forward) return -1;
     if (p.smoother != AMG_SMOOTH_JA && p.smoother != AMG_SMOOTH_GS) return -1;
     const int L = static_cast<int>(h->lv.size()) - 1;
+    const bool fp64 = p.precision == AMG_PREC_FP64;
+    if (L == 0 || L + 1 > TAIL_LEVELS_MAX) return -1;
+    // several visits of a level (nu > 1): all of them from the parent's
+    // restriction are one linear map; in FP64 only, since a reduced-precision
+    // cycle's later visits run on the levels' own rounded operators
+    if (p.nu > 1 && !fp64) return -1;
+    // the whole cycle of a small system (FP64: the reduced cycles keep the
+    // finest level's own precision)
+    int64_t bytes = 0;
+    for (int k = 0; k <= L; ++k) bytes += 72 * static_cast<int64_t>(h->lv[k].n);
+    if (fp64 && bytes <= TAIL_LDS_MAX && h->lv[0].A.nnz <= TAIL_NNZ_MAX) return 0;
     for (int k = 1; k < L; ++k) {
         const int m = h->lv[k].mode == 3 ? 3 * h->lv[k].n : h->lv[k].n;
         if (m <= TAIL_DENSE_MAX) return k;
@@ -640,50 +647,36 @@ int dense_tail_level(const amg_ctx *h) {
 }
 
 void setup_tail(amg_ctx *h) {
-    h->tail_start = -1;
     h->dense_start = -1;
     h->tail_m = 0;
     h->tail_dense.release();
     const amg_params &p = h->prm;
-    if (!p.fuse_coarse || p.nu != 1 || h->post_forward) return;
-    if (p.smoother != AMG_SMOOTH_JA && p.smoother != AMG_SMOOTH_GS) return;
-    const int L = static_cast<int>(h->lv.size()) - 1;
-    if (L == 0) return;
     const int d = dense_tail_level(h);
-    if (d > 0) {
-        TailArgs u;
-        double algo = 0.0;
-        DevBuf<TailLevel> desc;
-        const int stride = tail_descriptors(h, d, desc, u, algo);
-        const int mode = h->lv[d].mode;
-        const int m = mode == 3 ? 3 * h->lv[d].n : h->lv[d].n;
-        h->tail_dense.alloc(static_cast<size_t>(m) * m);
-        const int chunk = 2048;
-        DevBuf<double> scratch(static_cast<size_t>(std::min(chunk, m)) * stride);
-        u.unit_rhs = 1;
-        u.m = m;
-        u.x_out = h->tail_dense.p;
-        u.gscratch = scratch.p;
-        u.gstride = stride;
-        for (int j0 = 0; j0 < m; j0 += chunk) {
-            u.unit_base = j0;
-            launch_tail(mode, u, 0, std::min(chunk, m - j0), h->stream);
-        }
-        AMG_HIP(hipStreamSynchronize(h->stream));
-        h->tail_m = m;
-        h->tail_nc = mode == 3 ? 1 : 3;
-        h->dense_start = d;
+    if (d < 0) return;
+    TailArgs u;
+    DevBuf<TailLevel> desc;
+    const int stride = tail_descriptors(h, d, desc, u);
+    const int mode = h->lv[d].mode;
+    const int m = mode == 3 ? 3 * h->lv[d].n : h->lv[d].n;
+    h->tail_dense.alloc(static_cast<size_t>(m) * m);
+    const int lds = stride * static_cast<int>(sizeof(double));
+    const bool in_lds = lds <= TAIL_LDS_MAX;
+    const int chunk = 2048;
+    DevBuf<double> scratch(in_lds ? 0 : static_cast<size_t>(std::min(chunk, m)) * stride);
+    u.m = m;
+    u.x_out = h->tail_dense.p;
+    u.gscratch = scratch.p;
+    u.gstride = stride;
+    u.nu = std::max(1, p.nu);
+    u.top_visits = d > 0 ? u.nu : 1;
+    for (int j0 = 0; j0 < m; j0 += chunk) {
+        u.unit_base = j0;
+        launch_tail(mode, u, in_lds ? lds : 0, std::min(chunk, m - j0), h->stream);
     }
-    // LDS tail from the finest level, if everything fits
-    int64_t bytes = 0;
-    for (int k = 0; k <= L; ++k) bytes += 72 * static_cast<int64_t>(h->lv[k].n);
-    if (bytes <= TAIL_LDS_MAX && h->lv[0].A.nnz <= TAIL_NNZ_MAX) {
-        double algo = 0.0;
-        const int off = tail_descriptors(h, 0, h->tail_levels, h->tail_args, algo);
-        h->tail_lds = off * static_cast<int>(sizeof(double));
-        h->tail_bytes = algo;
-        h->tail_start = 0;
-    }
+    AMG_HIP(hipStreamSynchronize(h->stream));
+    h->tail_m = m;
+    h->tail_nc = mode == 3 ? 1 : 3;
+    h->dense_start = d;
 }
 
 // Braess-Sarazin on saddle level l (Section 3.3): the Schur complement
@@ -1279,9 +1272,8 @@ void build_hierarchy(amg_ctx *h, const amg_system *sys) {
                 setup_smoother(h, L);
                 if (h->saddle) saddle_setup_level(h, L);
             }
-            const bool used =
-                reduced ? l == 0
-                        : ((tail_from < 0 || static_cast<int>(l) < tail_from) && (l == 0 || !sweeps_give_residual(h, L)));
+            const bool used = l == 0 || (!reduced && (tail_from < 0 || static_cast<int>(l) < tail_from) &&
+                                         !sweeps_give_residual(h, L));
             if (p.autotune && used) {
                 SetupPhase ph(h, "autotune");
                 autotune_level(h, L);

@@ -1,13 +1,14 @@
-// The coarse end of Algorithm 1 in one workgroup.
+// The assembly of the coarse end of Algorithm 1 as an explicit operator.
 //
-// On the smallest levels every operation of the V-cycle is a few hundred rows:
-// launched one by one, each Gauss-Seidel colour, residual, restriction and
-// prolongation would cost a full dispatch (about 4.5 us on gfx950, the
-// latency floor of a kernel) for well under a microsecond of work. Here one
-// workgroup of 1024 threads runs the whole remaining V-cycle, from the
-// pre-smoothing of the first tail level down to the coarsest solve and back
-// up: the level vectors live in LDS, colours and phases are separated by
-// workgroup barriers, and the operators stream from L2.
+// From a zero guess the cycle from a level down is a fixed linear map of that
+// level's right-hand side. Workgroup j of 1024 threads runs the whole of it,
+// from the pre-smoothing of its first level down to the coarsest solve and
+// back up (nu visits of every level below a parent), on the j-th unit
+// right-hand side: colours and phases are separated by workgroup barriers,
+// the level vectors live in LDS where they fit, and the operators stream from
+// L2. Run once per cycle instead, one workgroup alone takes 370-460 us on a
+// 729-node hierarchy (a chain of some 60 barriers with a dependent load chain
+// each); the assembled operator's product takes 5-10 us.
 #include "common.h"
 #include "kernels.h"
 #include "tail.h"
@@ -125,8 +126,8 @@ __device__ void tail_smooth(const TailArgs &a, const TailLevel &L, double *x, co
 template <int MODE>
 __global__ void __launch_bounds__(TBLOCK) k_tail(const TailArgs a) {
     extern __shared__ double lds_buf[];
-    // level vectors: in LDS, or (when assembling a tail too large for LDS)
-    // in this workgroup's slice of a global scratch buffer
+    // level vectors: in LDS, or in this workgroup's slice of a global scratch
+    // buffer
     double *lds = a.gscratch ? a.gscratch + static_cast<int64_t>(blockIdx.x) * a.gstride : lds_buf;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const TailLevel *lv = a.lv;
@@ -134,79 +135,87 @@ __global__ void __launch_bounds__(TBLOCK) k_tail(const TailArgs a) {
         const TailLevel &L = lv[0];
         double *x = lds + L.lds_off, *b = x + 3 * L.n;
         const int uj = a.unit_base + static_cast<int>(blockIdx.x);
-        const int unit = a.unit_rhs ? (MODE == 3 ? uj : 3 * uj) : -1;
+        const int unit = MODE == 3 ? uj : 3 * uj;
         for (int t = tid; t < 3 * L.n; t += TBLOCK) {
-            b[t] = a.unit_rhs ? (t == unit ? 1.0 : 0.0) : a.b_in[t];
-            x[t] = (a.x_in_zero || a.unit_rhs) ? 0.0 : a.x_out[t];
+            b[t] = t == unit ? 1.0 : 0.0;
+            x[t] = 0.0;
         }
         __syncthreads();
     }
-    // down: smoothing, residual, restriction
-    for (int l = 0; l + 1 < a.nlev; ++l) {
-        const TailLevel &L = lv[l];
-        const TailLevel &C = lv[l + 1];
-        double *x = lds + L.lds_off, *b = x + 3 * L.n, *r = b + 3 * L.n;
-        tail_smooth<MODE>(a, L, x, b, r, true, l > 0 || a.x_in_zero, wave, lane);
-        tail_residual<MODE>(L, x, b, r, wave, lane);
-        double *xc = lds + C.lds_off, *bc = xc + 3 * C.n;
-        for (int t = tid; t < 3 * C.n; t += TBLOCK) {
-            const int J = t / 3, c = t % 3;
-            double s = 0.0;
-            for (int k = L.r_rowptr[J]; k < L.r_rowptr[J + 1]; ++k) s += L.r_val[k] * r[3 * L.r_col[k] + c];
-            bc[t] = s;
-            xc[t] = 0.0;
-        }
-        __syncthreads();
-    }
-    // coarsest: x = A_L^{-1} b with the explicit inverse
-    {
-        const TailLevel &L = lv[a.nlev - 1];
-        double *x = lds + L.lds_off, *b = x + 3 * L.n;
-        for (int row = wave; row < a.cm; row += TWAVES) {
-            double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-            const double *M = a.cinv + static_cast<int64_t>(row) * a.cm;
-            for (int j = lane; j < a.cm; j += 64) {
-                const double v = M[j];
-                s0 += v * b[j * a.cnc];
-                if (a.cnc > 1) {
-                    s1 += v * b[j * a.cnc + 1];
-                    s2 += v * b[j * a.cnc + 2];
-                }
+    // visits made of level l since its parent's last restriction (uniform over
+    // the workgroup)
+    int visits[TAIL_LEVELS_MAX];
+    for (int l = 0; l < TAIL_LEVELS_MAX; ++l) visits[l] = 0;
+    int l = 0;
+    for (;;) {
+        // down: smoothing, residual, restriction
+        for (; l + 1 < a.nlev; ++l) {
+            const TailLevel &L = lv[l];
+            const TailLevel &C = lv[l + 1];
+            double *x = lds + L.lds_off, *b = x + 3 * L.n, *r = b + 3 * L.n;
+            tail_smooth<MODE>(a, L, x, b, r, true, visits[l] == 0, wave, lane);
+            tail_residual<MODE>(L, x, b, r, wave, lane);
+            double *xc = lds + C.lds_off, *bc = xc + 3 * C.n;
+            for (int t = tid; t < 3 * C.n; t += TBLOCK) {
+                const int J = t / 3, c = t % 3;
+                double s = 0.0;
+                for (int k = L.r_rowptr[J]; k < L.r_rowptr[J + 1]; ++k) s += L.r_val[k] * r[3 * L.r_col[k] + c];
+                bc[t] = s;
+                xc[t] = 0.0;
             }
-            s0 = wave_sum(s0);
-            s1 = wave_sum(s1);
-            s2 = wave_sum(s2);
-            if (lane < a.cnc) x[row * a.cnc + lane] = lane == 0 ? s0 : (lane == 1 ? s1 : s2);
+            visits[l + 1] = 0;
+            __syncthreads();
         }
-        __syncthreads();
-    }
-    // up: prolongation and post-smoothing
-    for (int l = a.nlev - 2; l >= 0; --l) {
-        const TailLevel &L = lv[l];
-        const TailLevel &C = lv[l + 1];
-        double *x = lds + L.lds_off, *b = x + 3 * L.n, *r = b + 3 * L.n;
-        const double *xc = lds + C.lds_off;
-        for (int t = tid; t < 3 * L.n; t += TBLOCK) {
-            const int I = t / 3, c = t % 3;
-            double s = 0.0;
-            for (int k = L.p_rowptr[I]; k < L.p_rowptr[I + 1]; ++k) s += L.p_val[k] * xc[3 * L.p_col[k] + c];
-            x[t] += s;
+        // coarsest: x = A_L^{-1} b with the explicit inverse
+        {
+            const TailLevel &L = lv[a.nlev - 1];
+            double *x = lds + L.lds_off, *b = x + 3 * L.n;
+            for (int row = wave; row < a.cm; row += TWAVES) {
+                double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+                const double *M = a.cinv + static_cast<int64_t>(row) * a.cm;
+                for (int j = lane; j < a.cm; j += 64) {
+                    const double v = M[j];
+                    s0 += v * b[j * a.cnc];
+                    if (a.cnc > 1) {
+                        s1 += v * b[j * a.cnc + 1];
+                        s2 += v * b[j * a.cnc + 2];
+                    }
+                }
+                s0 = wave_sum(s0);
+                s1 = wave_sum(s1);
+                s2 = wave_sum(s2);
+                if (lane < a.cnc) x[row * a.cnc + lane] = lane == 0 ? s0 : (lane == 1 ? s1 : s2);
+            }
+            __syncthreads();
         }
-        __syncthreads();
-        tail_smooth<MODE>(a, L, x, b, r, false, false, wave, lane);
+        // up: prolongation and post-smoothing, until a level is due another visit
+        bool again = false;
+        while (l > 0 && !again) {
+            --l;
+            const TailLevel &L = lv[l];
+            const TailLevel &C = lv[l + 1];
+            double *x = lds + L.lds_off, *b = x + 3 * L.n, *r = b + 3 * L.n;
+            const double *xc = lds + C.lds_off;
+            for (int t = tid; t < 3 * L.n; t += TBLOCK) {
+                const int I = t / 3, c = t % 3;
+                double s = 0.0;
+                for (int k = L.p_rowptr[I]; k < L.p_rowptr[I + 1]; ++k) s += L.p_val[k] * xc[3 * L.p_col[k] + c];
+                x[t] += s;
+            }
+            __syncthreads();
+            tail_smooth<MODE>(a, L, x, b, r, false, false, wave, lane);
+            again = ++visits[l] < (l > 0 ? a.nu : a.top_visits);
+        }
+        if (!again) break;
     }
     {
         const TailLevel &L = lv[0];
         const double *x = lds + L.lds_off;
-        if (a.unit_rhs) {
-            const int64_t j = a.unit_base + static_cast<int64_t>(blockIdx.x);
-            if constexpr (MODE == 3) {
-                for (int i = tid; i < 3 * L.n; i += TBLOCK) a.x_out[static_cast<int64_t>(i) * a.m + j] = x[i];
-            } else {
-                for (int i = tid; i < L.n; i += TBLOCK) a.x_out[static_cast<int64_t>(i) * a.m + j] = x[3 * i];
-            }
+        const int64_t j = a.unit_base + static_cast<int64_t>(blockIdx.x);
+        if constexpr (MODE == 3) {
+            for (int i = tid; i < 3 * L.n; i += TBLOCK) a.x_out[static_cast<int64_t>(i) * a.m + j] = x[i];
         } else {
-            for (int t = tid; t < 3 * L.n; t += TBLOCK) a.x_out[t] = x[t];
+            for (int i = tid; i < L.n; i += TBLOCK) a.x_out[static_cast<int64_t>(i) * a.m + j] = x[3 * i];
         }
     }
 }

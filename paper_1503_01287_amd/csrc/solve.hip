@@ -240,15 +240,6 @@ static void run_dense_tail(amg_ctx *h, const double *b, double *x) {
     launch_dense_gemv(h->tail_dense.p, h->tail_m, h->tail_nc, b, x, h->stream);
 }
 
-static void run_tail(amg_ctx *h, const double *b, double *x, bool x_zero) {
-    TailArgs a = h->tail_args;
-    a.b_in = b;
-    a.x_out = x;
-    a.x_in_zero = x_zero ? 1 : 0;
-    ProfScope ps(h, "tail", h->tail_bytes);
-    launch_tail(h->lv[0].mode, a, h->tail_lds, 1, h->stream);
-}
-
 // Algorithm 1: AMG(K_l, x_l, b_l). x_zero: x_l is zero on entry (the first
 // Jacobi step then needs no operator pass); filled: its buffer holds the zeros.
 static void cycle(amg_ctx *h, int l, const double *b, double *x, bool x_zero, bool filled) {
@@ -256,10 +247,6 @@ static void cycle(amg_ctx *h, int l, const double *b, double *x, bool x_zero, bo
     if (h->nsys > 0) ending_systems(h, l, b, x);
     if (L.coarsest) {
         if (h->nsys == 0) coarse_solve(h, b, x);
-        return;
-    }
-    if (l == h->tail_start) {
-        run_tail(h, b, x, x_zero);
         return;
     }
     if (l == h->dense_start && x_zero) {
@@ -290,8 +277,9 @@ static void cycle(amg_ctx *h, int l, const double *b, double *x, bool x_zero, bo
         if (h->nsys > 0) ending_systems(h, l + 1, C.b.p, C.x.p);
         else coarse_solve(h, C.b.p, C.x.p);
     } else {
-        // x_{l+1} = 0, then nu recursive calls (nu = 1: V-cycle, 2: W-cycle)
-        const int nu = std::max(1, h->prm.nu);
+        // x_{l+1} = 0, then nu recursive calls (nu = 1: V-cycle, 2: W-cycle;
+        // the assembled coarse end covers all of them)
+        const int nu = l + 1 == h->dense_start ? 1 : std::max(1, h->prm.nu);
         for (int k = 0; k < nu; ++k) cycle(h, l + 1, C.b.p, C.x.p, k == 0, k == 0);
     }
     // one-launch sweeps read their iterate from L.t: the prolongation puts it there

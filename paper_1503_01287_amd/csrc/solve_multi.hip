@@ -183,7 +183,7 @@ struct MCycle {
         if (C.coarsest) {
             coarse(l + 1, vb(l + 1), e);
         } else {
-            const int nu = std::max(1, h->prm.nu);
+            const int nu = l + 1 == h->dense_start ? 1 : std::max(1, h->prm.nu);
             for (int k = 0; k < nu; ++k) e = cycle(l + 1, vb(l + 1), e, k == 0);
         }
         {

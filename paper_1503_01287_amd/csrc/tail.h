@@ -1,4 +1,4 @@
-// Descriptors of the levels handled by the single-workgroup tail kernel.
+// Descriptors of the levels whose cycle k_tail.hip assembles as an operator.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -32,16 +32,15 @@ struct TailArgs {
     int nlev = 0;        // tail levels, the last one the coarsest
     int smoother = 1;    // AMG_SMOOTH_JA or AMG_SMOOTH_GS
     int pre = 1, post = 1;
-    int x_in_zero = 1;   // 1: the first tail level starts from x = 0
+    int nu = 1;          // visits of a level per visit of its parent
+    int top_visits = 1;  // visits of the first tail level, from zero
     const TailLevel *lv = nullptr;  // device array of nlev descriptors
     const double *cinv = nullptr;   // coarsest explicit inverse (cm x cm)
     int cm = 0, cnc = 1;
-    const double *b_in = nullptr;   // right-hand side of the first tail level
-    double *x_out = nullptr;        // its solution (also the initial guess if !x_in_zero)
-    // unit_rhs = 1: workgroup j solves for the j-th unit right-hand side
-    // (mode 3: e_j over the 3n unknowns; mode 1: component 0 of node j) and
-    // writes its result as column j of the row-major m x m matrix x_out
-    int unit_rhs = 0;
+    // workgroup j solves for the j-th unit right-hand side (mode 3: e_j over
+    // the 3n unknowns; mode 1: component 0 of node j) and writes its result as
+    // column j of the row-major m x m matrix x_out
+    double *x_out = nullptr;
     int m = 0;
     int unit_base = 0;   // workgroup j handles unit right-hand side unit_base + j
     // if set, workgroup j keeps its level vectors at gscratch + j * gstride
@@ -50,11 +49,15 @@ struct TailArgs {
     int64_t gstride = 0;
 };
 
-constexpr int TAIL_LDS_MAX = 64 * 1024;   // bytes of LDS the tail may use
-constexpr int64_t TAIL_NNZ_MAX = 40000;   // stored entries of the first tail level
+constexpr int TAIL_LEVELS_MAX = 32;       // levels of a tail at most
+constexpr int TAIL_LDS_MAX = 64 * 1024;   // bytes of LDS a workgroup's level vectors may take
+// The finest level is part of the operator where its assembly costs little: the
+// level vectors in LDS and this many stored entries (about 2 ms; a cycle's
+// launches take 90 us against 5-10 us for the product)
+constexpr int64_t TAIL_NNZ_MAX = 40000;
 constexpr int TAIL_DENSE_MAX = 9000;      // largest tail operator kept as an explicit matrix
 
-// grid = 1 for a solve, grid = m with unit_rhs = 1 to assemble the operator
+// `grid` columns from unit_base on
 void launch_tail(int mode, const TailArgs &a, int lds_bytes, int grid, hipStream_t s);
 
 }  // namespace amgp2
