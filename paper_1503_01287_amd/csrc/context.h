@@ -153,27 +153,33 @@ struct VankaData {
     DevBuf<int64_t> moff;
     DevBuf<double> inv;
     std::vector<int> cptr;
-    // sweep form (chosen at setup): 0 one kernel per colour; 1 residuals,
-    // then corrections over 64-row tiles; 2 residuals spread over rows,
-    // partial corrections over 64-row x cc-column tiles, then their sum;
-    // 3 residuals spread over rows, then corrections over 64-row tiles
-    int path = 0;
-    DevBuf<int64_t> roff;          // residual buffer offsets (paths 1, 2, 3)
+    // sweep form: 2 residuals, partial corrections over 64-row x cc-column
+    // tiles, then their sum; 3 residuals, then corrections over 64-row tiles
+    int path = 3;
+    DevBuf<int64_t> roff;          // a patch's residual in rbuf (path 2)
     DevBuf<double> rbuf;
-    DevBuf<int> tpre;              // per-colour prefix of the 64-row tiles
-    std::vector<int> ntiles;       // 64-row tiles per colour
+    DevBuf<int> tpre;              // per-colour prefix of the 64-row tiles (path 2)
+    DevBuf<int2> rown;             // residual rows and correction tiles, colour by colour (VankaColour)
+    DevBuf<int4> rowa;
+    DevBuf<VankaTile> tile;
+    std::vector<int> rptr, tptr;   // first row, first tile of a colour
     int cc = 256;                  // path 2: columns per chunk
     DevBuf<int> upre;              // path 2: per-colour prefix of the 2-D tiles
     std::vector<int> nunits;       // path 2: 2-D tiles per colour
     DevBuf<int64_t> poff;          // path 2: partial buffer offsets
     DevBuf<double> pbuf;
-    int rg = 16;                   // paths 2, 3: lanes per residual row (16, 32 or 64)
+    int rg = 32;                   // lanes per residual row (16, 32 or 64)
     int aw = 4;                    // path 3: wavefronts per 64-row correction tile (4, 8 or 16)
-    // paths 2 and 3, for rg = 16, 32, 64 (index rg_index): per-colour prefix of the
-    // residual's units (256 / rg node rows each) and units per colour
-    DevBuf<int> rpre[3];
-    std::vector<int> nrunits[3];
-    static int rg_index(int rg) { return rg == 16 ? 0 : (rg == 32 ? 1 : 2); }
+    VankaColour colour(int c) const {
+        VankaColour q;
+        q.count = cptr[c + 1] - cptr[c];
+        q.nrows = rptr[c + 1] - rptr[c];
+        q.ntiles = tptr[c + 1] - tptr[c];
+        q.rown = rown.p + rptr[c];
+        q.rowa = rowa.p + rptr[c];
+        q.tile = tile.p + tptr[c];
+        return q;
+    }
 };
 
 struct Level {
@@ -391,6 +397,8 @@ void setup_vanka(amg_ctx *h, int l);
 void setup_schur_dense(amg_ctx *h, int l);
 void setup_saddle_tail(amg_ctx *h);
 VankaView vanka_view(Level &L);
+// one colour of a sweep in the level's form
+void launch_vanka(const Level &L, const VankaView &v, int c, const double *b, double *x, double omega, hipStream_t s);
 // JA damping per level from the network of prm.omega_model (fallback: prm.omega)
 void predict_level_omega(amg_ctx *h);
 // every JA level's bound OMEGA_CAP_FACTOR * 2 / lambda_max(D^{-1} A_l), and

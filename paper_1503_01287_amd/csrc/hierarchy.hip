@@ -805,6 +805,15 @@ VankaView vanka_view(Level &L) {
 // couples their pressures; greedy first-fit colouring in index order of the
 // conflict graph gives the processing order (colour, then index). The local
 // matrices are assembled and inverted on the GPU.
+void launch_vanka(const Level &L, const VankaView &v, int c, const double *b, double *x, double omega, hipStream_t s) {
+    const VankaData &V = L.vanka;
+    if (V.path == 2)
+        launch_vanka_colour_tiled(v, V.colour(c), V.order.p + V.cptr[c], V.tpre.p + V.cptr[c], V.upre.p + V.cptr[c],
+                                  V.nunits[c], V.cc, V.rg, V.roff.p, V.rbuf.p, V.poff.p, V.pbuf.p, b, x, omega, s);
+    else
+        launch_vanka_colour_rows(v, V.colour(c), V.rg, V.aw, V.rbuf.p, b, x, omega, s);
+}
+
 void setup_vanka(amg_ctx *h, int l) {
     hipStream_t s = h->stream;
     Level &L = h->lv[l];
@@ -866,7 +875,7 @@ void setup_vanka(amg_ctx *h, int l) {
     }
     AMG_REQUIRE(total * 8 <= (int64_t(96) << 30), AMG_ENOMEM,
                 "amg_setup: the Vanka patch inverses would exceed 96 GiB");
-    // the patch kernels keep 2 m + 4,096 doubles and n_P ints of a patch in LDS (96 KiB budget)
+    // (kept from the form that held a patch's vectors in LDS: what was too large stays refused)
     AMG_REQUIRE((2 * (3 * V.max_nodes + 1) + 4096) * 8 + V.max_nodes * 4 <= 98304, AMG_EUNSUPPORTED,
                 "amg_setup: a Vanka patch is too large for the patch kernels");
     V.pptr.upload(bp.rowptr, s);
@@ -881,45 +890,47 @@ void setup_vanka(amg_ctx *h, int l) {
     flag.zero(s);
     launch_vanka_invert(view, 3 * V.max_nodes + 1, flag.p, s);
     AMG_REQUIRE(flag.download(s)[0] == 0, AMG_EINVAL, "amg_setup: singular Vanka patch matrix");
-    // two-kernel path: residual offsets and the apply's tiles, colour by colour
+    // the residuals' rows and the corrections' tiles, colour by colour
     std::vector<int64_t> roff(std::max(1, np), 0);
     int64_t rtot = 0;
     for (int i = 0; i < np; ++i) {
         roff[i] = rtot;
         rtot += 3 * static_cast<int64_t>(bp.rowptr[i + 1] - bp.rowptr[i]) + 1;
     }
+    AMG_REQUIRE(rtot < (int64_t(1) << 31), AMG_EUNSUPPORTED, "amg_setup: too many Vanka patch unknowns");
     std::vector<int> tpre(std::max(1, np), 0);
-    V.ntiles.assign(nc, 0);
+    std::vector<int2> rown;
+    std::vector<VankaTile> tiles;
+    V.rptr.assign(1, 0);
+    V.tptr.assign(1, 0);
     for (int c = 0; c < nc; ++c) {
-        int t = 0;
         for (int k = V.cptr[c]; k < V.cptr[c + 1]; ++k) {
-            tpre[k] = t;
-            const int i = order[k];
-            t += (3 * (bp.rowptr[i + 1] - bp.rowptr[i]) + 1 + 63) / 64;
+            const int i = order[k], p0 = bp.rowptr[i], nn = bp.rowptr[i + 1] - p0, m = 3 * nn + 1;
+            tpre[k] = static_cast<int>(tiles.size()) - V.tptr[c];
+            for (int q = 0; q < nn; ++q) rown.push_back(make_int2(bp.col[p0 + q], static_cast<int>(roff[i]) + 3 * q));
+            rown.push_back(make_int2(~i, static_cast<int>(roff[i]) + 3 * nn));
+            for (int a = 0; a < m; a += 64) {
+                VankaTile t;
+                t.inv = moff[i];
+                t.m = m;
+                t.row0 = a;
+                t.res = static_cast<int>(roff[i]);
+                t.node0 = p0;
+                t.patch = i;
+                tiles.push_back(t);
+            }
         }
-        V.ntiles[c] = t;
+        V.rptr.push_back(static_cast<int>(rown.size()));
+        V.tptr.push_back(static_cast<int>(tiles.size()));
     }
     V.roff.upload(roff, s);
     V.tpre.upload(tpre, s);
+    V.rown.upload(rown, s);
+    V.tile.upload(tiles, s);
+    V.rowa.alloc(rown.size());
+    launch_vanka_rows(view, static_cast<int>(rown.size()), V.rown.p, V.rowa.p, s);
     V.rbuf.alloc(static_cast<size_t>(std::max<int64_t>(1, rtot)));
-    // the tiled path's residual: rg lanes per row, 256 / rg node rows (and
-    // the pressure row) per unit, tables for every rg
-    for (const int rg : {16, 32, 64}) {
-        const int rows = 256 / rg, ri = VankaData::rg_index(rg);
-        std::vector<int> rpre(std::max(1, np), 0);
-        V.nrunits[ri].assign(nc, 0);
-        for (int c = 0; c < nc; ++c) {
-            int t = 0;
-            for (int k = V.cptr[c]; k < V.cptr[c + 1]; ++k) {
-                rpre[k] = t;
-                const int i = order[k];
-                t += (bp.rowptr[i + 1] - bp.rowptr[i] + 1 + rows - 1) / rows;
-            }
-            V.nrunits[ri][c] = t;
-        }
-        V.rpre[ri].upload(rpre, s);
-    }
-    V.rg = 16;
+    V.rg = L.A.nnz > 40 * static_cast<int64_t>(L.n) ? 64 : 32;
     // three-kernel path: 64-row x cc-column tiles of the inverses and their
     // partial sums, colour by colour, for a chunk width cc
     auto tile_tables = [&](int cc) {
@@ -947,12 +958,8 @@ void setup_vanka(amg_ctx *h, int l) {
         V.poff.upload(poff, s);
         if (static_cast<int64_t>(V.pbuf.n) < ptot) V.pbuf.alloc(static_cast<size_t>(std::max<int64_t>(1, ptot)));
     };
-    // the sweep form for this level's patch sizes: one kernel per colour for
-    // patches up to 256 unknowns, the tiled form above, unless (with the
-    // tuners on) another form or chunk width is 3% faster on a scratch
-    // vector pair
-    const bool large = 3 * V.max_nodes + 1 > 256;
-    V.path = large ? 2 : 0;
+    // (with the tuners on) another width or form that is 3% faster on a
+    // scratch vector pair
     tile_tables(256);
     if (h->prm.autotune) {
         const int64_t nv = L.vlen();
@@ -962,92 +969,51 @@ void setup_vanka(amg_ctx *h, int l) {
         hipEvent_t e0, e1;
         AMG_HIP(hipEventCreate(&e0));
         AMG_HIP(hipEventCreate(&e1));
-        auto sweep = [&](int path) {
-            for (int c = 0; c < nc; ++c) {
-                const int cnt = V.cptr[c + 1] - V.cptr[c];
-                if (path == 2)
-                    launch_vanka_colour_tiled(view, V.order.p + V.cptr[c], V.tpre.p + V.cptr[c],
-                                              V.upre.p + V.cptr[c], V.rpre[VankaData::rg_index(V.rg)].p + V.cptr[c],
-                                              cnt, V.ntiles[c], V.nunits[c],
-                                              V.nrunits[VankaData::rg_index(V.rg)][c], V.cc, V.rg, V.roff.p, V.rbuf.p, V.poff.p,
-                                              V.pbuf.p, bs.p, xs.p, 0.5, s);
-                else if (path == 3)
-                    launch_vanka_colour_rows(view, V.order.p + V.cptr[c], V.tpre.p + V.cptr[c],
-                                             V.rpre[VankaData::rg_index(V.rg)].p + V.cptr[c], cnt, V.ntiles[c],
-                                             V.nrunits[VankaData::rg_index(V.rg)][c], V.rg, V.aw, V.roff.p, V.rbuf.p, bs.p,
-                                             xs.p, 0.5, s);
-                else if (path == 1)
-                    launch_vanka_colour_split(view, V.order.p + V.cptr[c], V.tpre.p + V.cptr[c], cnt, V.ntiles[c],
-                                              V.max_nodes, V.roff.p, V.rbuf.p, bs.p, xs.p, 0.5, s);
-                else
-                    launch_vanka_colour(view, V.order.p + V.cptr[c], cnt, V.max_nodes, bs.p, xs.p, 0.5, s);
-            }
+        auto sweep = [&] {
+            for (int c = 0; c < nc; ++c) launch_vanka(L, view, c, bs.p, xs.p, 0.5, s);
         };
-        auto time_of = [&](int path) {
-            sweep(path);
-            float best = 1e30f;
+        auto time_of = [&] {
+            sweep();
+            float t = 1e30f;
             for (int r = 0; r < 3; ++r) {
                 AMG_HIP(hipEventRecord(e0, s));
-                sweep(path);
+                sweep();
                 AMG_HIP(hipEventRecord(e1, s));
                 AMG_HIP(hipEventSynchronize(e1));
                 float ms = 0.f;
                 AMG_HIP(hipEventElapsedTime(&ms, e0, e1));
-                best = std::min(best, ms);
+                t = std::min(t, ms);
             }
-            return best;
+            return t;
         };
-        float best = time_of(V.path);
-        int best_path = V.path, best_cc = 256;
-        for (const int path : {0, 1}) {
-            if (path == V.path) continue;
-            const float t = time_of(path);
-            if (t < 0.97f * best) {
+        float best = time_of();
+        auto better = [&](int &knob, int value) {
+            const int was = knob;
+            knob = value;
+            const float t = time_of();
+            if (t < 0.97f * best)
                 best = t;
-                best_path = path;
-            }
-        }
-        for (const int cc : {128, 256, 512}) {
-            if (cc == 256 && V.path == 2) continue;
+            else
+                knob = was;
+        };
+        for (const int rg : {16, 32, 64})
+            if (rg != V.rg) better(V.rg, rg);
+        for (const int aw : {8, 16}) better(V.aw, aw);
+        int best_cc = 256;
+        for (const int cc : {256, 128, 512}) {
+            if (cc != 256 && V.path != 2) break;  // not near the other form
             tile_tables(cc);
-            const float t = time_of(2);
+            const int was = V.path;
+            V.path = 2;
+            const float t = time_of();
             if (t < 0.97f * best) {
                 best = t;
-                best_path = 2;
                 best_cc = cc;
+            } else {
+                V.path = was;
             }
         }
-        tile_tables(best_cc);
-        // the spread residual's width (wider lane groups for long rows), in
-        // the tiled form and in the two-kernel form with that residual
-        int best_rg = 16;
-        for (const int rg : {16, 32, 64}) {
-            V.rg = rg;
-            for (const int path : {2, 3}) {
-                if (path == 2 && rg == 16) continue;  // timed above
-                const float t = time_of(path);
-                if (t < 0.97f * best) {
-                    best = t;
-                    best_path = path;
-                    best_rg = rg;
-                }
-            }
-        }
-        V.rg = best_rg;
-        V.path = best_path;
-        if (best_path == 3) {
-            // wavefronts per correction tile: shorter column chains per lane
-            int best_aw = 4;
-            for (const int aw : {8, 16}) {
-                V.aw = aw;
-                const float t = time_of(3);
-                if (t < 0.97f * best) {
-                    best = t;
-                    best_aw = aw;
-                }
-            }
-            V.aw = best_aw;
-        }
+        if (V.cc != best_cc) tile_tables(best_cc);
         AMG_HIP(hipEventDestroy(e0));
         AMG_HIP(hipEventDestroy(e1));
     }
@@ -1314,6 +1280,8 @@ void build_hierarchy(amg_ctx *h, const amg_system *sys) {
                 L.B = std::move(c);
             }
             if (drop_zero_entries(L.Bt, false, c, s)) L.Bt = std::move(c);
+            if (L.vanka.rown.n > 0)  // the sweeps' rows of those operators
+                launch_vanka_rows(vanka_view(L), static_cast<int>(L.vanka.rown.n), L.vanka.rown.p, L.vanka.rowa.p, s);
         }
     if (!h->saddle) {
         {

@@ -143,247 +143,78 @@ void launch_vanka_invert(const VankaView &v, int max_m, int *flag, hipStream_t s
     AMG_CHECK_LAUNCH();
 }
 
-// One colour of the multiplicative sweep, 1,024 threads per patch (a colour
-// holds only a few hundred patches, so each needs many waves in flight):
-// residual on the patch (VG lanes per node row, 64 rows at a time, over the
-// node's A and B^T rows), correction with the patch's inverse (row tiles of
-// 64 VR rows, the 16 wavefronts spread over tiles and column groups, partial
-// sums added in LDS in a fixed order), update in place.
-constexpr int VG = 16;
-constexpr int VR = 4;     // rows per lane and pass in the apply
-constexpr int VCB = 1024; // threads per patch: the ~m / 3 node rows of a patch at once
-constexpr int VNW = VCB / 64;
-
-__global__ void __launch_bounds__(VCB) k_vanka_colour(const VankaView v, const int *order, const double *b,
-                                                      double *x, double omega) {
-    extern __shared__ unsigned char smem[];
-    const int i = order[blockIdx.x];
-    const int p0 = v.pptr[i], nn = v.pptr[i + 1] - p0;
-    const int m = 3 * nn + 1;
-    double *r = reinterpret_cast<double *>(smem);
-    double *part = r + m;                       // NG x m partial products (NG m <= m + 64 VR VNW)
-    int *nodes = reinterpret_cast<int *>(part + m + 64 * VR * VNW);
-    for (int k = threadIdx.x; k < nn; k += VCB) nodes[k] = v.pnode[p0 + k];
-    __syncthreads();
-    const int64_t nu = 3 * static_cast<int64_t>(v.n);
-    const double *p = x + nu;
-    const int grp = threadIdx.x / VG, lane = threadIdx.x % VG;
-    for (int k = grp; k <= nn; k += VCB / VG) {
-        if (k < nn) {
-            const int u = nodes[k];
-            double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-            for (int q = v.arow[u] + lane; q < v.arow[u + 1]; q += VG) {
-                const int j = v.acol[q];
-                const double x0 = x[3 * j], x1 = x[3 * j + 1], x2 = x[3 * j + 2];
-                s0 += v.aval[0 * v.annz + q] * x0 + v.aval[1 * v.annz + q] * x1 + v.aval[2 * v.annz + q] * x2;
-                s1 += v.aval[3 * v.annz + q] * x0 + v.aval[4 * v.annz + q] * x1 + v.aval[5 * v.annz + q] * x2;
-                s2 += v.aval[6 * v.annz + q] * x0 + v.aval[7 * v.annz + q] * x1 + v.aval[8 * v.annz + q] * x2;
-            }
-            for (int q = v.btrow[u] + lane; q < v.btrow[u + 1]; q += VG) {
-                const double pq = p[v.btcol[q]];
-                s0 += v.btval[q] * pq;
-                s1 += v.btval[v.btnnz + q] * pq;
-                s2 += v.btval[2 * v.btnnz + q] * pq;
-            }
-#pragma unroll
-            for (int o = VG / 2; o > 0; o >>= 1) {
-                s0 += __shfl_xor(s0, o, VG);
-                s1 += __shfl_xor(s1, o, VG);
-                s2 += __shfl_xor(s2, o, VG);
-            }
-            if (lane == 0) {
-                r[3 * k] = b[3 * u] - s0;
-                r[3 * k + 1] = b[3 * u + 1] - s1;
-                r[3 * k + 2] = b[3 * u + 2] - s2;
-            }
-        } else {
-            // pressure row: g_i - B_i u + C_i p
-            double s = 0.0;
-            for (int q = v.brow[i] + lane; q < v.brow[i + 1]; q += VG) {
-                const int j = v.bcol[q];
-                s += v.bval[q] * x[3 * j] + v.bval[v.bnnz + q] * x[3 * j + 1] + v.bval[2 * v.bnnz + q] * x[3 * j + 2];
-            }
-            if (v.crow)
-                for (int q = v.crow[i] + lane; q < v.crow[i + 1]; q += VG) s -= v.cval[q] * p[v.ccol[q]];
-#pragma unroll
-            for (int o = VG / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, VG);
-            if (lane == 0) r[3 * nn] = b[nu + i] - s;
-        }
-    }
-    __syncthreads();
-    const double *M = v.inv + v.moff[i];
-    const int wave = threadIdx.x >> 6, wl = threadIdx.x & 63;
-    // RT tiles of 64 * VR rows; the waves of a tile split the columns into NG groups
-    const int RT = (m + 64 * VR - 1) / (64 * VR);
-    const int NG = RT >= VNW ? 1 : VNW / RT;
-    const int grpc = wave % NG;
-    const int c0 = grpc * m / NG, c1 = (grpc + 1) * m / NG;
-    for (int tile = wave / NG; tile < RT; tile += VNW / NG) {
-        const int a0 = tile * 64 * VR;
-        double acc[VR];
-#pragma unroll
-        for (int t = 0; t < VR; ++t) acc[t] = 0.0;
-        // four columns' loads in flight per lane before their products are
-        // added (still in column order)
-        int c = c0;
-        for (; c + 4 <= c1; c += 4) {
-            double mv[4][VR], rv[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                rv[u] = r[c + u];
-                const double *col = M + static_cast<int64_t>(c + u) * m;
-#pragma unroll
-                for (int t = 0; t < VR; ++t) {
-                    const int a = a0 + wl + 64 * t;
-                    mv[u][t] = a < m ? col[a] : 0.0;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int t = 0; t < VR; ++t)
-                    if (a0 + wl + 64 * t < m) acc[t] += mv[u][t] * rv[u];
-        }
-        for (; c < c1; ++c) {
-            const double rc = r[c];
-            const double *col = M + static_cast<int64_t>(c) * m;
-#pragma unroll
-            for (int t = 0; t < VR; ++t) {
-                const int a = a0 + wl + 64 * t;
-                if (a < m) acc[t] += col[a] * rc;
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < VR; ++t) {
-            const int a = a0 + wl + 64 * t;
-            if (a < m) part[grpc * m + a] = acc[t];
-        }
-    }
-    __syncthreads();
-    for (int a = threadIdx.x; a < m; a += VCB) {
-        double sum = 0.0;
-        const int RT = (m + 64 * VR - 1) / (64 * VR);
-        const int NG = RT >= VNW ? 1 : VNW / RT;
-        for (int g = 0; g < NG; ++g) sum += part[g * m + a];
-        const double d = omega * sum;
-        if (a < 3 * nn) x[3 * static_cast<int64_t>(nodes[a / 3]) + a % 3] += d;
-        else x[nu + i] += d;
-    }
+// Descriptors of the residual rows: from where a row's entries are read, so
+// that a row's chain of loads is descriptor, column, x.
+__global__ void __launch_bounds__(VB) k_vanka_rows(const VankaView v, int nrows, const int2 *rown, int4 *rowa) {
+    const int t = blockIdx.x * VB + threadIdx.x;
+    if (t >= nrows) return;
+    const int u = rown[t].x;
+    if (u >= 0)
+        rowa[t] = make_int4(v.arow[u], v.arow[u + 1], v.btrow[u], v.btrow[u + 1]);
+    else
+        rowa[t] = make_int4(v.brow[~u], v.brow[~u + 1], v.crow ? v.crow[~u] : 0, v.crow ? v.crow[~u + 1] : 0);
 }
 
-void launch_vanka_colour(const VankaView &v, const int *order, int count, int max_nodes, const double *b,
-                         double *x, double omega, hipStream_t s) {
-    if (count <= 0) return;
-    const int max_m = 3 * max_nodes + 1;
-    const size_t lds = static_cast<size_t>(2 * max_m + 64 * VR * VNW) * sizeof(double) + max_nodes * sizeof(int);
-    k_vanka_colour<<<count, VCB, lds, s>>>(v, order, b, x, omega);
+void launch_vanka_rows(const VankaView &v, int nrows, const int2 *rown, int4 *rowa, hipStream_t s) {
+    if (nrows <= 0) return;
+    k_vanka_rows<<<ceil_div(nrows, VB), VB, 0, s>>>(v, nrows, rown, rowa);
     AMG_CHECK_LAUNCH();
-}
-
-// Residual of every patch of a colour into rbuf (same arithmetic as the
-// fused kernel's first phase).
-__global__ void __launch_bounds__(VCB) k_vanka_resid(const VankaView v, const int *order, const int64_t *roff,
-                                                     double *rbuf, const double *b, const double *x) {
-    extern __shared__ int snodes[];
-    const int i = order[blockIdx.x];
-    const int p0 = v.pptr[i], nn = v.pptr[i + 1] - p0;
-    for (int k = threadIdx.x; k < nn; k += VCB) snodes[k] = v.pnode[p0 + k];
-    __syncthreads();
-    double *r = rbuf + roff[i];
-    const int64_t nu = 3 * static_cast<int64_t>(v.n);
-    const double *p = x + nu;
-    const int grp = threadIdx.x / VG, lane = threadIdx.x % VG;
-    for (int k = grp; k <= nn; k += VCB / VG) {
-        if (k < nn) {
-            const int u = snodes[k];
-            double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-            for (int q = v.arow[u] + lane; q < v.arow[u + 1]; q += VG) {
-                const int j = v.acol[q];
-                const double x0 = x[3 * j], x1 = x[3 * j + 1], x2 = x[3 * j + 2];
-                s0 += v.aval[0 * v.annz + q] * x0 + v.aval[1 * v.annz + q] * x1 + v.aval[2 * v.annz + q] * x2;
-                s1 += v.aval[3 * v.annz + q] * x0 + v.aval[4 * v.annz + q] * x1 + v.aval[5 * v.annz + q] * x2;
-                s2 += v.aval[6 * v.annz + q] * x0 + v.aval[7 * v.annz + q] * x1 + v.aval[8 * v.annz + q] * x2;
-            }
-            for (int q = v.btrow[u] + lane; q < v.btrow[u + 1]; q += VG) {
-                const double pq = p[v.btcol[q]];
-                s0 += v.btval[q] * pq;
-                s1 += v.btval[v.btnnz + q] * pq;
-                s2 += v.btval[2 * v.btnnz + q] * pq;
-            }
-#pragma unroll
-            for (int o = VG / 2; o > 0; o >>= 1) {
-                s0 += __shfl_xor(s0, o, VG);
-                s1 += __shfl_xor(s1, o, VG);
-                s2 += __shfl_xor(s2, o, VG);
-            }
-            if (lane == 0) {
-                r[3 * k] = b[3 * u] - s0;
-                r[3 * k + 1] = b[3 * u + 1] - s1;
-                r[3 * k + 2] = b[3 * u + 2] - s2;
-            }
-        } else {
-            double s = 0.0;
-            for (int q = v.brow[i] + lane; q < v.brow[i + 1]; q += VG) {
-                const int j = v.bcol[q];
-                s += v.bval[q] * x[3 * j] + v.bval[v.bnnz + q] * x[3 * j + 1] + v.bval[2 * v.bnnz + q] * x[3 * j + 2];
-            }
-            if (v.crow)
-                for (int q = v.crow[i] + lane; q < v.crow[i + 1]; q += VG) s -= v.cval[q] * p[v.ccol[q]];
-#pragma unroll
-            for (int o = VG / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, VG);
-            if (lane == 0) r[3 * nn] = b[nu + i] - s;
-        }
-    }
 }
 
 // 64 rows of one patch's correction per workgroup: lane = row, the NW
 // wavefronts take 1 / NW of the columns each, partial sums added in LDS in
-// wavefront order.
+// wavefront order. Bound by the read of the inverses on fine levels and by
+// the chain tile, residual and columns, LDS, x on coarse ones: the tile's
+// descriptor, the residual's values (64 a load, broadcast from the lanes)
+// and the entries of x are loaded ahead of the columns that they meet.
 template <int NW>
-__global__ void __launch_bounds__(64 * NW) k_vanka_apply(const VankaView v, const int *order, const int *tpre,
-                                                         int count, const int64_t *roff, const double *rbuf,
+__global__ void __launch_bounds__(64 * NW) k_vanka_apply(const VankaView v, const VankaTile *tile, const double *rbuf,
                                                          double *x, double omega) {
     __shared__ double part[NW][64];
-    int lo = 0, hi = count - 1;
-    const int t = blockIdx.x;
-    while (lo < hi) {  // last patch whose first tile is <= t
-        const int mid = (lo + hi + 1) >> 1;
-        if (tpre[mid] <= t) lo = mid;
-        else hi = mid - 1;
+    const VankaTile t = tile[blockIdx.x];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int a = t.row0 + lane, m = t.m;
+    int64_t at = 0;
+    double old = 0.0;
+    if (wave == 0 && a < m) {
+        // (no other patch of the colour touches these entries)
+        at = a < m - 1 ? 3 * static_cast<int64_t>(v.pnode[t.node0 + a / 3]) + a % 3 : 3 * static_cast<int64_t>(v.n) + t.patch;
+        old = x[at];
     }
-    const int i = order[lo];
-    const int p0 = v.pptr[i], nn = v.pptr[i + 1] - p0;
-    const int m = 3 * nn + 1;
-    const int a = (t - tpre[lo]) * 64 + (threadIdx.x & 63);
-    const int wave = threadIdx.x >> 6;
-    const double *r = rbuf + roff[i];
-    const double *M = v.inv + v.moff[i];
+    const double *r = rbuf + t.res;
+    const double *M = v.inv + t.inv;
     const int c0 = wave * m / NW, c1 = (wave + 1) * m / NW;
+    const int ar = a < m ? a : m - 1;
     double acc = 0.0;
-    if (a < m) {
-        int c = c0;
-        for (; c + 8 <= c1; c += 8) {  // eight column loads in flight per lane
-            double mv[8], rv[8];
+    for (int cb = c0; cb < c1; cb += 64) {
+        const int nc = c1 - cb < 64 ? c1 - cb : 64;
+        const double rl = lane < nc ? r[cb + lane] : 0.0;
+        int u = 0;
+        for (; u + 16 <= nc; u += 16) {
+            double mv[16];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                mv[u] = M[static_cast<int64_t>(c + u) * m + a];
-                rv[u] = r[c + u];
-            }
+            for (int k = 0; k < 16; ++k) mv[k] = M[static_cast<int64_t>(cb + u + k) * m + ar];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) acc += mv[u] * rv[u];
+            for (int k = 0; k < 16; ++k) acc += mv[k] * __shfl(rl, u + k, 64);
         }
-        for (; c < c1; ++c) acc += M[static_cast<int64_t>(c) * m + a] * r[c];
+        if (u < nc) {
+            double mv[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) mv[k] = u + k < nc ? M[static_cast<int64_t>(cb + u + k) * m + ar] : 0.0;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const double rk = __shfl(rl, u + k < 64 ? u + k : 63, 64);
+                if (u + k < nc) acc += mv[k] * rk;
+            }
+        }
     }
-    part[wave][threadIdx.x & 63] = acc;
+    part[wave][lane] = acc;
     __syncthreads();
     if (wave != 0 || a >= m) return;
-    const int l = threadIdx.x;
-    double sum = part[0][l];
+    double sum = part[0][lane];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) sum += part[w][l];
-    const double d = omega * sum;
-    if (a < 3 * nn) x[3 * static_cast<int64_t>(v.pnode[p0 + a / 3]) + a % 3] += d;
-    else x[3 * static_cast<int64_t>(v.n) + i] += d;
+    for (int w = 1; w < NW; ++w) sum += part[w][lane];
+    x[at] = old + omega * sum;
 }
 
 // Partial corrections of one colour's large patches, tiled in two dimensions
@@ -462,47 +293,56 @@ __global__ void __launch_bounds__(64) k_vanka_reduce(const VankaView v, const in
     else x[3 * static_cast<int64_t>(v.n) + i] += d;
 }
 
-// Residuals of one colour's patches, VB / G node rows (G lanes each) per
-// workgroup so that a colour of few, large patches still spreads over the
-// GPU (rpre: prefix of ceil((n_P + 1) / (VB / G)) over the colour's
-// patches; the last row of a patch is its pressure row); with G = 16 the
-// same arithmetic as k_vanka_resid, wider groups for the long rows of
-// coarse levels.
+// Residuals of one colour's patches: G lanes per row, a patch's rows its
+// velocity nodes and last its pressure. Row-to-row chains bound it (a colour
+// holds a few thousand rows at most), so nothing is searched: descriptor,
+// columns of A and B^T together, x, two entries of A per lane in flight.
 template <int G>
-__global__ void __launch_bounds__(VB) k_vanka_resid_rows(const VankaView v, const int *order, const int *rpre,
-                                                         int count, const int64_t *roff, double *rbuf,
-                                                         const double *b, const double *x) {
-    constexpr int VRW = VB / G;  // node rows per workgroup
-    int lo = 0, hi = count - 1;
-    const int t = blockIdx.x;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (rpre[mid] <= t) lo = mid;
-        else hi = mid - 1;
-    }
-    const int i = order[lo];
-    const int p0 = v.pptr[i], nn = v.pptr[i + 1] - p0;
-    const int grp = threadIdx.x / G, lane = threadIdx.x % G;
-    const int k = (t - rpre[lo]) * VRW + grp;
-    if (k > nn) return;  // whole G-lane groups leave together
-    double *r = rbuf + roff[i];
+__global__ void __launch_bounds__(VB) k_vanka_resid_rows(const VankaView v, int nrows, const int2 *rown,
+                                                         const int4 *rowa, double *rbuf, const double *b,
+                                                         const double *x) {
+    const int t = (blockIdx.x * VB + threadIdx.x) / G, lane = threadIdx.x % G;
+    if (t >= nrows) return;  // whole G-lane groups leave together
+    const int2 rn = rown[t];
+    const int4 ra = rowa[t];
     const int64_t nu = 3 * static_cast<int64_t>(v.n);
     const double *p = x + nu;
-    if (k < nn) {
-        const int u = v.pnode[p0 + k];
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-        for (int q = v.arow[u] + lane; q < v.arow[u + 1]; q += G) {
-            const int j = v.acol[q];
-            const double x0 = x[3 * j], x1 = x[3 * j + 1], x2 = x[3 * j + 2];
-            s0 += v.aval[0 * v.annz + q] * x0 + v.aval[1 * v.annz + q] * x1 + v.aval[2 * v.annz + q] * x2;
-            s1 += v.aval[3 * v.annz + q] * x0 + v.aval[4 * v.annz + q] * x1 + v.aval[5 * v.annz + q] * x2;
-            s2 += v.aval[6 * v.annz + q] * x0 + v.aval[7 * v.annz + q] * x1 + v.aval[8 * v.annz + q] * x2;
+    const int u = rn.x;
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+    if (u >= 0) {
+        const double bi = lane < 3 ? b[3 * static_cast<int64_t>(u) + lane] : 0.0;
+        int q = ra.x + lane, w = ra.z + lane;
+        int j0 = q < ra.y ? v.acol[q] : -1, j1 = q + G < ra.y ? v.acol[q + G] : -1;
+        const int jb = w < ra.w ? v.btcol[w] : -1;
+        for (; q < ra.y; q += 2 * G) {
+            const double *x0 = x + 3 * static_cast<int64_t>(j0 < 0 ? 0 : j0), *x1 = x + 3 * static_cast<int64_t>(j1 < 0 ? 0 : j1);
+            double e0[9], e1[9], y0[3], y1[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                y0[k] = x0[k];
+                y1[k] = j1 < 0 ? 0.0 : x1[k];
+            }
+#pragma unroll
+            for (int k = 0; k < 9; ++k) {
+                e0[k] = v.aval[k * v.annz + q];
+                e1[k] = j1 < 0 ? 0.0 : v.aval[k * v.annz + q + G];
+            }
+            s0 += e0[0] * y0[0] + e0[1] * y0[1] + e0[2] * y0[2];
+            s1 += e0[3] * y0[0] + e0[4] * y0[1] + e0[5] * y0[2];
+            s2 += e0[6] * y0[0] + e0[7] * y0[1] + e0[8] * y0[2];
+            if (j1 >= 0) {
+                s0 += e1[0] * y1[0] + e1[1] * y1[1] + e1[2] * y1[2];
+                s1 += e1[3] * y1[0] + e1[4] * y1[1] + e1[5] * y1[2];
+                s2 += e1[6] * y1[0] + e1[7] * y1[1] + e1[8] * y1[2];
+            }
+            j0 = q + 2 * G < ra.y ? v.acol[q + 2 * G] : -1;
+            j1 = q + 3 * G < ra.y ? v.acol[q + 3 * G] : -1;
         }
-        for (int q = v.btrow[u] + lane; q < v.btrow[u + 1]; q += G) {
-            const double pq = p[v.btcol[q]];
-            s0 += v.btval[q] * pq;
-            s1 += v.btval[v.btnnz + q] * pq;
-            s2 += v.btval[2 * v.btnnz + q] * pq;
+        for (; w < ra.w; w += G) {
+            const double pq = p[w == ra.z + lane ? jb : v.btcol[w]];
+            s0 += v.btval[w] * pq;
+            s1 += v.btval[v.btnnz + w] * pq;
+            s2 += v.btval[2 * v.btnnz + w] * pq;
         }
 #pragma unroll
         for (int o = G / 2; o > 0; o >>= 1) {
@@ -510,69 +350,55 @@ __global__ void __launch_bounds__(VB) k_vanka_resid_rows(const VankaView v, cons
             s1 += __shfl_xor(s1, o, G);
             s2 += __shfl_xor(s2, o, G);
         }
-        if (lane == 0) {
-            r[3 * k] = b[3 * u] - s0;
-            r[3 * k + 1] = b[3 * u + 1] - s1;
-            r[3 * k + 2] = b[3 * u + 2] - s2;
-        }
+        if (lane < 3) rbuf[rn.y + lane] = bi - (lane == 0 ? s0 : (lane == 1 ? s1 : s2));
     } else {
-        double s = 0.0;
-        for (int q = v.brow[i] + lane; q < v.brow[i + 1]; q += G) {
-            const int j = v.bcol[q];
-            s += v.bval[q] * x[3 * j] + v.bval[v.bnnz + q] * x[3 * j + 1] + v.bval[2 * v.bnnz + q] * x[3 * j + 2];
+        // pressure row: g_i - B_i u + C_i p
+        const double bi = lane == 0 ? b[nu + ~u] : 0.0;
+        for (int q = ra.x + lane; q < ra.y; q += G) {
+            const int64_t j = v.bcol[q];
+            s0 += v.bval[q] * x[3 * j] + v.bval[v.bnnz + q] * x[3 * j + 1] + v.bval[2 * v.bnnz + q] * x[3 * j + 2];
         }
-        if (v.crow)
-            for (int q = v.crow[i] + lane; q < v.crow[i + 1]; q += G) s -= v.cval[q] * p[v.ccol[q]];
+        for (int q = ra.z + lane; q < ra.w; q += G) s0 -= v.cval[q] * p[v.ccol[q]];
 #pragma unroll
-        for (int o = G / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, G);
-        if (lane == 0) r[3 * nn] = b[nu + i] - s;
+        for (int o = G / 2; o > 0; o >>= 1) s0 += __shfl_xor(s0, o, G);
+        if (lane == 0) rbuf[rn.y] = bi - s0;
     }
 }
 
-static void resid_rows(const VankaView &v, const int *order, const int *rpre, int count, int nrunits, int rg,
-                       const int64_t *roff, double *rbuf, const double *b, const double *x, hipStream_t s) {
+static void resid_rows(const VankaView &v, const VankaColour &c, int rg, double *rbuf, const double *b,
+                       const double *x, hipStream_t s) {
+    const int nb = ceil_div(static_cast<int64_t>(c.nrows) * rg, VB);
     switch (rg) {
-        case 16: k_vanka_resid_rows<16><<<nrunits, VB, 0, s>>>(v, order, rpre, count, roff, rbuf, b, x); break;
-        case 32: k_vanka_resid_rows<32><<<nrunits, VB, 0, s>>>(v, order, rpre, count, roff, rbuf, b, x); break;
-        case 64: k_vanka_resid_rows<64><<<nrunits, VB, 0, s>>>(v, order, rpre, count, roff, rbuf, b, x); break;
+        case 16: k_vanka_resid_rows<16><<<nb, VB, 0, s>>>(v, c.nrows, c.rown, c.rowa, rbuf, b, x); break;
+        case 32: k_vanka_resid_rows<32><<<nb, VB, 0, s>>>(v, c.nrows, c.rown, c.rowa, rbuf, b, x); break;
+        case 64: k_vanka_resid_rows<64><<<nb, VB, 0, s>>>(v, c.nrows, c.rown, c.rowa, rbuf, b, x); break;
         default: throw Error(AMG_EINVAL, "Vanka residual: 16, 32 or 64 lanes per row");
     }
     AMG_CHECK_LAUNCH();
 }
 
-void launch_vanka_colour_rows(const VankaView &v, const int *order, const int *tpre, const int *rpre, int count,
-                              int ntiles, int nrunits, int rg, int aw, const int64_t *roff, double *rbuf,
+void launch_vanka_colour_rows(const VankaView &v, const VankaColour &c, int rg, int aw, double *rbuf,
                               const double *b, double *x, double omega, hipStream_t s) {
-    if (count <= 0) return;
-    resid_rows(v, order, rpre, count, nrunits, rg, roff, rbuf, b, x, s);
+    if (c.count <= 0) return;
+    resid_rows(v, c, rg, rbuf, b, x, s);
     switch (aw) {
-        case 4: k_vanka_apply<4><<<ntiles, 256, 0, s>>>(v, order, tpre, count, roff, rbuf, x, omega); break;
-        case 8: k_vanka_apply<8><<<ntiles, 512, 0, s>>>(v, order, tpre, count, roff, rbuf, x, omega); break;
-        case 16: k_vanka_apply<16><<<ntiles, 1024, 0, s>>>(v, order, tpre, count, roff, rbuf, x, omega); break;
+        case 4: k_vanka_apply<4><<<c.ntiles, 256, 0, s>>>(v, c.tile, rbuf, x, omega); break;
+        case 8: k_vanka_apply<8><<<c.ntiles, 512, 0, s>>>(v, c.tile, rbuf, x, omega); break;
+        case 16: k_vanka_apply<16><<<c.ntiles, 1024, 0, s>>>(v, c.tile, rbuf, x, omega); break;
         default: throw Error(AMG_EINVAL, "Vanka corrections: 4, 8 or 16 wavefronts per tile");
     }
     AMG_CHECK_LAUNCH();
 }
 
-void launch_vanka_colour_tiled(const VankaView &v, const int *order, const int *tpre, const int *upre,
-                               const int *rpre, int count, int ntiles, int nunits, int nrunits, int cc, int rg,
-                               const int64_t *roff, double *rbuf, const int64_t *poff, double *pbuf, const double *b,
-                               double *x, double omega, hipStream_t s) {
-    if (count <= 0) return;
-    resid_rows(v, order, rpre, count, nrunits, rg, roff, rbuf, b, x, s);
-    k_vanka_apply_part<<<nunits, VB, 0, s>>>(v, order, upre, count, cc, roff, rbuf, poff, pbuf);
+void launch_vanka_colour_tiled(const VankaView &v, const VankaColour &c, const int *order, const int *tpre,
+                               const int *upre, int nunits, int cc, int rg, const int64_t *roff, double *rbuf,
+                               const int64_t *poff, double *pbuf, const double *b, double *x, double omega,
+                               hipStream_t s) {
+    if (c.count <= 0) return;
+    resid_rows(v, c, rg, rbuf, b, x, s);
+    k_vanka_apply_part<<<nunits, VB, 0, s>>>(v, order, upre, c.count, cc, roff, rbuf, poff, pbuf);
     AMG_CHECK_LAUNCH();
-    k_vanka_reduce<<<ntiles, 64, 0, s>>>(v, order, tpre, count, cc, poff, pbuf, x, omega);
-    AMG_CHECK_LAUNCH();
-}
-
-void launch_vanka_colour_split(const VankaView &v, const int *order, const int *tpre, int count, int ntiles,
-                               int max_nodes, const int64_t *roff, double *rbuf, const double *b, double *x,
-                               double omega, hipStream_t s) {
-    if (count <= 0) return;
-    k_vanka_resid<<<count, VCB, max_nodes * sizeof(int), s>>>(v, order, roff, rbuf, b, x);
-    AMG_CHECK_LAUNCH();
-    k_vanka_apply<4><<<ntiles, 256, 0, s>>>(v, order, tpre, count, roff, rbuf, x, omega);
+    k_vanka_reduce<<<c.ntiles, 64, 0, s>>>(v, order, tpre, c.count, cc, poff, pbuf, x, omega);
     AMG_CHECK_LAUNCH();
 }
 

@@ -551,25 +551,7 @@ static void vanka_step(amg_ctx *h, int l, const double *b, double *x) {
     const VankaView v = vanka_view(L);
     const int nc = static_cast<int>(L.vanka.cptr.size()) - 1;
     ProfScope ps(h, tag("vanka", l), L.vanka.inv_bytes);  // algorithmic: the patch inverses
-    VankaData &V = L.vanka;
-    for (int c = 0; c < nc; ++c) {
-        const int cnt = V.cptr[c + 1] - V.cptr[c];
-        if (V.path == 2)
-            launch_vanka_colour_tiled(v, V.order.p + V.cptr[c], V.tpre.p + V.cptr[c], V.upre.p + V.cptr[c],
-                                      V.rpre[VankaData::rg_index(V.rg)].p + V.cptr[c], cnt, V.ntiles[c], V.nunits[c],
-                                      V.nrunits[VankaData::rg_index(V.rg)][c], V.cc, V.rg,
-                                      V.roff.p, V.rbuf.p, V.poff.p, V.pbuf.p, b, x, h->prm.vanka_omega, h->stream);
-        else if (V.path == 3)
-            launch_vanka_colour_rows(v, V.order.p + V.cptr[c], V.tpre.p + V.cptr[c],
-                                     V.rpre[VankaData::rg_index(V.rg)].p + V.cptr[c], cnt, V.ntiles[c],
-                                     V.nrunits[VankaData::rg_index(V.rg)][c], V.rg, V.aw, V.roff.p, V.rbuf.p, b, x,
-                                     h->prm.vanka_omega, h->stream);
-        else if (V.path == 1)
-            launch_vanka_colour_split(v, V.order.p + V.cptr[c], V.tpre.p + V.cptr[c], cnt, V.ntiles[c], V.max_nodes,
-                                      V.roff.p, V.rbuf.p, b, x, h->prm.vanka_omega, h->stream);
-        else
-            launch_vanka_colour(v, V.order.p + V.cptr[c], cnt, V.max_nodes, b, x, h->prm.vanka_omega, h->stream);
-    }
+    for (int c = 0; c < nc; ++c) launch_vanka(L, v, c, b, x, h->prm.vanka_omega, h->stream);
 }
 static void vanka_step(amg_ctx *, int, const float *, float *) {
     throw Error(AMG_EUNSUPPORTED, "the Vanka smoother runs in FP64");

@@ -36,34 +36,45 @@ struct VankaView {
 // inverses in place; flag |= 1 on an exactly zero pivot
 void launch_vanka_assemble(const VankaView &v, int max_nodes, hipStream_t s);
 void launch_vanka_invert(const VankaView &v, int max_m, int *flag, hipStream_t s);
-// one colour: the patches order[0 .. count); x = [u (3n); p]
-void launch_vanka_colour(const VankaView &v, const int *order, int count, int max_nodes, const double *b,
-                         double *x, double omega, hipStream_t s);
-// the same colour in two kernels, for large patches: the patches' residuals
-// into rbuf (patch i at rbuf + roff[i]), then the corrections with
-// ceil(m_i / 64) workgroups per patch (tpre: prefix of those counts over the
-// colour's patches, ntiles their total)
-void launch_vanka_colour_split(const VankaView &v, const int *order, const int *tpre, int count, int ntiles,
-                               int max_nodes, const int64_t *roff, double *rbuf, const double *b, double *x,
-                               double omega, hipStream_t s);
-// the residual spread as in the tiled form (rpre, nrunits, rg), then the
-// corrections over 64-row tiles of every inverse as the two-kernel form
-// (tpre, ntiles), aw (4, 8 or 16) wavefronts per tile splitting its columns
-void launch_vanka_colour_rows(const VankaView &v, const int *order, const int *tpre, const int *rpre, int count,
-                              int ntiles, int nrunits, int rg, int aw, const int64_t *roff, double *rbuf,
+// 64 rows of a patch's correction
+struct VankaTile {
+    int64_t inv = 0;   // the patch's inverse in VankaView::inv
+    int m = 0;         // its unknowns
+    int row0 = 0;      // first row of the tile
+    int res = 0;       // the patch's residual in rbuf
+    int node0 = 0;     // its first node in pnode
+    int patch = 0;
+    int pad = 0;
+};
+
+// What one colour's patches read: their residual rows (a patch's velocity
+// nodes, then its pressure; rown: node, or ~pressure, and place in rbuf;
+// rowa: entries of A and B^T, or of B and C) and their correction tiles
+struct VankaColour {
+    int count = 0, nrows = 0, ntiles = 0;
+    const int2 *rown = nullptr;
+    const int4 *rowa = nullptr;
+    const VankaTile *tile = nullptr;
+};
+
+// rowa from rown and the level's operators
+void launch_vanka_rows(const VankaView &v, int nrows, const int2 *rown, int4 *rowa, hipStream_t s);
+// One colour, x = [u (3n); p], in two kernels: the patches' residuals into
+// rbuf, rg lanes per row (16, 32 or 64), then the corrections over 64-row
+// tiles of every inverse, aw (4, 8 or 16) wavefronts per tile splitting its
+// columns.
+void launch_vanka_colour_rows(const VankaView &v, const VankaColour &c, int rg, int aw, double *rbuf,
                               const double *b, double *x, double omega, hipStream_t s);
-// the same colour in three kernels for colours of few, large patches: the
-// residuals into rbuf, rg lanes per row (16, 32 or 64) and 256 / rg node
-// rows per workgroup (rpre: prefix of ceil((n_P + 1) / (256 / rg)) over the
-// colour's patches, nrunits their total),
+// The same colour in three kernels, for few, large patches: the residuals,
 // then partial corrections over 64-row x cc-column tiles of every inverse
 // into pbuf (patch i's ceil(m_i / cc) chunks of m_i values at pbuf +
-// poff[i]; upre: prefix of the tiles ceil(m_i / 64) ceil(m_i / cc) over the
-// colour's patches, nunits their total), then the chunks summed in order
-// into x over the 64-row tiles (tpre, ntiles)
-void launch_vanka_colour_tiled(const VankaView &v, const int *order, const int *tpre, const int *upre,
-                               const int *rpre, int count, int ntiles, int nunits, int nrunits, int cc, int rg,
-                               const int64_t *roff, double *rbuf, const int64_t *poff, double *pbuf, const double *b,
-                               double *x, double omega, hipStream_t s);
+// poff[i]; its residual at rbuf + roff[i]; upre: prefix of the tiles
+// ceil(m_i / 64) ceil(m_i / cc) over the colour's patches order[0 .. count),
+// nunits their total), then the chunks summed in order into x over the
+// 64-row tiles (tpre: prefix of their counts over the colour's patches)
+void launch_vanka_colour_tiled(const VankaView &v, const VankaColour &c, const int *order, const int *tpre,
+                               const int *upre, int nunits, int cc, int rg, const int64_t *roff, double *rbuf,
+                               const int64_t *poff, double *pbuf, const double *b, double *x, double omega,
+                               hipStream_t s);
 
 }  // namespace amgp2
