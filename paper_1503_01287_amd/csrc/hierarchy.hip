@@ -321,6 +321,7 @@ static void setup_smoother(amg_ctx *h, Level &L) {
     L.cptr.assign(ncol + 1, 0);
     for (int i = 0; i < L.n; ++i) ++L.cptr[L.colour[i] + 1];
     std::partial_sum(L.cptr.begin(), L.cptr.end(), L.cptr.begin());
+    if (h->batch_member) return;  // (its sweeps run on the merged levels)
     std::vector<int> grp(L.n + 1, 0);
     L.colour_nnz.assign(ncol, 0);
     const std::vector<int> arp = L.A.rowptr.download(s);  // stored rows (zero blocks dropped)
@@ -729,7 +730,7 @@ void setup_schur(amg_ctx *h, int l) {
         std::vector<int> order(std::max(1, n)), next(q.cptr.begin(), q.cptr.end() - 1);
         for (int i = 0; i < n; ++i) order[next[colour[i]]++] = i;
         q.rowid.upload(order, s);
-        group_schur_rows(q, s);
+        if (!h->batch_member) group_schur_rows(q, s);
         q.dinv.alloc(std::max(1, n));
         DevBuf<int> flag(1);
         flag.zero(s);
