@@ -500,7 +500,7 @@ void build_batch(amg_ctx *h, int nsys, const amg_system *sys) {
     h->partial.alloc(static_cast<size_t>(std::max(1024 * 128, row_blocks(h->lv[0].n, 64))));
     h->tune_flush.release();
     h->sc.alloc(SC_COUNT);
-    if (!h->h_sc) AMG_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->h_sc), SC_COUNT * sizeof(double)));
+    if (!h->h_sc) AMG_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->h_sc), SC_COUNT * sizeof(double), hipHostMallocCoherent));
     AMG_HIP(hipStreamSynchronize(s));
 }
 
@@ -769,7 +769,7 @@ void build_batch_spd(amg_ctx *h, int nsys, const amg_system *sys) {
     }
     h->tune_flush.release();
     h->sc.alloc(SC_COUNT);
-    if (!h->h_sc) AMG_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->h_sc), SC_COUNT * sizeof(double)));
+    if (!h->h_sc) AMG_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->h_sc), SC_COUNT * sizeof(double), hipHostMallocCoherent));
     AMG_HIP(hipStreamSynchronize(s));
 }
 

@@ -289,6 +289,8 @@ struct ProfStat {
 
 struct amg_ctx_impl;
 
+enum GraphKind : int { GRAPH_PRECONDITION = 0, GRAPH_CG_STEP, GRAPH_CG_NEXT };
+
 }  // namespace amgp2
 
 struct amg_ctx {
@@ -352,15 +354,16 @@ struct amg_ctx {
     amgp2::DevBuf<double> b_b, b_x;                   // merged-layout right-hand side / iterate
     // recorded preconditioner applications (HIP graphs) and staging vectors
     struct GraphEntry {
-        const double *r;
+        int kind;         // GraphKind
+        const double *r;  // of a preconditioner application
         double *z;
-        bool filled;
         hipGraphExec_t exec;
     };
     std::vector<GraphEntry> graphs;
     amgp2::DevBuf<double> g_in, g_out;
     // Krylov workspace
     amgp2::DevBuf<double> kr, kz, kp, kq, kw;
+    amgp2::DevBuf<double> kx;  // the iterate of a solve whose iterations are replayed graphs
     amgp2::MultiWork multi;  // amg_solve_multi
     amgp2::DevBuf<double> partial, sc;
     double *h_sc = nullptr;  // pinned host copy of the scalars

@@ -448,12 +448,16 @@ int launch_dot_partial(const double *a, const double *b, int64_t n, double *part
 constexpr int RBLOCK = 1024;
 
 template <int POST>
-__global__ void __launch_bounds__(RBLOCK) k_reduce(const double *partial, int np, double *sc, int dst) {
+__global__ void __launch_bounds__(RBLOCK) k_reduce(const double *partial, int np, double *sc, int dst, double *host) {
     double acc = 0.0;
     for (int i = threadIdx.x; i < np; i += RBLOCK) acc += partial[i];
     const double t = block_sum<RBLOCK>(acc);
     if (threadIdx.x != 0) return;
     sc[dst] = t;
+    if (host) {
+        host[dst] = t;
+        host[SC_PQ] = sc[SC_PQ];
+    }
     if constexpr (POST == RED_CG_ALPHA) {
         sc[SC_ALPHA] = sc[SC_RZ] / t;
     } else if constexpr (POST == RED_CG_BETA) {
@@ -467,20 +471,20 @@ __global__ void __launch_bounds__(RBLOCK) k_reduce(const double *partial, int np
     }
 }
 
-void launch_reduce(const double *partial, int np, double *sc, int dst, hipStream_t s, int post) {
+void launch_reduce(const double *partial, int np, double *sc, int dst, hipStream_t s, int post, double *host) {
     switch (post) {
-        case RED_NONE: k_reduce<RED_NONE><<<1, RBLOCK, 0, s>>>(partial, np, sc, dst); break;
-        case RED_CG_ALPHA: k_reduce<RED_CG_ALPHA><<<1, RBLOCK, 0, s>>>(partial, np, sc, dst); break;
-        case RED_CG_BETA: k_reduce<RED_CG_BETA><<<1, RBLOCK, 0, s>>>(partial, np, sc, dst); break;
-        case RED_FCG_BETA: k_reduce<RED_FCG_BETA><<<1, RBLOCK, 0, s>>>(partial, np, sc, dst); break;
-        case RED_FCG_ALPHA: k_reduce<RED_FCG_ALPHA><<<1, RBLOCK, 0, s>>>(partial, np, sc, dst); break;
+        case RED_NONE: k_reduce<RED_NONE><<<1, RBLOCK, 0, s>>>(partial, np, sc, dst, host); break;
+        case RED_CG_ALPHA: k_reduce<RED_CG_ALPHA><<<1, RBLOCK, 0, s>>>(partial, np, sc, dst, host); break;
+        case RED_CG_BETA: k_reduce<RED_CG_BETA><<<1, RBLOCK, 0, s>>>(partial, np, sc, dst, host); break;
+        case RED_FCG_BETA: k_reduce<RED_FCG_BETA><<<1, RBLOCK, 0, s>>>(partial, np, sc, dst, host); break;
+        case RED_FCG_ALPHA: k_reduce<RED_FCG_ALPHA><<<1, RBLOCK, 0, s>>>(partial, np, sc, dst, host); break;
         default: throw Error(AMG_EINVAL, "reduce: unknown post operation");
     }
     AMG_CHECK_LAUNCH();
 }
 
 __global__ void k_cg_update(double *x, double *r, const double *p, const double *q, const double *sc,
-                            int64_t n, double *partial, double *zero) {
+                            int64_t n, double *partial) {
     const double al = sc[SC_ALPHA];
     double acc = 0.0;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * BLOCK + threadIdx.x; i < n;
@@ -489,16 +493,15 @@ __global__ void k_cg_update(double *x, double *r, const double *p, const double 
         const double ri = r[i] - al * q[i];
         r[i] = ri;
         acc += ri * ri;
-        if (zero) zero[i] = 0.0;
     }
     const double t = block_sum(acc);
     if (threadIdx.x == 0) partial[blockIdx.x] = t;
 }
 
 int launch_cg_update(double *x, double *r, const double *p, const double *q, const double *sc,
-                     int64_t n, double *partial, double *zero, hipStream_t s) {
+                     int64_t n, double *partial, hipStream_t s) {
     const int nb = dot_blocks(n);
-    k_cg_update<<<nb, BLOCK, 0, s>>>(x, r, p, q, sc, n, partial, zero);
+    k_cg_update<<<nb, BLOCK, 0, s>>>(x, r, p, q, sc, n, partial);
     AMG_CHECK_LAUNCH();
     return nb;
 }

@@ -90,10 +90,12 @@ enum ReducePost : int {
     RED_FCG_BETA,   // dst = TMP: beta = -tmp / pq_prev
     RED_FCG_ALPHA,  // dst = PR:  alpha = pr / pq, pq_prev = pq
 };
-void launch_reduce(const double *partial, int np, double *sc, int dst, hipStream_t s, int post = RED_NONE);
-// x += alpha p; r -= alpha q; partial of <r, r>; zero[i] = 0 if zero != nullptr
+// host: if set, sc[dst] and sc[SC_PQ] are also written there (pinned memory)
+void launch_reduce(const double *partial, int np, double *sc, int dst, hipStream_t s, int post = RED_NONE,
+                   double *host = nullptr);
+// x += alpha p; r -= alpha q; partial of <r, r>
 int launch_cg_update(double *x, double *r, const double *p, const double *q, const double *sc,
-                     int64_t n, double *partial, double *zero, hipStream_t s);
+                     int64_t n, double *partial, hipStream_t s);
 // p = z + beta p  (beta from sc)
 void launch_cg_direction(double *p, const double *z, const double *sc, int64_t n, hipStream_t s);
 // y = a x + b y with host scalars

@@ -299,8 +299,7 @@ void vcycle(amg_ctx *h, int l, const double *b, double *x) { cycle(h, l, b, x, t
 
 // z = M^{-1} r: `cycles` successive applications of Algorithm 1 on the
 // finest level, the first from z = 0, each further one from the current z.
-// z_filled: z already holds zeros.
-static void precondition_eager(amg_ctx *h, const double *r, double *z, bool z_filled) {
+static void precondition_eager(amg_ctx *h, const double *r, double *z) {
     if (h->saddle) {
         saddle_precondition(h, r, z);
         return;
@@ -310,18 +309,16 @@ static void precondition_eager(amg_ctx *h, const double *r, double *z, bool z_fi
         return;
     }
     const int cyc = std::max(1, h->prm.cycles);
-    for (int k = 0; k < cyc; ++k) cycle(h, 0, r, z, k == 0, k == 0 && z_filled);
+    for (int k = 0; k < cyc; ++k) cycle(h, 0, r, z, k == 0, false);
 }
 
-// The preconditioner's launches recorded once into a HIP graph per (r, z)
-// pair and replayed: one launch call instead of hundreds. The recording
-// runs on a stream of the library's own (a capture cannot run on the legacy
-// default stream) and contains kernels only: no host synchronisation, no
-// memset nodes, no event records (profiling runs eagerly).
-static hipGraphExec_t graph_for(amg_ctx *h, const double *r, double *z, bool z_filled) {
-    for (const auto &g : h->graphs)
-        if (g.r == r && g.z == z && g.filled == z_filled) return g.exec;
-    if (h->graphs.size() >= 8) return nullptr;
+// Launches recorded once into a HIP graph and replayed: one launch call
+// instead of hundreds. The recording runs on a stream of the library's own (a
+// capture cannot run on the legacy default stream) and contains kernels only:
+// no host synchronisation, no memset or copy nodes, no event records
+// (profiling runs eagerly).
+template <typename F>
+static hipGraphExec_t record_graph(amg_ctx *h, F &&launches) {
     hipStream_t cs = nullptr;
     AMG_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
     // the capture stream must see everything ordered before it on the caller's stream
@@ -335,7 +332,7 @@ static hipGraphExec_t graph_for(amg_ctx *h, const double *r, double *z, bool z_f
     h->stream = cs;
     AMG_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed));
     try {
-        precondition_eager(h, r, z, z_filled);
+        launches();
     } catch (...) {
         (void)hipStreamEndCapture(cs, &graph);
         if (graph) (void)hipGraphDestroy(graph);
@@ -351,26 +348,34 @@ static hipGraphExec_t graph_for(amg_ctx *h, const double *r, double *z, bool z_f
     AMG_HIP(hipStreamSynchronize(cs));
     AMG_HIP(hipStreamDestroy(cs));
     AMG_HIP(hipEventDestroy(ev));
-    h->graphs.push_back({r, z, z_filled, exec});
     return exec;
 }
 
+// the preconditioner's graph, one per (r, z) pair
+static hipGraphExec_t graph_for(amg_ctx *h, const double *r, double *z) {
+    for (const auto &g : h->graphs)
+        if (g.kind == GRAPH_PRECONDITION && g.r == r && g.z == z) return g.exec;
+    if (h->graphs.size() >= 8) return nullptr;
+    h->graphs.push_back({GRAPH_PRECONDITION, r, z, record_graph(h, [&] { precondition_eager(h, r, z); })});
+    return h->graphs.back().exec;
+}
+
 // z = M^{-1} r for pointers that stay the same from call to call
-static void precondition_impl(amg_ctx *h, const double *r, double *z, bool z_filled) {
+static void precondition_impl(amg_ctx *h, const double *r, double *z) {
     if (h->prm.graph && !h->prof) {
-        if (hipGraphExec_t g = graph_for(h, r, z, z_filled)) {
+        if (hipGraphExec_t g = graph_for(h, r, z)) {
             AMG_HIP(hipGraphLaunch(g, h->stream));
             return;
         }
     }
-    precondition_eager(h, r, z, z_filled);
+    precondition_eager(h, r, z);
 }
 
 // z = M^{-1} r for pointers that change from call to call (the flexible
 // GMRES basis): through staging vectors so that one recording serves all
 void precondition_staged(amg_ctx *h, const double *r, double *z) {
     if (!h->prm.graph || h->prof) {
-        precondition_eager(h, r, z, false);
+        precondition_eager(h, r, z);
         return;
     }
     if (h->g_in.n != static_cast<size_t>(h->n_dof)) {
@@ -378,11 +383,11 @@ void precondition_staged(amg_ctx *h, const double *r, double *z) {
         h->g_out.alloc(h->n_dof);
     }
     launch_copy(h->g_in.p, r, h->n_dof, h->stream);
-    precondition_impl(h, h->g_in.p, h->g_out.p, false);
+    precondition_impl(h, h->g_in.p, h->g_out.p);
     launch_copy(z, h->g_out.p, h->n_dof, h->stream);
 }
 
-void precondition(amg_ctx *h, const double *r, double *z) { precondition_impl(h, r, z, false); }
+void precondition(amg_ctx *h, const double *r, double *z) { precondition_impl(h, r, z); }
 
 }  // namespace amgp2
 
@@ -395,11 +400,11 @@ static double read_scalar(amg_ctx *h, int idx) {
     return h->h_sc[idx];
 }
 
-// The scalars' copy to the host, waited on separately (scalars_wait), so
-// that work enqueued in between overlaps the host's round trip.
+// The stopping test's scalars, which the update's reduction has written to
+// pinned host memory, waited on separately (scalars_wait), so that work
+// enqueued in between overlaps the host's round trip.
 static void scalars_begin(amg_ctx *h) {
     if (!h->sc_ready) AMG_HIP(hipEventCreateWithFlags(&h->sc_ready, hipEventDisableTiming));
-    AMG_HIP(hipMemcpyAsync(h->h_sc, h->sc.p, SC_COUNT * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     AMG_HIP(hipEventRecord(h->sc_ready, h->stream));
 }
 static void scalars_wait(amg_ctx *h) { AMG_HIP(hipEventSynchronize(h->sc_ready)); }
@@ -431,12 +436,60 @@ static void spmv_dot(amg_ctx *h, const double *p, double *q, int post) {
     launch_reduce(h->partial.p, row_blocks(L.n, L.G), h->sc.p, SC_PQ, h->stream, post);
 }
 
-// x += alpha p, r -= alpha q, <r, r> into sc[SC_RR]; zeroes z for the next
-// preconditioner application
-static void cg_update(amg_ctx *h, double *x, double *r, const double *p, const double *q, double *z) {
-    ProfScope ps(h, "blas", 7.0 * h->n_dof * 8.0);
-    const int nb = launch_cg_update(x, r, p, q, h->sc.p, h->n_dof, h->partial.p, z, h->stream);
-    launch_reduce(h->partial.p, nb, h->sc.p, SC_RR, h->stream);
+// x += alpha p, r -= alpha q, <r, r> into sc[SC_RR] and, with <p, q>, into
+// the host's copy
+static void cg_update(amg_ctx *h, double *x, double *r, const double *p, const double *q) {
+    ProfScope ps(h, "blas", 6.0 * h->n_dof * 8.0);
+    const int nb = launch_cg_update(x, r, p, q, h->sc.p, h->n_dof, h->partial.p, h->stream);
+    launch_reduce(h->partial.p, nb, h->sc.p, SC_RR, h->stream, RED_NONE, h->h_sc);
+}
+
+// One iteration in two halves, either of which a small system replays as one
+// graph: its kernels take 2-5 us each, as long as their launch calls on the
+// host (Laplacian 4^3, 10 calls an iteration: 61 us of which the GPU works
+// 28). cg_step: up to the stopping test's scalars; cg_next: the next
+// direction, which may go ahead of that test (it leaves x and r alone).
+static void cg_step(amg_ctx *h, bool fcg, double *x) {
+    double *r = h->kr.p, *p = h->kp.p, *q = h->kq.p;
+    if (fcg) {
+        spmv_dot(h, p, q, RED_NONE);
+        dot_into(h, p, r, SC_PR, RED_FCG_ALPHA);
+    } else {
+        spmv_dot(h, p, q, RED_CG_ALPHA);
+    }
+    cg_update(h, x, r, p, q);
+}
+static void cg_next_direction(amg_ctx *h, bool fcg) {
+    double *r = h->kr.p, *z = h->kz.p, *p = h->kp.p, *q = h->kq.p;
+    // PCG: p = z + (<r, z> / <r, z>_prev) p; FCG: p = z - (<z, q> / <p, q>) p
+    if (fcg)
+        dot_into(h, z, q, SC_TMP, RED_FCG_BETA);
+    else
+        dot_into(h, r, z, SC_TMP, RED_CG_BETA);
+    launch_cg_direction(p, z, h->sc.p, h->n_dof, h->stream);
+}
+static void cg_next(amg_ctx *h, bool fcg) {
+    precondition_impl(h, h->kr.p, h->kz.p);
+    cg_next_direction(h, fcg);
+}
+
+// Unknowns up to which CG replays its iteration as two graphs: beyond, an
+// iteration works longer on the GPU than its launch calls take (elasticity
+// 21^3, 238,521 unknowns: no difference), and the iterate's two copies count.
+constexpr int CG_GRAPH_MAX = 100000;
+
+static hipGraphExec_t cg_graph(amg_ctx *h, int kind, bool fcg) {
+    for (const auto &g : h->graphs)
+        if (g.kind == kind) return g.exec;
+    h->graphs.push_back({kind, nullptr, nullptr, record_graph(h, [&] {
+                             if (kind == GRAPH_CG_STEP) {
+                                 cg_step(h, fcg, h->kx.p);
+                             } else {
+                                 precondition_eager(h, h->kr.p, h->kz.p);
+                                 cg_next_direction(h, fcg);
+                             }
+                         })});
+    return h->graphs.back().exec;
 }
 
 double true_relres(amg_ctx *h, const double *b, const double *x, double r0norm) {
@@ -469,78 +522,61 @@ static int check(double rr, double rr0, double tol) {
     return -1;
 }
 
-int solve_pcg(amg_ctx *h, const double *b, double *x, double tol, int maxit, amg_result *res) {
+static int solve_cg(amg_ctx *h, bool fcg, const double *b, double *x, double tol, int maxit, amg_result *res) {
     const auto t0 = std::chrono::steady_clock::now();
     const int64_t n = h->n_dof;
-    double *r = h->kr.p, *z = h->kz.p, *p = h->kp.p, *q = h->kq.p;
+    double *r = h->kr.p, *z = h->kz.p, *p = h->kp.p;
     residual(h, 0, b, x, r);
     dot_into(h, r, r, SC_RR);
     const double rr0 = read_scalar(h, SC_RR);
     const double r0 = std::sqrt(rr0);
     if (rr0 == 0.0) return finish(h, b, x, r0, 0, AMG_OK, t0, res);
     if (!(rr0 == rr0)) return finish(h, b, x, r0, 0, AMG_DIVERGED, t0, res);
-    precondition(h, r, z);
-    dot_into(h, r, z, SC_RZ);
+    if (maxit <= 0) return finish(h, b, x, r0, 0, AMG_NOT_CONVERGED, t0, res);
+    const bool graphs = h->prm.graph && !h->prof && n <= CG_GRAPH_MAX;
+    double *xi = x;  // the iterate (recorded launches need a place of their own for it)
+    hipGraphExec_t step = nullptr, next = nullptr;
+    if (graphs) {
+        if (h->kx.n != static_cast<size_t>(n)) h->kx.alloc(static_cast<size_t>(n));
+        xi = h->kx.p;
+        launch_copy(xi, x, n, h->stream);
+        step = cg_graph(h, GRAPH_CG_STEP, fcg);
+        next = cg_graph(h, GRAPH_CG_NEXT, fcg);
+    }
+    precondition_impl(h, r, z);
+    if (!fcg) dot_into(h, r, z, SC_RZ);
     launch_copy(p, z, n, h->stream);
     int it = 0, status = AMG_NOT_CONVERGED;
     double rel = 1.0;
     while (it < maxit) {
-        spmv_dot(h, p, q, RED_CG_ALPHA);
-        cg_update(h, x, r, p, q, z);
+        if (step) AMG_HIP(hipGraphLaunch(step, h->stream));
+        else cg_step(h, fcg, xi);
         ++it;
         scalars_begin(h);
         const bool ahead = it < maxit && rel > KRYLOV_AHEAD * tol;
-        if (ahead) precondition_impl(h, r, z, true);
+        auto go = [&] {
+            if (next) AMG_HIP(hipGraphLaunch(next, h->stream));
+            else cg_next(h, fcg);
+        };
+        if (ahead) go();
         scalars_wait(h);
         const double rr = h->h_sc[SC_RR];
         if (!(h->h_sc[SC_PQ] > 0.0)) { status = AMG_BREAKDOWN; break; }
         const int c = check(rr, rr0, tol);
         if (c >= 0) { status = c; break; }
         rel = std::sqrt(rr / rr0);
-        if (!ahead) precondition_impl(h, r, z, true);
-        dot_into(h, r, z, SC_TMP, RED_CG_BETA);
-        launch_cg_direction(p, z, h->sc.p, n, h->stream);
+        if (!ahead && it < maxit) go();
     }
+    if (xi != x) launch_copy(x, xi, n, h->stream);
     return finish(h, b, x, r0, it, status, t0, res);
 }
 
+int solve_pcg(amg_ctx *h, const double *b, double *x, double tol, int maxit, amg_result *res) {
+    return solve_cg(h, false, b, x, tol, maxit, res);
+}
+
 int solve_fcg(amg_ctx *h, const double *b, double *x, double tol, int maxit, amg_result *res) {
-    const auto t0 = std::chrono::steady_clock::now();
-    const int64_t n = h->n_dof;
-    double *r = h->kr.p, *z = h->kz.p, *p = h->kp.p, *q = h->kq.p;
-    residual(h, 0, b, x, r);
-    dot_into(h, r, r, SC_RR);
-    const double rr0 = read_scalar(h, SC_RR);
-    const double r0 = std::sqrt(rr0);
-    if (rr0 == 0.0) return finish(h, b, x, r0, 0, AMG_OK, t0, res);
-    if (!(rr0 == rr0)) return finish(h, b, x, r0, 0, AMG_DIVERGED, t0, res);
-    int it = 0, status = AMG_NOT_CONVERGED;
-    double rel = 1.0;
-    bool ahead = false;  // this iteration's preconditioner already enqueued
-    while (it < maxit) {
-        if (!ahead) precondition_impl(h, r, z, it > 0);
-        if (it == 0) {
-            launch_copy(p, z, n, h->stream);
-        } else {
-            // p = z - (<z, q_prev> / <p_prev, q_prev>) p_prev
-            dot_into(h, z, q, SC_TMP, RED_FCG_BETA);
-            launch_cg_direction(p, z, h->sc.p, n, h->stream);
-        }
-        spmv_dot(h, p, q, RED_NONE);
-        dot_into(h, p, r, SC_PR, RED_FCG_ALPHA);
-        cg_update(h, x, r, p, q, z);
-        ++it;
-        scalars_begin(h);
-        ahead = it < maxit && rel > KRYLOV_AHEAD * tol;
-        if (ahead) precondition_impl(h, r, z, true);
-        scalars_wait(h);
-        const double rr = h->h_sc[SC_RR];
-        if (!(h->h_sc[SC_PQ] > 0.0)) { status = AMG_BREAKDOWN; break; }
-        const int c = check(rr, rr0, tol);
-        if (c >= 0) { status = c; break; }
-        rel = std::sqrt(rr / rr0);
-    }
-    return finish(h, b, x, r0, it, status, t0, res);
+    return solve_cg(h, true, b, x, tol, maxit, res);
 }
 
 // Stand-alone AMG: repeated Algorithm 1 from the current iterate.
