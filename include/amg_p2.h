@@ -341,7 +341,9 @@ int amg_get_level_colors(amg_handle h, int32_t level, int32_t *colors);
  * the FP64 colour sweeps, AMG_SHAPE_NATURAL_RP / AMG_SHAPE_SWEEP_RP the same
  * kernels of the reduced-precision copies. (All colours of a sweep run in
  * one launch by default; a level whose sweep shape is set here runs one
- * launch of that shape per colour, followed by a natural-order residual.) lanes: lanes of the 64-wide
+ * launch of that shape per colour, followed by a natural-order residual.
+ * Likewise a large scalar finest level runs its natural-order kernels in
+ * tiles of rows until their shape is set here.) lanes: lanes of the 64-wide
  * wavefront per row, one of 4, 8, 16, 32, 64. trip: entries per lane and
  * loop trip, 1, 2 or 4 (a lane's entries of one trip have their loads in
  * flight together; the sums do not depend on it; the prolongation kernels

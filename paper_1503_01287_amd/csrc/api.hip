@@ -627,7 +627,11 @@ int amg_set_launch_shape(amg_handle h, int32_t level, int32_t kernels, int32_t l
         const bool sweep = kernels == AMG_SHAPE_SWEEP || kernels == AMG_SHAPE_SWEEP_RP;
         AMG_REQUIRE(sweep || xcd == 0, AMG_EINVAL, "amg_set_launch_shape: xcd applies to colour sweeps only");
         switch (kernels) {
-            case AMG_SHAPE_NATURAL: L.G = lanes; L.trip = trip; break;
+            case AMG_SHAPE_NATURAL:
+                L.G = lanes;
+                L.trip = trip;
+                L.by_rows = true;
+                break;
             case AMG_SHAPE_SWEEP:
                 L.Gg = lanes;
                 L.tripg = trip;
@@ -640,6 +644,7 @@ int amg_set_launch_shape(amg_handle h, int32_t level, int32_t kernels, int32_t l
                 if (kernels == AMG_SHAPE_NATURAL_RP) {
                     L.mp.G = lanes;
                     L.mp.trip = trip;
+                    L.mp.by_rows = true;
                 } else {
                     L.mp.Gg = lanes;
                     L.mp.tripg = trip;

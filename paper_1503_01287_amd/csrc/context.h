@@ -14,6 +14,7 @@
 #include "mixed.h"
 #include "saddle.h"
 #include "sweep.h"
+#include "tile.h"
 #include "tail.h"
 #include "vanka.h"
 
@@ -36,6 +37,7 @@ struct LevelMP {
     int xcd = 0;                   // per-XCD contiguous rows in the colour sweeps (as Level::gs_xcd)
     SweepShape shape;              // of its one-launch sweeps
     bool by_colour = false;        // as Level::by_colour
+    bool by_rows = false;          // as Level::by_rows
     DevBuf<float> a32, ag32;       // FP32 planes
     DevBuf<uint16_t> a16, ag16;    // BF16 planes (values / row scale)
     DevBuf<float> scale;           // BF16: scale of every scalar row
@@ -110,6 +112,33 @@ struct SweepData {
     void build(const std::vector<int> &cptr, const std::vector<int> &rowid, int n, int stride, hipStream_t s);
     bool usable() const { return ncolors > 0 && ncolors <= SWEEP_MAX_COLOURS; }
     void fill(SweepArgs &a, const SweepShape &q, const SweepBuf &buf) const;
+};
+
+// The finest level's natural-order operator in tiles (k_tile.hip), with the
+// values that its kernels read: FP64 (the outer operator, FP64 cycles), FP32.
+struct TileData {
+    int lds_nodes = 0;             // 0: none
+    int64_t table_bytes = 0;       // row tables and lists, read once per pass
+    bool stream = false;
+    DevBuf<int2> rows;
+    DevBuf<int> base, list, count;
+    DevBuf<uint16_t> lcol;
+    DevBuf<double> v64;
+    DevBuf<float> v32;
+    TileArgs args(TileKind kind) const {
+        TileArgs a;
+        a.nrows = static_cast<int>(rows.n);
+        a.rows = rows.p;
+        a.base = base.p;
+        a.list = list.p;
+        a.count = count.p;
+        a.lds_nodes = lds_nodes;
+        a.lcol = lcol.p;
+        a.val = kind == TILE_F64 ? static_cast<const void *>(v64.p) : v32.p;
+        a.stream = stream;
+        return a;
+    }
+    double bytes(TileKind kind, int64_t nnz) const { return (kind == TILE_F64 ? 10.0 : 6.0) * nnz + table_bytes; }
 };
 
 // One level of the scalar hierarchy of a Braess-Sarazin Schur complement
@@ -198,6 +227,8 @@ struct Level {
     SweepData sweep;
     SweepShape shape;         // of its one-launch sweeps
     bool by_colour = false;   // one launch per colour instead (a forced launch shape)
+    TileData tiles;           // of A (a large scalar finest level)
+    bool by_rows = false;     // the row kernels instead (a forced launch shape)
     DevBuf<int> d_cptr;       // cptr on the device (tail kernel)
     // transfer between this level and the next coarser one
     DMat P, R;                // P: n x n_c scalar, R = P^T

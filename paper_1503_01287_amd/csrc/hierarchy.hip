@@ -1110,6 +1110,108 @@ void cap_learned_omega(amg_ctx *h) {
     h->level_omega[L] = h->level_omega[L - 1];
 }
 
+// Scalar finest levels from here on run their natural-order operator in
+// tiles. A tile's chain (row, base, entries; list, x, LDS) takes some 6 us
+// where a row's takes 3, and 256 rows a workgroup leave a small level with
+// few of them (Laplacian, FP64 operator, rows against tiles: 20^3, 68921
+// nodes, 11.9 and 14.0 us; 24^3, 117649, 16.3 and 14.9; 28^3 24.3 and 17.5;
+// 48^3 123 and 87; FP32 residual 9.2 and 12.7, 12.8 and 13.0, 17.0 and 15.5,
+// 87 and 54).
+constexpr int TILE_MIN_ROWS = 110000;
+// Values and places are read past the caches (non-temporal loads) where those
+// of a solve's operators, read in turn, would not stay in the 256 MB Infinity
+// Cache beside its vectors, but push these out (solves with and without:
+// 48^3 mixed, 442 MB, 10.6 and 11.4 ms; 40^3, 257 MB, 7.2 and 7.7; 36^3,
+// 188 MB, 5.57 and 5.54; 32^3, 132 MB, 4.77 and 4.43).
+constexpr double TILE_STREAM_BYTES = 200e6;
+
+// Per level, an order of its nodes in which neighbours in the mesh are close,
+// as places: the nodes of one coarse node follow each other, in the order of
+// the coarse level, and so on down to the coarsest one. A fine node goes with
+// the first coarse node that it is interpolated from; a linear node of a
+// level that coarsens its two kinds apart, with its first quadratic neighbour.
+// (256 rows together read 4.5 nodes of x per row at 48^3, in natural order
+// 7.3; 2.8 along a space-filling curve through the nodes' places in space,
+// which the setup is not given.)
+static std::vector<int> places_from_coarse(const Level &L, const std::vector<int> &coarse) {
+    std::vector<int> key(L.n, 0);
+    for (int i = 0; i < L.n; ++i)
+        if (L.hP.rowptr[i] < L.hP.rowptr[i + 1]) key[i] = coarse[L.hP.col[L.hP.rowptr[i]]];
+    if (L.n_quad > 0)
+        for (int i = 0; i < L.n_lin; ++i) {
+            const auto b = L.hpat.col.begin() + L.hpat.rowptr[i], e = L.hpat.col.begin() + L.hpat.rowptr[i + 1];
+            const auto j = std::lower_bound(b, e, L.n_lin);
+            if (j != e) key[i] = key[*j];
+        }
+    std::vector<int> first(coarse.size() + 1, 0), place(L.n);
+    for (int i = 0; i < L.n; ++i) ++first[key[i] + 1];
+    std::partial_sum(first.begin(), first.end(), first.begin());
+    for (int i = 0; i < L.n; ++i) place[i] = first[key[i]]++;
+    return place;
+}
+
+// Tables of the finest level's tiles; false: a tile would read more than
+// TILE_LIST nodes, or the entries' places pass 31 bits.
+static bool build_tiles(Level &L, const std::vector<int> &place, hipStream_t s) {
+    TileData &T = L.tiles;
+    const std::vector<int> rp = L.A.rowptr.download(s);
+    std::vector<int> order(L.n);
+    for (int i = 0; i < L.n; ++i) order[place[i]] = i;
+    auto length = [&](int i) { return rp[i + 1] - rp[i]; };
+    // a tile's rows by length, longest first (a slice's steps are those of
+    // its longest row)
+    std::vector<int2> rows(L.n);
+    std::vector<int> first;
+    for (int q = 0; q < L.n; q += TILE_ROWS) {
+        const int e = std::min(L.n, q + TILE_ROWS);
+        int most = 0;
+        for (int k = q; k < e; ++k) most = std::max(most, length(order[k]));
+        first.assign(most + 2, 0);
+        for (int k = q; k < e; ++k) ++first[most - length(order[k]) + 1];
+        std::partial_sum(first.begin(), first.end(), first.begin());
+        for (int k = q; k < e; ++k) rows[q + first[most - length(order[k])]++] = make_int2(order[k], length(order[k]));
+    }
+    std::vector<int> base(ceil_div(L.n, TILE_SLICE));
+    int64_t at = 0;
+    for (size_t k = 0; k < base.size(); ++k) {
+        base[k] = static_cast<int>(at);
+        at += 64 * ((static_cast<int64_t>(rows[k * TILE_SLICE].y) + TILE_LANES - 1) / TILE_LANES);
+        if (at + TILE_AHEAD >= (int64_t(1) << 31)) return false;
+    }
+    const int nt = ceil_div(L.n, TILE_ROWS);
+    T.rows.upload(rows, s);
+    T.base.upload(base, s);
+    T.count.alloc(nt);
+    T.list.alloc(static_cast<size_t>(nt) * TILE_LIST);
+    T.lcol.alloc(static_cast<size_t>(at + TILE_AHEAD));
+    launch_tile_lists(L.n, T.rows.p, T.base.p, L.A.rowptr.p, L.A.col.p, T.count.p, T.list.p, T.lcol.p, s);
+    const std::vector<int> nodes = T.count.download(s);
+    T.lds_nodes = *std::max_element(nodes.begin(), nodes.end());
+    T.table_bytes = 8 * static_cast<int64_t>(L.n) + 4 * std::accumulate(nodes.begin(), nodes.end(), int64_t(0));
+    return T.lds_nodes <= TILE_LIST;
+}
+
+static void setup_tiles(amg_ctx *h) {
+    hipStream_t s = h->stream;
+    Level &L = h->lv[0];
+    // (Gauss-Seidel sweeps leave the cycle no natural-order pass)
+    const bool reduced = h->prm.precision != AMG_PREC_FP64;
+    const bool f32 = reduced && h->prm.smoother == AMG_SMOOTH_JA;
+    if (h->saddle || h->batch_member || L.coarsest || L.mode != 1 || L.n < TILE_MIN_ROWS) return;
+    std::vector<int> place(h->lv.back().n);
+    std::iota(place.begin(), place.end(), 0);
+    for (int l = static_cast<int>(h->lv.size()) - 2; l >= 0; --l) place = places_from_coarse(h->lv[l], place);
+    if (!build_tiles(L, place, s)) {
+        L.tiles = TileData();
+        return;
+    }
+    TileData &T = L.tiles;
+    T.v64.alloc(T.lcol.n);
+    if (f32) T.v32.alloc(T.lcol.n);
+    T.stream = 10.0 * T.v64.n + 6.0 * T.v32.n > TILE_STREAM_BYTES;
+    launch_tile_values(TILE_F64, L.n, T.rows.p, T.base.p, L.A.rowptr.p, L.A.val.p, T.v64.p, s);
+}
+
 void build_hierarchy(amg_ctx *h, const amg_system *sys) {
     check_system(sys);
     h->saddle = sys->n_pres > 0;
@@ -1220,6 +1322,10 @@ void build_hierarchy(amg_ctx *h, const amg_system *sys) {
             }
         }
     }
+    {
+        SetupPhase ph(h, "tiles");
+        setup_tiles(h);
+    }
     // The FP64 kernels' tuner runs where those kernels run in solves: with a
     // reduced-precision cycle only the finest level's natural-order kernels
     // (the outer Krylov operator); in the FP64 cycle every level above the
@@ -1241,7 +1347,7 @@ void build_hierarchy(amg_ctx *h, const amg_system *sys) {
             }
             const bool used = l == 0 || (!reduced && (tail_from < 0 || static_cast<int>(l) < tail_from) &&
                                          !sweeps_give_residual(h, L));
-            if (p.autotune && used) {
+            if (p.autotune && used && L.tiles.v64.n == 0) {  // (tiles have no shapes to choose)
                 SetupPhase ph(h, "autotune");
                 autotune_level(h, L);
             }

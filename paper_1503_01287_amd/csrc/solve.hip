@@ -70,9 +70,20 @@ static RowArgs row_args(const DMat &m) {
 
 static std::string tag(const char *cls, int l) { return std::string(cls) + ".L" + std::to_string(l); }
 
+// The level's operator in tiles, where it has them.
+static bool in_tiles(const Level &L) { return L.tiles.v64.n > 0 && !L.by_rows; }
+
 // ---------------------------------------------------------------- level ops
 void apply_level(amg_ctx *h, int l, const double *x, double *y) {
     Level &L = h->lv[l];
+    if (in_tiles(L) && x != y) {
+        TileArgs a = L.tiles.args(TILE_F64);
+        a.x = x;
+        a.y = y;
+        ProfScope ps(h, tag("spmv", l), L.tiles.bytes(TILE_F64, L.A.nnz) + 3.0 * L.n * 16.0);
+        launch_tile(TILE_SPMV, TILE_F64, a, h->stream);
+        return;
+    }
     RowArgs a = row_args(L.A);
     a.x = x;
     a.y = y;
@@ -84,6 +95,15 @@ void apply_level(amg_ctx *h, int l, const double *x, double *y) {
 // r = b - A x on the level's first `rows` rows (all of them: -1)
 static void residual(amg_ctx *h, int l, const double *b, const double *x, double *r, int rows = -1) {
     Level &L = h->lv[l];
+    if (in_tiles(L) && (rows < 0 || rows == L.n)) {
+        TileArgs a = L.tiles.args(TILE_F64);
+        a.x = x;
+        a.b = b;
+        a.y = r;
+        ProfScope ps(h, tag("resid", l), L.tiles.bytes(TILE_F64, L.A.nnz) + 3.0 * L.n * 24.0);
+        launch_tile(TILE_RESID, TILE_F64, a, h->stream);
+        return;
+    }
     RowArgs a = row_args(L.A);
     if (rows >= 0) a.nrows = rows;
     a.x = x;
@@ -119,7 +139,16 @@ static void jacobi_step(amg_ctx *h, int l, const double *b, double *x, bool zero
     a.dinv = L.dinv.p;
     a.dinv_n = L.n;
     a.omega = om;
-    {
+    if (in_tiles(L) && L.nA == L.n) {
+        TileArgs q = L.tiles.args(TILE_F64);
+        q.x = x;
+        q.b = b;
+        q.y = L.t.p;
+        q.dinv = L.dinv.p;
+        q.omega = om;
+        ProfScope ps(h, tag("jacobi", l), L.tiles.bytes(TILE_F64, L.A.nnz) + 3.0 * L.n * 24.0 + 8.0 * L.n);
+        launch_tile(TILE_JACOBI, TILE_F64, q, h->stream);
+    } else {
         ProfScope ps(h, tag("jacobi", l), row_bytes(L.A, L.A.nnz, L.n) + 3.0 * L.n * 24.0 + nb * 8.0 * L.n);
         a.trip = L.trip;
         launch_row(L.mode, OP_JACOBI, L.G, a, h->stream);
@@ -428,12 +457,21 @@ static void spmv_dot(amg_ctx *h, const double *p, double *q, int post) {
     a.x = p;
     a.y = q;
     a.partial = h->partial.p;
-    {
+    int nb = row_blocks(L.n, L.G);
+    if (in_tiles(L)) {
+        TileArgs t = L.tiles.args(TILE_F64);
+        t.x = p;
+        t.y = q;
+        t.partial = h->partial.p;
+        nb = ceil_div(L.n, TILE_ROWS);
+        ProfScope ps(h, "spmv.L0", L.tiles.bytes(TILE_F64, L.A.nnz) + 3.0 * L.n * 16.0);
+        launch_tile(TILE_SPMV_DOT, TILE_F64, t, h->stream);
+    } else {
         ProfScope ps(h, "spmv.L0", row_bytes(L.A, L.A.nnz, L.n) + 3.0 * L.n * 16.0);
         a.trip = L.trip;
         launch_row(L.mode, OP_SPMV_DOT, L.G, a, h->stream);
     }
-    launch_reduce(h->partial.p, row_blocks(L.n, L.G), h->sc.p, SC_PQ, h->stream, post);
+    launch_reduce(h->partial.p, nb, h->sc.p, SC_PQ, h->stream, post);
 }
 
 // x += alpha p, r -= alpha q, <r, r> into sc[SC_RR] and, with <p, q>, into

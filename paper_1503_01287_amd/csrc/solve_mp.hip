@@ -13,6 +13,9 @@
 
 namespace amgp2 {
 
+// The FP32 operator in tiles, where the level has it.
+static bool in_tiles(const Level &L) { return L.tiles.v32.n > 0 && !L.mp.by_rows && L.nA == L.n; }
+
 // The reduced-precision kernels read half (FP32) or a quarter (BF16) of the
 // bytes per entry, so their best lanes per row can differ from the FP64
 // kernels': time them on their own, starting from the FP64 choice and
@@ -117,6 +120,8 @@ void build_mixed(amg_ctx *h) {
                                    M.ag16.p, s);
             }
         }
+        if (L.tiles.v32.n > 0)
+            launch_tile_values(TILE_F32, L.n, L.tiles.rows.p, L.tiles.base.p, L.A.rowptr.p, M.a32.p, L.tiles.v32.p, s);
         if (L.sweep.usable()) L.sweep.f32.build(SWEEP_F32, L.sweep.places, 4, s);
         M.dinv.alloc(L.dinv.n);
         launch_to_f32(L.dinv.p, M.dinv.p, static_cast<int64_t>(L.dinv.n), s);
@@ -129,8 +134,9 @@ void build_mixed(amg_ctx *h) {
         // timing noise
         M.G = M.Gg = lanes_for(L.A.nnz, L.n);
         // (not the levels inside the assembled coarse end, nor those whose
-        // sweeps give the residual: those kernels do not run in the cycle)
-        if (h->prm.autotune && (h->dense_start < 0 || static_cast<int>(l) < h->dense_start) &&
+        // sweeps give the residual or in tiles: those kernels do not run in
+        // the cycle)
+        if (h->prm.autotune && !in_tiles(L) && (h->dense_start < 0 || static_cast<int>(l) < h->dense_start) &&
             !sweeps_give_residual(h, L))
             autotune_mp(h, L);
     }
@@ -216,6 +222,15 @@ static double mat_bytes(const Level &L, int64_t nnz, int rows) {
 // (on the leading nA rows: in a batch, the systems still coarsening)
 static void residual_mp(amg_ctx *h, int l, const float *b, const float *x, float *r) {
     Level &L = h->lv[l];
+    if (in_tiles(L)) {
+        TileArgs a = L.tiles.args(TILE_F32);
+        a.x = x;
+        a.b = b;
+        a.y = r;
+        ProfScope ps(h, tag("resid", l), L.tiles.bytes(TILE_F32, L.A.nnz) + 3.0 * L.n * 12.0);
+        launch_tile(TILE_RESID, TILE_F32, a, h->stream);
+        return;
+    }
     RowArgsMP a = args_natural(L);
     a.nrows = L.nA;
     a.x = x;
@@ -250,7 +265,16 @@ static float *jacobi_mp(amg_ctx *h, int l, const float *b, float *x, bool zero) 
     a.dinv = L.mp.dinv.p;
     a.dinv_n = L.n;
     a.omega = om;
-    {
+    if (in_tiles(L)) {
+        TileArgs q = L.tiles.args(TILE_F32);
+        q.x = x;
+        q.b = b;
+        q.y = out;
+        q.dinv = L.mp.dinv.p;
+        q.omega = om;
+        ProfScope ps(h, tag("jacobi", l), L.tiles.bytes(TILE_F32, L.A.nnz) + 3.0 * L.n * 12.0 + 4.0 * L.n);
+        launch_tile(TILE_JACOBI, TILE_F32, q, h->stream);
+    } else {
         ProfScope ps(h, tag("jacobi", l), mat_bytes(L, L.A.nnz, L.nA) + 3.0 * L.nA * 12.0 + nb * 4.0 * L.nA);
         launch_row_mp(L.mode, OP_JACOBI, L.mp.G, L.mp.kind, a, h->stream);
     }
