@@ -349,8 +349,9 @@ int amg_get_level_colors(amg_handle h, int32_t level, int32_t *colors);
  * flight together; the sums do not depend on it; the prolongation kernels
  * always take 1). xcd (colour sweeps only): 1 = each XCD takes one
  * contiguous eighth of a colour's rows, 0 = round-robin placement.
- * AMG_SHAPE_VANKA (Vanka smoother, any level but the coarsest): the
- * level's sweeps compute the patch residuals with `lanes` lanes per row
+ * AMG_SHAPE_VANKA (Vanka smoother, any level but the coarsest; all colours
+ * of its sweeps run in one launch by default): the level's sweeps run
+ * colour by colour and compute the patch residuals with `lanes` lanes per row
  * (16, 32 or 64), then, for trip 1, partial corrections over 64-row x
  * chunk tiles of the patch inverses and their sum in chunk order, for
  * trip 2, the corrections over 64-row tiles of the inverses (xcd 0).

@@ -658,6 +658,7 @@ int amg_set_launch_shape(amg_handle h, int32_t level, int32_t kernels, int32_t l
                 AMG_REQUIRE(lanes >= 16 && (trip == 1 || trip == 2) && xcd == 0, AMG_EINVAL,
                             "amg_set_launch_shape: the Vanka residual takes 16, 32 or 64 lanes, trip 1 or 2, xcd 0");
                 L.vanka.path = trip == 1 ? 2 : 3;
+                L.vanka.by_colour = true;
                 L.vanka.rg = lanes;
                 break;
             case AMG_SHAPE_VANKA_APPLY:
@@ -666,6 +667,7 @@ int amg_set_launch_shape(amg_handle h, int32_t level, int32_t kernels, int32_t l
                 AMG_REQUIRE(lanes >= 4 && lanes <= 16 && trip == 1 && xcd == 0, AMG_EINVAL,
                             "amg_set_launch_shape: 4, 8 or 16 wavefronts per Vanka correction tile, trip 1, xcd 0");
                 L.vanka.path = 3;
+                L.vanka.by_colour = true;
                 L.vanka.aw = lanes;
                 break;
             default: throw Error(AMG_EINVAL, "amg_set_launch_shape: unknown kernel class");

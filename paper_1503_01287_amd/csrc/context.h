@@ -182,8 +182,9 @@ struct VankaData {
     DevBuf<int64_t> moff;
     DevBuf<double> inv;
     std::vector<int> cptr;
-    // sweep form: 2 residuals, partial corrections over 64-row x cc-column
-    // tiles, then their sum; 3 residuals, then corrections over 64-row tiles
+    // form of the launches per colour: 2 residuals, partial corrections over
+    // 64-row x cc-column tiles, then their sum; 3 residuals, then corrections
+    // over 64-row tiles
     int path = 3;
     DevBuf<int64_t> roff;          // a patch's residual in rbuf (path 2)
     DevBuf<double> rbuf;
@@ -199,6 +200,16 @@ struct VankaData {
     DevBuf<double> pbuf;
     int rg = 32;                   // lanes per residual row (16, 32 or 64)
     int aw = 4;                    // path 3: wavefronts per 64-row correction tile (4, 8 or 16)
+    // all colours in one launch (k_vanka_sweep), faster at every size measured
+    // (125 to 4,913 patches); not where a table would pass 31 bits
+    bool one_launch = false;
+    bool by_colour = false;        // launches per colour instead (a forced launch shape)
+    int nitems = 0;
+    DevBuf<int2> item, own, entry;
+    DevBuf<int> ctl;
+    DevBuf<VankaTile> stile;
+    DevBuf<VankaRow> srow;
+    DevBuf<double> xs, rs, x_old;
     VankaColour colour(int c) const {
         VankaColour q;
         q.count = cptr[c + 1] - cptr[c];
@@ -428,6 +439,7 @@ void precondition_mp(amg_ctx *h, const double *r, double *z);
 void saddle_setup_level(amg_ctx *h, Level &L);
 void setup_schur(amg_ctx *h, int l);
 void setup_vanka(amg_ctx *h, int l);
+void setup_vanka_sweep(amg_ctx *h, int l);
 void setup_schur_dense(amg_ctx *h, int l);
 void setup_saddle_tail(amg_ctx *h);
 VankaView vanka_view(Level &L);

@@ -908,6 +908,7 @@ void setup_vanka(amg_ctx *h, int l) {
         for (int k = V.cptr[c]; k < V.cptr[c + 1]; ++k) {
             const int i = order[k], p0 = bp.rowptr[i], nn = bp.rowptr[i + 1] - p0, m = 3 * nn + 1;
             tpre[k] = static_cast<int>(tiles.size()) - V.tptr[c];
+            const int row = static_cast<int>(rown.size());
             for (int q = 0; q < nn; ++q) rown.push_back(make_int2(bp.col[p0 + q], static_cast<int>(roff[i]) + 3 * q));
             rown.push_back(make_int2(~i, static_cast<int>(roff[i]) + 3 * nn));
             for (int a = 0; a < m; a += 64) {
@@ -918,6 +919,7 @@ void setup_vanka(amg_ctx *h, int l) {
                 t.res = static_cast<int>(roff[i]);
                 t.node0 = p0;
                 t.patch = i;
+                t.row = row;
                 tiles.push_back(t);
             }
         }
@@ -933,91 +935,115 @@ void setup_vanka(amg_ctx *h, int l) {
     V.rbuf.alloc(static_cast<size_t>(std::max<int64_t>(1, rtot)));
     V.rg = L.A.nnz > 40 * static_cast<int64_t>(L.n) ? 64 : 32;
     // three-kernel path: 64-row x cc-column tiles of the inverses and their
-    // partial sums, colour by colour, for a chunk width cc
-    auto tile_tables = [&](int cc) {
-        std::vector<int> upre(std::max(1, np), 0);
-        std::vector<int64_t> poff(std::max(1, np), 0);
-        V.nunits.assign(nc, 0);
-        int64_t ptot = 0;
-        for (int i = 0; i < np; ++i) {
-            const int64_t m = 3 * static_cast<int64_t>(bp.rowptr[i + 1] - bp.rowptr[i]) + 1;
-            poff[i] = ptot;
-            ptot += ((m + cc - 1) / cc) * m;
-        }
-        for (int c = 0; c < nc; ++c) {
-            int t = 0;
-            for (int k = V.cptr[c]; k < V.cptr[c + 1]; ++k) {
-                upre[k] = t;
-                const int i = order[k];
-                const int m = 3 * (bp.rowptr[i + 1] - bp.rowptr[i]) + 1;
-                t += ((m + 63) / 64) * ((m + cc - 1) / cc);
-            }
-            V.nunits[c] = t;
-        }
-        V.cc = cc;
-        V.upre.upload(upre, s);
-        V.poff.upload(poff, s);
-        if (static_cast<int64_t>(V.pbuf.n) < ptot) V.pbuf.alloc(static_cast<size_t>(std::max<int64_t>(1, ptot)));
-    };
-    // (with the tuners on) another width or form that is 3% faster on a
-    // scratch vector pair
-    tile_tables(256);
-    if (h->prm.autotune) {
-        const int64_t nv = L.vlen();
-        DevBuf<double> xs(nv), bs(nv);
-        launch_fill(xs.p, 0.0, nv, s);
-        launch_fill(bs.p, 1.0, nv, s);
-        hipEvent_t e0, e1;
-        AMG_HIP(hipEventCreate(&e0));
-        AMG_HIP(hipEventCreate(&e1));
-        auto sweep = [&] {
-            for (int c = 0; c < nc; ++c) launch_vanka(L, view, c, bs.p, xs.p, 0.5, s);
-        };
-        auto time_of = [&] {
-            sweep();
-            float t = 1e30f;
-            for (int r = 0; r < 3; ++r) {
-                AMG_HIP(hipEventRecord(e0, s));
-                sweep();
-                AMG_HIP(hipEventRecord(e1, s));
-                AMG_HIP(hipEventSynchronize(e1));
-                float ms = 0.f;
-                AMG_HIP(hipEventElapsedTime(&ms, e0, e1));
-                t = std::min(t, ms);
-            }
-            return t;
-        };
-        float best = time_of();
-        auto better = [&](int &knob, int value) {
-            const int was = knob;
-            knob = value;
-            const float t = time_of();
-            if (t < 0.97f * best)
-                best = t;
-            else
-                knob = was;
-        };
-        for (const int rg : {16, 32, 64})
-            if (rg != V.rg) better(V.rg, rg);
-        for (const int aw : {8, 16}) better(V.aw, aw);
-        int best_cc = 256;
-        for (const int cc : {256, 128, 512}) {
-            if (cc != 256 && V.path != 2) break;  // not near the other form
-            tile_tables(cc);
-            const int was = V.path;
-            V.path = 2;
-            const float t = time_of();
-            if (t < 0.97f * best) {
-                best = t;
-                best_cc = cc;
-            } else {
-                V.path = was;
-            }
-        }
-        if (V.cc != best_cc) tile_tables(best_cc);
-        AMG_HIP(hipEventDestroy(e0));
-        AMG_HIP(hipEventDestroy(e1));
+    // partial sums, colour by colour
+    const int cc = V.cc;
+    std::vector<int> upre(std::max(1, np), 0);
+    std::vector<int64_t> poff(std::max(1, np), 0);
+    V.nunits.assign(nc, 0);
+    int64_t ptot = 0;
+    for (int i = 0; i < np; ++i) {
+        const int64_t m = 3 * static_cast<int64_t>(bp.rowptr[i + 1] - bp.rowptr[i]) + 1;
+        poff[i] = ptot;
+        ptot += ((m + cc - 1) / cc) * m;
     }
+    for (int c = 0; c < nc; ++c) {
+        int t = 0;
+        for (int k = V.cptr[c]; k < V.cptr[c + 1]; ++k) {
+            upre[k] = t;
+            const int i = order[k];
+            const int m = 3 * (bp.rowptr[i + 1] - bp.rowptr[i]) + 1;
+            t += ((m + 63) / 64) * ((m + cc - 1) / cc);
+        }
+        V.nunits[c] = t;
+    }
+    V.upre.upload(upre, s);
+    V.poff.upload(poff, s);
+    V.pbuf.alloc(static_cast<size_t>(std::max<int64_t>(1, ptot)));
+    AMG_HIP(hipStreamSynchronize(s));
+}
+
+// Tables of the one-launch sweeps, from the operators that the sweeps read
+// (zero blocks dropped).
+void setup_vanka_sweep(amg_ctx *h, int l) {
+    hipStream_t s = h->stream;
+    Level &L = h->lv[l];
+    VankaData &V = L.vanka;
+    const int nc = static_cast<int>(V.cptr.size()) - 1, nrows = V.rptr.back();
+    // (a half of xs stays below 2 GiB)
+    if (nrows == 0 || nrows >= (1 << 26)) return;
+    const std::vector<int2> rown = V.rown.download(s);
+    const std::vector<int4> rowa = V.rowa.download(s);
+    const std::vector<VankaTile> tiles = V.tile.download(s);
+    std::vector<VankaTile> stile;
+    std::vector<VankaRow> srow;
+    srow.reserve(nrows);
+    std::vector<int> ptr(nrows + 1, 0), colour(nrows), nptr(L.n + L.n_pres + 1, 0);
+    std::vector<int2> item, writer(nrows);
+    int64_t total = 0;
+    auto unknown = [&](int t) { return rown[t].x >= 0 ? rown[t].x : L.n + ~rown[t].x; };
+    for (int t = 0; t < nrows; ++t) {
+        total += rowa[t].y - rowa[t].x + rowa[t].w - rowa[t].z;
+        if (total >= (int64_t(1) << 31)) return;  // (the launches per colour have no such table)
+        ptr[t + 1] = static_cast<int>(total);
+        ++nptr[unknown(t) + 1];
+    }
+    std::partial_sum(nptr.begin(), nptr.end(), nptr.begin());
+    std::vector<int> next(nptr.begin(), nptr.end() - 1);
+    for (int c = 0; c < nc; ++c) {
+        for (int t = V.rptr[c]; t < V.rptr[c + 1]; ++t) {
+            colour[t] = c;
+            writer[next[unknown(t)]++] = make_int2(t, c);
+        }
+        for (const bool lng : {true, false}) {
+            const int first = static_cast<int>(srow.size()), per = lng ? VANKA_ITEM_ROWS / 2 : VANKA_ITEM_ROWS;
+            for (int t = V.rptr[c]; t < V.rptr[c + 1]; ++t)
+                if ((ptr[t + 1] - ptr[t] > VANKA_SHORT) == lng) {
+                    VankaRow q;
+                    q.node = rown[t].x;
+                    q.res = rown[t].y;
+                    q.first = ptr[t];
+                    q.entries = rowa[t];
+                    srow.push_back(q);
+                }
+            const int end = static_cast<int>(srow.size());
+            for (int k = first; k < end; k += per)
+                item.push_back(make_int2(k, lng ? -std::min(per, end - k) : std::min(per, end - k)));
+        }
+        for (int t = V.tptr[c]; t < V.tptr[c + 1]; ++t) {
+            VankaTile q = tiles[t];
+            if (q.row0 > 0) continue;
+            q.groups = q.m <= 104 ? 4 : q.m <= 208 ? 2 : 1;
+            const int most = 64 * q.groups, pieces = ceil_div(q.m, most);
+            for (int k = 0; k < pieces; ++k) {
+                q.row0 = static_cast<int>(static_cast<int64_t>(k) * q.m / pieces);
+                q.rows = static_cast<int>(static_cast<int64_t>(k + 1) * q.m / pieces) - q.row0;
+                item.push_back(make_int2(~static_cast<int>(stile.size()), 0));
+                stile.push_back(q);
+            }
+        }
+    }
+    V.nitems = static_cast<int>(item.size());
+    V.item.upload(item, s);
+    V.stile.upload(stile, s);
+    V.srow.upload(srow, s);
+    V.entry.alloc(static_cast<size_t>(std::max<int64_t>(1, total)));
+    V.own.alloc(static_cast<size_t>(nrows));
+    DevBuf<int> dptr, dcolour, dnptr;
+    DevBuf<int2> dwriter;
+    dptr.upload(ptr, s);
+    dcolour.upload(colour, s);
+    dnptr.upload(nptr, s);
+    dwriter.upload(writer, s);
+    launch_vanka_entries(vanka_view(L), nrows, V.rown.p, V.rowa.p, dptr.p, dcolour.p, dnptr.p, dwriter.p,
+                        V.entry.p, V.own.p, s);
+    V.xs.alloc(8 * static_cast<size_t>(nrows));
+    V.rs.alloc(2 * V.rbuf.n);
+    launch_vanka_absent(V.xs.p, static_cast<int64_t>(V.xs.n), s);
+    launch_vanka_absent(V.rs.p, static_cast<int64_t>(V.rs.n), s);
+    V.ctl.alloc(VANKA_CTL_INTS);
+    V.ctl.zero(s);
+    V.x_old.alloc(static_cast<size_t>(L.vlen()));
+    V.one_launch = true;
     AMG_HIP(hipStreamSynchronize(s));
 }
 
@@ -1387,8 +1413,10 @@ void build_hierarchy(amg_ctx *h, const amg_system *sys) {
                 L.B = std::move(c);
             }
             if (drop_zero_entries(L.Bt, false, c, s)) L.Bt = std::move(c);
-            if (L.vanka.rown.n > 0)  // the sweeps' rows of those operators
+            if (L.vanka.rown.n > 0) {  // the sweeps' rows of those operators
                 launch_vanka_rows(vanka_view(L), static_cast<int>(L.vanka.rown.n), L.vanka.rown.p, L.vanka.rowa.p, s);
+                setup_vanka_sweep(h, static_cast<int>(&L - h->lv.data()));
+            }
         }
     if (!h->saddle) {
         {

@@ -402,4 +402,423 @@ void launch_vanka_colour_tiled(const VankaView &v, const VankaColour &c, const i
     AMG_CHECK_LAUNCH();
 }
 
+// ------------------------------------------------- all colours in one launch
+// Two launches per colour cost 5 to 7 us each, most of it the launch and a
+// chain of dependent loads; a colour has 5 to 40 patches, well under 2 us of
+// bandwidth. Here the workgroups stay for the whole sweep and take items
+// from a ticket counter: a colour's residual rows, then its patches'
+// corrections. An item loads what does not depend on the others (operator
+// entries, columns of the inverse, 100 of its 128 registers a lane), waits
+// for the values that do, and stores its own at device scope (sc1, which the
+// 8 XCDs see alike). A value that is not there yet holds a NaN of a fixed
+// payload, as in the Gauss-Seidel sweeps: an unknown has a place for every
+// patch that it is in, so each place is written once in a sweep, and a reader
+// knows (VankaSweep::entry) whose place holds the value of its colour. Two
+// buffers of places: a sweep uses one and fills the other with the payload;
+// the last workgroup out turns them over.
+//
+// Progress: an item waits only for items of smaller tickets, and a ticket is
+// taken by a running workgroup, so the smallest unfinished one never waits,
+// whatever part of the grid is resident. The waits are bounded all the same;
+// past the bound the values become NaN, which the Krylov loops report as
+// divergence.
+//
+// What bounds it: two trips to memory a colour (residual to corrections,
+// corrections to the next colour's residual), 4.2 us in all on small levels;
+// with many patches a colour also how many items are in flight ahead of it,
+// so items are large (1024 threads; 49 rows of an inverse a wavefront, four
+// or two groups of rows where 26 columns a lane cover it) and a residual row
+// has 32 lanes, 64 only past 64 entries. Where it has more than two entries
+// a lane, the last written are its last. us per sweep, launches per colour ->
+// this kernel, mixed elasticity:
+//    4^3 level 0 (  125 patches, 44 colours)   358 -> 182
+//    8^3 level 0 (  729 patches, 59 colours)   530 -> 251
+//   12^3 level 0 (2,197 patches, 62 colours)   738 -> 353
+//   12^3 level 1 (  343 patches, 72 colours)   865 -> 398
+//   16^3 level 0 (4,913 patches)             1,051 -> 631
+// (64 lanes for every row: 12^3 425 and 415; two workgroups of 512 threads to
+// a CU: 535 and 437; 64-row tiles of every inverse: 461 and 408; 50 columns a
+// lane spill: 1,134.)
+namespace {
+
+constexpr int SWEEP_WAVES = 16;
+constexpr unsigned SPIN_MAX = 1u << 21;  // a second or two of polls
+constexpr uint64_t ABSENT = 0x7ffdead0beef0001ull;  // payload of "not there yet" (a quiet NaN)
+
+template <typename T>
+__device__ __forceinline__ T agent_load(const T *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void agent_store(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double absent() { return __longlong_as_double(static_cast<long long>(ABSENT)); }
+__device__ __forceinline__ bool is_absent(double v) { return static_cast<uint64_t>(__double_as_longlong(v)) == ABSENT; }
+__device__ __forceinline__ double present(double v, bool bad) { return bad || is_absent(v) ? __builtin_nan("") : v; }
+
+__device__ __forceinline__ double lane_value(double v, int k) {
+    const uint64_t w = static_cast<uint64_t>(__double_as_longlong(v));
+    const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(w), k));
+    const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(w >> 32), k));
+    return __longlong_as_double(static_cast<long long>(static_cast<uint64_t>(hi) << 32 | lo));
+}
+
+// sum over each 32 lanes, in the order of a butterfly: 4 of its 5 steps
+// without a trip through LDS
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+    const uint64_t w = static_cast<uint64_t>(__double_as_longlong(v));
+    const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(w), CTRL, 0xf, 0xf, true));
+    const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(w >> 32), CTRL, 0xf, 0xf, true));
+    return __longlong_as_double(static_cast<long long>(static_cast<uint64_t>(hi) << 32 | lo));
+}
+__device__ __forceinline__ double sum32(double v) {
+    v += dpp<0xb1>(v);   // lane ^ 1 (quad_perm 1, 0, 3, 2)
+    v += dpp<0x4e>(v);   // lane ^ 2 (quad_perm 2, 3, 0, 1)
+    v += dpp<0x141>(v);  // the other quad of 8 (row_half_mirror)
+    v += dpp<0x140>(v);  // the other 8 of 16 (row_mirror)
+    return v + __shfl_xor(v, 16, 64);
+}
+
+// device-scope loads of a row's unknowns (the buffer's descriptor covers one
+// half of xs)
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+constexpr int AUX_SC1 = 16;  // the scope bit of device-scope accesses
+__device__ __forceinline__ double from_words(uint32_t lo, uint32_t hi) {
+    return __longlong_as_double(static_cast<long long>(static_cast<uint64_t>(hi) << 32 | lo));
+}
+__device__ __forceinline__ void gather(__amdgpu_buffer_rsrc_t xs, int row, double *v) {
+    const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(xs, 32 * row, 0, AUX_SC1);
+    const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(xs, 32 * row + 16, 0, AUX_SC1);
+    v[0] = from_words(q.x, q.y);
+    v[1] = from_words(q.z, q.w);
+    v[2] = from_words(w.x, w.y);
+}
+
+// load() until it is true in every lane, or the bound is reached (bad)
+template <typename Load>
+__device__ __forceinline__ void wait_for(Load &&load, int *gave_up, bool &bad) {
+    bool there = false;
+    unsigned n = 0;
+    for (;;) {
+        if (!there) {
+            asm volatile("" ::: "memory");  // a new load every time
+            there = load();
+        }
+        if (__all(there) || bad) break;
+        if ((++n & 0xfff) == 0) {
+            if (n > SPIN_MAX) agent_store(gave_up, 1);
+            bad = agent_load(gave_up) != 0;
+        }
+        if (n > 2) __builtin_amdgcn_s_sleep(1);
+    }
+}
+
+}  // namespace
+
+__global__ void __launch_bounds__(64 * SWEEP_WAVES, 4) k_vanka_sweep(const VankaView v, const VankaSweep a) {
+    constexpr int NW = SWEEP_WAVES;
+    constexpr int U = 2;    // entries per lane loaded before the wait
+    constexpr int KC = 26;  // columns of an inverse per lane loaded before the wait
+    __shared__ int sh_ticket[2];
+    __shared__ double part[NW][64];
+    const int tid = threadIdx.x;
+    int *const ticket = a.ctl, *const exits = a.ctl + 32, *const turn = a.ctl + 64, *const gave_up = a.ctl + 96;
+    int next = 0;
+    if (tid == 0) {
+        next = atomicAdd(ticket, 1);
+        sh_ticket[0] = next;
+        next = atomicAdd(ticket, 1);
+    }
+    const int which = *turn;
+    double *const xs = a.xs + (which ? a.xs_half : 0), *const xfill = a.xs + (which ? 0 : a.xs_half);
+    double *const rs = a.rs + (which ? a.rs_half : 0), *const rfill = a.rs + (which ? 0 : a.rs_half);
+    const __amdgpu_buffer_rsrc_t xsr =
+        __builtin_amdgcn_make_buffer_rsrc(xs, 0, static_cast<int>(a.xs_half * sizeof(double)), 0x00027000);
+    const int64_t nu = 3 * static_cast<int64_t>(v.n);
+    __syncthreads();
+    bool bad = false;
+    int t = sh_ticket[0], phase = 1;
+    // an item and what it is described by, loaded while the one before it
+    // waits
+    int2 it = make_int2(0, 0);
+    VankaRow row_next;
+    VankaTile tl_next;
+    auto fetch = [&](int k) {
+        if (k >= a.nitems) return;
+        it = a.item[k];
+        it.x = __builtin_amdgcn_readfirstlane(it.x);
+        it.y = __builtin_amdgcn_readfirstlane(it.y);
+        if (it.x >= 0) {
+            const int grp = tid / (it.y > 0 ? 32 : 64), count = it.y > 0 ? it.y : -it.y;
+            row_next = a.row[it.x + (grp < count ? grp : 0)];
+        } else {
+            tl_next = a.tile[~it.x];
+        }
+    };
+    fetch(t);
+    while (t < a.nitems) {
+        if (tid == 0) sh_ticket[phase] = next;
+        __syncthreads();
+        const int t_next = sh_ticket[phase];
+        phase ^= 1;
+        if (tid == 0 && t_next < a.nitems) next = atomicAdd(ticket, 1);
+        const int2 item = it;
+        const VankaRow rd = row_next;
+        const VankaTile tl = tl_next;
+        fetch(t_next);
+        t = t_next;
+        if (item.x >= 0) {
+            // residual rows, 32 or 64 lanes each
+            const int G = item.y > 0 ? 32 : 64, lane = tid & (G - 1), grp = tid / G;
+            const bool on = grp < (item.y > 0 ? item.y : -item.y);
+            const int2 rn = make_int2(rd.node, rd.res);
+            const int4 ra = rd.entries;
+            const int p0 = rd.first;
+            const bool vel = rn.x >= 0;
+            const int n0 = ra.y - ra.x, n1 = on ? n0 + ra.w - ra.z : 0;  // entries of A (B), and with those of B^T (C)
+            const int comps = vel ? 3 : 1;
+            double bc = 0.0;
+            if (on && lane < comps) {
+                bc = a.b[vel ? 3 * static_cast<int64_t>(rn.x) + lane : nu + ~rn.x];
+                rfill[rn.y + lane] = absent();
+            }
+            double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+            for (int k = lane; __any(k < n1); k += U * G) {
+                int j[U];
+                bool first[U];  // an entry of A or B (its column is a node), else of B^T or C
+                double e[U][9], y[U][3];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int ku = k + u * G;
+                    const bool in = ku < n1;
+                    const int2 en = in ? a.entry[p0 + ku] : make_int2(0, 0);
+                    first[u] = en.y < n0;
+                    j[u] = en.x;
+#pragma unroll
+                    for (int q = 0; q < 9; ++q) e[u][q] = 0.0;
+                    y[u][0] = y[u][1] = y[u][2] = 0.0;
+                    if (in) {
+                        if (vel) {
+                            if (first[u]) {
+#pragma unroll
+                                for (int q = 0; q < 9; ++q) e[u][q] = v.aval[q * v.annz + ra.x + en.y];
+                            } else {
+#pragma unroll
+                                for (int q = 0; q < 3; ++q) e[u][3 * q] = v.btval[q * v.btnnz + ra.z + en.y - n0];
+                            }
+                        } else if (first[u]) {
+#pragma unroll
+                            for (int q = 0; q < 3; ++q) e[u][q] = v.bval[q * v.bnnz + ra.x + en.y];
+                        } else {
+                            e[u][0] = -v.cval[ra.z + en.y - n0];
+                        }
+                        if (j[u] < 0) {  // no patch of an earlier colour has it
+                            const int64_t at = first[u] ? 3 * static_cast<int64_t>(~j[u]) : nu + ~j[u];
+                            y[u][0] = a.x_old[at];
+                            if (first[u]) {
+                                y[u][1] = a.x_old[at + 1];
+                                y[u][2] = a.x_old[at + 2];
+                            }
+                        }
+                    }
+                }
+                // most of them were written a while ago: an ordinary load finds
+                // these, in the L2 for its XCD's other rows. (It never finds an
+                // earlier sweep's: the launch before this one wrote "absent"
+                // over them.) The others are waited for at device scope.
+                bool got[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    got[u] = k + u * G >= n1 || j[u] < 0;
+                    if (!got[u]) {
+                        const double *q = xs + 4 * static_cast<int64_t>(j[u]);
+                        y[u][0] = q[0];
+                        if (first[u]) {
+                            y[u][1] = q[1];
+                            y[u][2] = q[2];
+                        }
+                        got[u] = !is_absent(y[u][0]) && !is_absent(y[u][1]) && !is_absent(y[u][2]);
+                    }
+                }
+                wait_for(
+                    [&] {
+#pragma unroll
+                        for (int u = 0; u < U; ++u)
+                            if (!got[u]) {
+                                gather(xsr, j[u], y[u]);
+                                got[u] = !is_absent(y[u][0]) && (!first[u] || (!is_absent(y[u][1]) && !is_absent(y[u][2])));
+                            }
+                        bool there = true;
+#pragma unroll
+                        for (int u = 0; u < U; ++u) there = there && got[u];
+                        return there;
+                    },
+                    gave_up, bad);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (k + u * G < n1) {
+                        if (vel && first[u]) {
+                            s0 += e[u][0] * y[u][0] + e[u][1] * y[u][1] + e[u][2] * y[u][2];
+                            s1 += e[u][3] * y[u][0] + e[u][4] * y[u][1] + e[u][5] * y[u][2];
+                            s2 += e[u][6] * y[u][0] + e[u][7] * y[u][1] + e[u][8] * y[u][2];
+                        } else if (vel) {
+                            s0 += e[u][0] * y[u][0];
+                            s1 += e[u][3] * y[u][0];
+                            s2 += e[u][6] * y[u][0];
+                        } else if (first[u]) {
+                            s0 += e[u][0] * y[u][0] + e[u][1] * y[u][1] + e[u][2] * y[u][2];
+                        } else {
+                            s0 += e[u][0] * y[u][0];
+                        }
+                    }
+            }
+            s0 = sum32(s0);
+            s1 = sum32(s1);
+            s2 = sum32(s2);
+            if (G == 64) {
+                s0 += __shfl_xor(s0, 32, 64);
+                s1 += __shfl_xor(s1, 32, 64);
+                s2 += __shfl_xor(s2, 32, 64);
+            }
+            if (on && lane < comps) agent_store(rs + rn.y + lane, present(bc - (lane == 0 ? s0 : (lane == 1 ? s1 : s2)), bad));
+        } else {
+            // rows row0 .. of a patch's correction: RG groups of up to 64, the
+            // columns split over the wavefronts of each
+            const int wave = tid >> 6, l64 = tid & 63, m = tl.m;
+            const int RG = tl.groups, CG = NW / RG, rg = wave % RG, cg = wave / RG;
+            const int width = (tl.rows + RG - 1) / RG, local = rg * width + l64;
+            const bool in = l64 < width && local < tl.rows;
+            const int r = tl.row0 + (in ? local : 0);
+            const bool mine = in && cg == 0;
+            double old = 0.0;
+            int2 own = make_int2(0, 0);
+            int64_t at = 0;
+            int slot = 0;
+            if (mine) {
+                const int row = tl.row + r / 3;
+                own = a.own[row];
+                at = r < m - 1 ? 3 * static_cast<int64_t>(a.rown[row].x) + r % 3 : nu + tl.patch;
+                slot = 4 * row + r % 3;
+                xfill[slot] = absent();
+                if (own.x < 0) old = a.x_old[at];
+            }
+            const double *M = v.inv + tl.inv + r;
+            // (the first column group has columns whatever m is)
+            const int per = (m + CG - 1) / CG, c0 = min(cg * per, m), c1 = min(c0 + per, m);
+            double acc = 0.0;
+            for (int c = c0; c < c1; c += KC) {
+                const int nc = c1 - c < KC ? c1 - c : KC;
+                double mv[KC];
+#pragma unroll
+                for (int k = 0; k < KC; ++k) mv[k] = k < nc ? M[static_cast<int64_t>(c + k) * m] : 0.0;
+                double rl = 0.0;
+                wait_for(
+                    [&] {
+                        if (l64 < nc) rl = agent_load(rs + tl.res + c + l64);
+                        if (mine && own.x >= 0) old = agent_load(xs + 4 * static_cast<int64_t>(own.x) + r % 3);
+                        return !is_absent(rl) && (own.x < 0 || !is_absent(old));
+                    },
+                    gave_up, bad);
+#pragma unroll
+                for (int k = 0; k < KC; ++k)
+                    if (k < nc) acc += mv[k] * lane_value(rl, k);
+            }
+            part[wave][l64] = acc;
+            __syncthreads();
+            if (mine) {
+                double sum = part[rg][l64];
+                for (int w = 1; w < CG; ++w) sum += part[rg + w * RG][l64];
+                const double xn = present(old + a.omega * sum, bad);
+                agent_store(xs + slot, xn);
+                if (own.y) a.x[at] = xn;
+            }
+            // (part is written again only past the loop's barrier)
+        }
+    }
+    // the last workgroup out readies the control words for the next sweep
+    if (tid == 0 && atomicAdd(exits, 1) == static_cast<int>(gridDim.x) - 1) {
+        agent_store(ticket, 0);
+        agent_store(exits, 0);
+        agent_store(gave_up, 0);
+        agent_store(turn, which ^ 1);
+    }
+}
+
+void launch_vanka_sweep(const VankaView &v, const VankaSweep &a, int grid, hipStream_t s) {
+    if (a.nitems <= 0) return;
+    AMG_REQUIRE(a.x != a.x_old, AMG_EINVAL, "Vanka sweep: in place");
+    k_vanka_sweep<<<grid, 64 * SWEEP_WAVES, 0, s>>>(v, a);
+    AMG_CHECK_LAUNCH();
+}
+
+// One wavefront per residual row. The last writer before the row's colour is
+// the last of the column's list (by colour) below it; entries are ranked by
+// it, so that a row's later trips are those that wait (a row of more entries
+// than LDS holds here keeps its order).
+constexpr int RANKED = 1024;
+__global__ void __launch_bounds__(VB) k_vanka_entries(const VankaView v, int nrows, const int2 *rown, const int4 *rowa,
+                                                      const int *pptr, const int *colour, const int *nptr,
+                                                      const int2 *writer, int2 *entry, int2 *own) {
+    __shared__ int keys[VB / 64][RANKED];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, row = blockIdx.x * (VB / 64) + wave;
+    const bool on = row < nrows;
+    const int u = on ? rown[row].x : 0, c = on ? colour[row] : 0;
+    const int4 ra = on ? rowa[row] : make_int4(0, 0, 0, 0);
+    const int n0 = ra.y - ra.x, n1 = n0 + ra.w - ra.z;
+    int2 *const mine = entry + (on ? pptr[row] : 0);
+    for (int k = lane; k < n1; k += 64) {
+        int j, list;  // the column, the list of its writers
+        if (k < n0) {
+            j = u >= 0 ? v.acol[ra.x + k] : v.bcol[ra.x + k];
+            list = j;
+        } else {
+            j = u >= 0 ? v.btcol[ra.z + k - n0] : v.ccol[ra.z + k - n0];
+            list = v.n + j;
+        }
+        int at = ~j;
+        for (int q = nptr[list]; q < nptr[list + 1] && writer[q].y < c; ++q) at = writer[q].x;
+        mine[k] = make_int2(at, k);
+        if (n1 <= RANKED) keys[wave][k] = at;
+    }
+    __syncthreads();
+    if (n1 <= RANKED)
+        for (int k = lane; k < n1; k += 64) {
+            const int key = keys[wave][k];
+            int rank = 0;
+            for (int q = 0; q < n1; ++q) rank += keys[wave][q] < key || (keys[wave][q] == key && q < k);
+            mine[rank] = make_int2(key, k);
+        }
+    if (on && lane == 0) {
+        const int list = u >= 0 ? u : v.n + ~u;
+        int2 o = make_int2(~0, 1);
+        for (int q = nptr[list]; q < nptr[list + 1]; ++q) {
+            if (writer[q].y < c) o.x = writer[q].x;
+            if (writer[q].y > c) o.y = 0;
+        }
+        own[row] = o;
+    }
+}
+
+void launch_vanka_entries(const VankaView &v, int nrows, const int2 *rown, const int4 *rowa, const int *pptr,
+                          const int *colour, const int *nptr, const int2 *writer, int2 *entry, int2 *own,
+                          hipStream_t s) {
+    if (nrows <= 0) return;
+    k_vanka_entries<<<ceil_div(nrows, VB / 64), VB, 0, s>>>(v, nrows, rown, rowa, pptr, colour, nptr, writer, entry, own);
+    AMG_CHECK_LAUNCH();
+}
+
+__global__ void __launch_bounds__(VB) k_vanka_absent(double *p, int64_t n) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * VB + threadIdx.x;
+    if (i < n) p[i] = absent();
+}
+
+void launch_vanka_absent(double *p, int64_t n, hipStream_t s) {
+    if (n <= 0) return;
+    k_vanka_absent<<<ceil_div(n, VB), VB, 0, s>>>(p, n);
+    AMG_CHECK_LAUNCH();
+}
+
 }  // namespace amgp2

@@ -549,8 +549,32 @@ static void bs_step(amg_ctx *h, int l, const T *b, T *x, bool x_zero) {
 static void vanka_step(amg_ctx *h, int l, const double *b, double *x) {
     Level &L = h->lv[l];
     const VankaView v = vanka_view(L);
-    const int nc = static_cast<int>(L.vanka.cptr.size()) - 1;
-    ProfScope ps(h, tag("vanka", l), L.vanka.inv_bytes);  // algorithmic: the patch inverses
+    VankaData &V = L.vanka;
+    const int nc = static_cast<int>(V.cptr.size()) - 1;
+    if (V.one_launch && !V.by_colour) {
+        launch_copy(V.x_old.p, x, L.vlen(), h->stream);
+        VankaSweep a;
+        a.nitems = V.nitems;
+        a.item = V.item.p;
+        a.rown = V.rown.p;
+        a.row = V.srow.p;
+        a.entry = V.entry.p;
+        a.own = V.own.p;
+        a.tile = V.stile.p;
+        a.xs = V.xs.p;
+        a.xs_half = static_cast<int64_t>(V.xs.n / 2);
+        a.rs = V.rs.p;
+        a.rs_half = static_cast<int64_t>(V.rs.n / 2);
+        a.ctl = V.ctl.p;
+        a.b = b;
+        a.x_old = V.x_old.p;
+        a.x = x;
+        a.omega = h->prm.vanka_omega;
+        ProfScope ps(h, tag("vanka", l), V.inv_bytes);  // algorithmic: the patch inverses
+        launch_vanka_sweep(v, a, std::min(V.nitems, 256), h->stream);
+        return;
+    }
+    ProfScope ps(h, tag("vanka", l), V.inv_bytes);
     for (int c = 0; c < nc; ++c) launch_vanka(L, v, c, b, x, h->prm.vanka_omega, h->stream);
 }
 static void vanka_step(amg_ctx *, int, const float *, float *) {
@@ -704,7 +728,12 @@ void setup_saddle_tail(amg_ctx *h) {
         const float sparse_ms = time_cycle(d, false);
         const double gemv_bytes = h->mixed ? 0.5 * bytes : bytes;  // FP32 copy in FP32 cycles
         if (gemv_bytes / 5.0e9 >= 0.9 * sparse_ms) continue;
-        const float asm_ms = h->mixed ? time_cycle(d, true) : sparse_ms;
+        // (Vanka sweeps are timed by their launches per colour here: those in
+        // one launch shorten an assembly, but pay for no larger map)
+        const bool vanka = h->prm.smoother == AMG_SMOOTH_VANKA;
+        for (int k = d; vanka && k < last; ++k) h->lv[k].vanka.by_colour = true;
+        const float asm_ms = h->mixed || vanka ? time_cycle(d, true) : sparse_ms;
+        for (int k = d; vanka && k < last; ++k) h->lv[k].vanka.by_colour = false;
         if (static_cast<double>(mmax) * asm_ms > SADDLE_TAIL_SETUP_MS) continue;
         // the maps' layout on level lev (one square block per system);
         // returns the largest block
