@@ -302,24 +302,21 @@ struct ChunkTable {
 
 // Work of amg_solve_multi (blocks of K right-hand sides), kept between calls
 // with the same K: per-level block vectors (FP64 or FP32 cycle), the outer
-// Krylov blocks, dot partials and pinned slots for per-column coefficients.
+// Krylov blocks, dot partials and their sums in host memory.
 struct MultiLevelWork {
     DevBuf<double> x, b, r, t;
     DevBuf<float> x32, b32, r32, t32;
 };
 
 struct MultiWork {
-    static constexpr int SLOTS = 16;
     int K = 0;
     std::vector<MultiLevelWork> lv;
-    DevBuf<double> B, X, R, Z, P, Q, partial, dots, coef;
-    double *h_coef = nullptr, *h_dots = nullptr;
-    int used = 0;
+    DevBuf<double> B, X, R, Z, P, Q, partial;
+    double *h_dots = nullptr;  // two sums per right-hand side, written by the GPU
     MultiWork() = default;
     MultiWork(const MultiWork &) = delete;
     MultiWork &operator=(const MultiWork &) = delete;
     ~MultiWork() {
-        if (h_coef) (void)hipHostFree(h_coef);
         if (h_dots) (void)hipHostFree(h_dots);
     }
 };

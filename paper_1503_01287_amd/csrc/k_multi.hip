@@ -364,47 +364,51 @@ int mdot_blocks(int64_t nd) {
     return static_cast<int>(nb < MDOT_MAX_BLOCKS ? (nb > 0 ? nb : 1) : MDOT_MAX_BLOCKS);
 }
 
+// partial[o] = the workgroup's sum of acc[o], a fixed-order tree
+template <int N>
+__device__ __forceinline__ void mpartials(const double *acc, double *partial) {
+    __shared__ double red[N][TB / 64];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+    for (int o = 0; o < N; ++o) {
+        const double v = gsum<64>(acc[o]);
+        if (lane == 0) red[o][w] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < N) {
+        double v = 0.0;
+#pragma unroll
+        for (int u = 0; u < TB / 64; ++u) v += red[threadIdx.x][u];
+        partial[static_cast<int64_t>(blockIdx.x) * N + threadIdx.x] = v;
+    }
+}
+
+template <typename T>
 struct DotPtrs {
-    const double *a[3];
+    const T *a[3];
     const double *b[3];
 };
 
-// per block: sums over the dofs d = t, t + stride, ... (a fixed assignment),
-// then a fixed-order tree over the block; partial[blk * np K + p K + r]
-template <int NP, int K>
-__global__ void __launch_bounds__(TB) k_mdot(DotPtrs q, int64_t nd, double *partial) {
-    __shared__ double red[NP * K][TB / 64];
-    double acc[NP][K];
+// per block: sums over the dofs d = t, t + stride, ... (a fixed assignment,
+// the same in every kernel below that sums), then a fixed-order tree over the
+// block; partial[blk * np K + p K + r]
+template <int NP, int K, typename T>
+__global__ void __launch_bounds__(TB) k_mdot(DotPtrs<T> q, int64_t nd, double *partial) {
+    double acc[NP * K];
 #pragma unroll
-    for (int p = 0; p < NP; ++p)
-#pragma unroll
-        for (int r = 0; r < K; ++r) acc[p][r] = 0.0;
+    for (int o = 0; o < NP * K; ++o) acc[o] = 0.0;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * TB;
     for (int64_t d = static_cast<int64_t>(blockIdx.x) * TB + threadIdx.x; d < nd; d += stride)
 #pragma unroll
         for (int p = 0; p < NP; ++p)
 #pragma unroll
-            for (int r = 0; r < K; ++r) acc[p][r] += q.a[p][d * K + r] * q.b[p][d * K + r];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-#pragma unroll
-    for (int p = 0; p < NP; ++p)
-#pragma unroll
-        for (int r = 0; r < K; ++r) {
-            const double v = gsum<64>(acc[p][r]);
-            if (lane == 0) red[p * K + r][w] = v;
-        }
-    __syncthreads();
-    if (threadIdx.x < NP * K) {
-        double v = 0.0;
-#pragma unroll
-        for (int u = 0; u < TB / 64; ++u) v += red[threadIdx.x][u];
-        partial[static_cast<int64_t>(blockIdx.x) * NP * K + threadIdx.x] = v;
-    }
+            for (int r = 0; r < K; ++r) acc[p * K + r] += static_cast<double>(q.a[p][d * K + r]) * q.b[p][d * K + r];
+    mpartials<NP * K>(acc, partial);
 }
 
 // out[o] = sum of partial[blk][o] over the nb blocks: one workgroup per
 // output; thread u sums blocks u, u + TB, ... in order, then a fixed-order
-// tree over the workgroup
+// tree over the workgroup. (out is host memory: no copy after it.)
 __global__ void __launch_bounds__(TB) k_mdot_reduce(const double *partial, int nb, int no, double *out) {
     __shared__ double red[TB / 64];
     const int o = blockIdx.x;
@@ -421,42 +425,162 @@ __global__ void __launch_bounds__(TB) k_mdot_reduce(const double *partial, int n
     }
 }
 
-template <int NP>
-static void mdot_np(int K, int nb, const DotPtrs &q, int64_t nd, double *partial, hipStream_t s) {
+static void mreduce(int nb, int no, const double *partial, double *out, hipStream_t s) {
+    AMG_CHECK_LAUNCH();
+    k_mdot_reduce<<<no, TB, 0, s>>>(partial, nb, no, out);
+    AMG_CHECK_LAUNCH();
+}
+
+template <int NP, typename T>
+static void mdot_np(int K, int nb, const DotPtrs<T> &q, int64_t nd, double *partial, hipStream_t s) {
     switch (K) {
-        case 2: k_mdot<NP, 2><<<nb, TB, 0, s>>>(q, nd, partial); break;
-        case 4: k_mdot<NP, 4><<<nb, TB, 0, s>>>(q, nd, partial); break;
-        case 8: k_mdot<NP, 8><<<nb, TB, 0, s>>>(q, nd, partial); break;
+        case 2: k_mdot<NP, 2, T><<<nb, TB, 0, s>>>(q, nd, partial); break;
+        case 4: k_mdot<NP, 4, T><<<nb, TB, 0, s>>>(q, nd, partial); break;
+        case 8: k_mdot<NP, 8, T><<<nb, TB, 0, s>>>(q, nd, partial); break;
         default: throw Error(AMG_EINVAL, "multi dot: K must be 2, 4 or 8");
     }
 }
 
 void launch_mdot(int np, int K, int64_t nd, const double *const *a, const double *const *b, double *partial,
                  double *out, hipStream_t s) {
-    AMG_REQUIRE(np >= 1 && np <= 3, AMG_EINVAL, "multi dot: 1 to 3 pairs");
-    DotPtrs q{};
+    AMG_REQUIRE(np == 1 || np == 2, AMG_EINVAL, "multi dot: 1 or 2 pairs");
+    DotPtrs<double> q{};
     for (int p = 0; p < np; ++p) {
         q.a[p] = a[p];
         q.b[p] = b[p];
     }
     const int nb = mdot_blocks(nd);
-    switch (np) {
-        case 1: mdot_np<1>(K, nb, q, nd, partial, s); break;
-        case 2: mdot_np<2>(K, nb, q, nd, partial, s); break;
-        default: mdot_np<3>(K, nb, q, nd, partial, s); break;
-    }
-    AMG_CHECK_LAUNCH();
-    const int no = np * K;
-    k_mdot_reduce<<<no, TB, 0, s>>>(partial, nb, no, out);
-    AMG_CHECK_LAUNCH();
+    if (np == 1) mdot_np<1>(K, nb, q, nd, partial, s);
+    else mdot_np<2>(K, nb, q, nd, partial, s);
+    mreduce(nb, np * K, partial, out, s);
 }
 
-__global__ void k_mlincomb(int K, int64_t n, double *y, const double *cy, const double *x, const double *cx) {
-    for (int64_t e = static_cast<int64_t>(blockIdx.x) * TB + threadIdx.x; e < n;
-         e += static_cast<int64_t>(gridDim.x) * TB) {
-        const int r = static_cast<int>(e % K);
-        y[e] = cy[r] * y[e] + cx[r] * x[e];
+void launch_mdot_f32(int K, int64_t nd, const float *a, const double *b, double *partial, double *out, hipStream_t s) {
+    DotPtrs<float> q{};
+    q.a[0] = a;
+    q.b[0] = b;
+    const int nb = mdot_blocks(nd);
+    mdot_np<1>(K, nb, q, nd, partial, s);
+    mreduce(nb, K, partial, out, s);
+}
+
+// The iteration's vector work is bound by memory (52 MB a vector of the 32^3
+// Laplacian with 8 right-hand sides), so each vector is read once per
+// synchronisation: both updates, <r, r> and the cycle's FP32 copy of r in one
+// pass, the next direction with its <p, r>; z stays in the cycle's FP32.
+// Thread t takes two neighbouring values (of columns c, c + 1), 16-byte loads
+// and stores side by side over the lanes (a dof's K values per thread, 64 bytes
+// apart, is stored at two thirds of the rate: 88 and 54 us). 52 and 31 us,
+// before them five passes and two conversions, 137 us.
+typedef double double2_t __attribute__((ext_vector_type(2)));
+typedef float float2_t __attribute__((ext_vector_type(2)));
+
+// partial[c] = the workgroup's sum over the threads of column c
+template <int K>
+__device__ __forceinline__ void mcolumns(double2_t acc, double *partial) {
+    __shared__ double red[K][TB / 64];
+    constexpr int H = K / 2;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    double a0 = acc.x, a1 = acc.y;
+#pragma unroll
+    for (int o = 32; o >= H; o >>= 1) {
+        a0 += __shfl_xor(a0, o, 64);
+        a1 += __shfl_xor(a1, o, 64);
     }
+    if (lane < H) {
+        red[2 * lane][w] = a0;
+        red[2 * lane + 1][w] = a1;
+    }
+    __syncthreads();
+    if (threadIdx.x < K) {
+        double v = 0.0;
+#pragma unroll
+        for (int u = 0; u < TB / 64; ++u) v += red[threadIdx.x][u];
+        partial[static_cast<int64_t>(blockIdx.x) * K + threadIdx.x] = v;
+    }
+}
+
+template <int K>
+__global__ void __launch_bounds__(TB) k_mupdate(int64_t n, const MCoef alpha, const double2_t *p, const double2_t *q,
+                                                double2_t *x, double2_t *r, float2_t *r32, double *partial) {
+    constexpr int H = K / 2;
+    const int64_t t = static_cast<int64_t>(blockIdx.x) * TB + threadIdx.x, stride = static_cast<int64_t>(gridDim.x) * TB;
+    const int c = 2 * static_cast<int>(t % H);  // (H divides the stride)
+    const double2_t al = {alpha.c[c], alpha.c[c + 1]};
+    double2_t acc = {0.0, 0.0};
+#pragma unroll 2
+    for (int64_t e = t; e < n; e += stride) {
+        x[e] = x[e] + al * p[e];
+        const double2_t rv = r[e] - al * q[e];
+        r[e] = rv;
+        if (r32) r32[e] = float2_t{static_cast<float>(rv.x), static_cast<float>(rv.y)};
+        acc += rv * rv;
+    }
+    mcolumns<K>(acc, partial);
+}
+
+static const double2_t *pv(const double *v) { return reinterpret_cast<const double2_t *>(v); }
+static double2_t *pv(double *v) { return reinterpret_cast<double2_t *>(v); }
+static const float2_t *pv(const float *v) { return reinterpret_cast<const float2_t *>(v); }
+static float2_t *pv(float *v) { return reinterpret_cast<float2_t *>(v); }
+
+void launch_mupdate(int K, int64_t nd, const MCoef &alpha, const double *p, const double *q, double *x, double *r,
+                    float *r32, double *partial, double *rr, hipStream_t s) {
+    const int nb = mdot_blocks(nd);
+    const int64_t n = nd * K / 2;
+    switch (K) {
+        case 2: k_mupdate<2><<<nb, TB, 0, s>>>(n, alpha, pv(p), pv(q), pv(x), pv(r), pv(r32), partial); break;
+        case 4: k_mupdate<4><<<nb, TB, 0, s>>>(n, alpha, pv(p), pv(q), pv(x), pv(r), pv(r32), partial); break;
+        case 8: k_mupdate<8><<<nb, TB, 0, s>>>(n, alpha, pv(p), pv(q), pv(x), pv(r), pv(r32), partial); break;
+        default: throw Error(AMG_EINVAL, "multi update: K must be 2, 4 or 8");
+    }
+    mreduce(nb, K, partial, rr, s);
+}
+
+// p = z + beta p (first: p = z) and, with r, the partials of <p, r>
+template <int K, typename Z>
+__global__ void __launch_bounds__(TB) k_mdirection(int64_t n, const MCoef beta, int first, const Z *z, double2_t *p,
+                                                   const double2_t *r, double *partial) {
+    constexpr int H = K / 2;
+    const int64_t t = static_cast<int64_t>(blockIdx.x) * TB + threadIdx.x, stride = static_cast<int64_t>(gridDim.x) * TB;
+    const int c = 2 * static_cast<int>(t % H);
+    const double2_t be = {beta.c[c], beta.c[c + 1]};
+    double2_t acc = {0.0, 0.0};
+#pragma unroll 2
+    for (int64_t e = t; e < n; e += stride) {
+        const Z zv = z[e];
+        double2_t pn = {static_cast<double>(zv.x), static_cast<double>(zv.y)};
+        if (!first) pn += be * p[e];
+        p[e] = pn;
+        if (r) acc += pn * r[e];
+    }
+    if (r) mcolumns<K>(acc, partial);
+}
+
+template <typename T>
+void launch_mdirection(int K, int64_t nd, const MCoef &beta, bool first, const T *z, double *p, const double *r,
+                       double *partial, double *pr, hipStream_t s) {
+    const int nb = mdot_blocks(nd), f = first ? 1 : 0;
+    const int64_t n = nd * K / 2;
+    switch (K) {
+        case 2: k_mdirection<2><<<nb, TB, 0, s>>>(n, beta, f, pv(z), pv(p), pv(r), partial); break;
+        case 4: k_mdirection<4><<<nb, TB, 0, s>>>(n, beta, f, pv(z), pv(p), pv(r), partial); break;
+        case 8: k_mdirection<8><<<nb, TB, 0, s>>>(n, beta, f, pv(z), pv(p), pv(r), partial); break;
+        default: throw Error(AMG_EINVAL, "multi direction: K must be 2, 4 or 8");
+    }
+    AMG_CHECK_LAUNCH();
+    if (r) mreduce(nb, K, partial, pr, s);
+}
+template void launch_mdirection<double>(int, int64_t, const MCoef &, bool, const double *, double *, const double *,
+                                        double *, double *, hipStream_t);
+template void launch_mdirection<float>(int, int64_t, const MCoef &, bool, const float *, double *, const double *,
+                                       double *, double *, hipStream_t);
+
+// r = b - r
+__global__ void k_msubtract(int64_t n, const double *b, double *r) {
+    for (int64_t e = static_cast<int64_t>(blockIdx.x) * TB + threadIdx.x; e < n;
+         e += static_cast<int64_t>(gridDim.x) * TB)
+        r[e] = b[e] - r[e];
 }
 
 static int grid_e(int64_t n) {
@@ -464,10 +588,9 @@ static int grid_e(int64_t n) {
     return static_cast<int>(nb > 8192 ? 8192 : (nb > 0 ? nb : 1));
 }
 
-void launch_mlincomb(int K, int64_t nd, double *y, const double *cy, const double *x, const double *cx,
-                     hipStream_t s) {
-    if (nd <= 0) return;
-    k_mlincomb<<<grid_e(nd * K), TB, 0, s>>>(K, nd * K, y, cy, x, cx);
+void launch_msubtract(int64_t n, const double *b, double *r, hipStream_t s) {
+    if (n <= 0) return;
+    k_msubtract<<<grid_e(n), TB, 0, s>>>(n, b, r);
     AMG_CHECK_LAUNCH();
 }
 

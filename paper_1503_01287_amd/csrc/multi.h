@@ -48,13 +48,25 @@ void launch_mdiag_solve(int mode, int kind, int K, int nrows, const int *rowid, 
 // double X, Y; 1 FP32 M, 2 BF16 M with float X, Y
 void launch_mdense(int mkind, const void *M, int m, int ld, int nc, const void *X, void *Y, hipStream_t s);
 // Krylov vector work on interleaved FP64 blocks of n_dof x K values
-// out[p * K + r] = <a_p, b_p> over right-hand side r, for the np pairs (np <= 3), fixed order
+// (sums in a fixed order, into host memory)
+// out[p * K + r] = <a_p, b_p> over right-hand side r, for the np pairs (1 or 2)
 int mdot_blocks(int64_t nd);
 void launch_mdot(int np, int K, int64_t nd, const double *const *a, const double *const *b, double *partial,
                  double *out, hipStream_t s);
-// y[i K + r] = cy[r] y[i K + r] + cx[r] x[i K + r] (coefficient arrays on the device)
-void launch_mlincomb(int K, int64_t nd, double *y, const double *cy, const double *x, const double *cx,
-                     hipStream_t s);
+void launch_mdot_f32(int K, int64_t nd, const float *a, const double *b, double *partial, double *out, hipStream_t s);
+// a coefficient per right-hand side
+struct MCoef {
+    double c[MULTI_MAX_K] = {};
+};
+// x += alpha p, r -= alpha q, r32 = r (unless null), rr[r] = <r, r>
+void launch_mupdate(int K, int64_t nd, const MCoef &alpha, const double *p, const double *q, double *x, double *r,
+                    float *r32, double *partial, double *rr, hipStream_t s);
+// p = z + beta p (first: z) and, unless r is null, pr[r] = <p, r>; z as the cycle leaves it
+template <typename T>
+void launch_mdirection(int K, int64_t nd, const MCoef &beta, bool first, const T *z, double *p, const double *r,
+                       double *partial, double *pr, hipStream_t s);
+// r = b - r over n values
+void launch_msubtract(int64_t n, const double *b, double *r, hipStream_t s);
 // between the caller's layout (nvec <= K vectors of nd one after another) and
 // the interleaved block (columns nvec..K-1 zero going in, dropped coming out)
 void launch_interleave(int K, int nvec, int64_t nd, const double *src, double *dst, bool to_interleaved,

@@ -200,21 +200,11 @@ struct MCycle {
         return smooth(l, b, x, false, false);
     }
 
-    // z = M^{-1} r on FP64 blocks of the finest level
-    void precondition(const double *r, double *z) {
-        const int64_t n = len(0);
+    // M^{-1} r on blocks of the finest level, left where the cycle ends
+    const T *precondition(const T *r, T *x) {
         const int cyc = std::max(1, h->prm.cycles);
-        if (RP) {
-            launch_to_f32(r, W.lv[0].b32.p, n, h->stream);
-            T *x = reinterpret_cast<T *>(W.lv[0].x32.p);
-            for (int k = 0; k < cyc; ++k) x = cycle(0, reinterpret_cast<const T *>(W.lv[0].b32.p), x, k == 0);
-            launch_to_f64(reinterpret_cast<const float *>(x), z, n, h->stream);
-        } else {
-            // (z pairs with the level's t buffer; the result ends in z)
-            T *x = reinterpret_cast<T *>(z);
-            for (int k = 0; k < cyc; ++k) x = cycle(0, reinterpret_cast<const T *>(r), x, k == 0);
-            if (x != reinterpret_cast<T *>(z)) copy(reinterpret_cast<T *>(z), x, n);
-        }
+        for (int k = 0; k < cyc; ++k) x = cycle(0, r, x, k == 0);
+        return x;
     }
 };
 
@@ -243,13 +233,10 @@ static void multi_alloc(amg_ctx *h, MultiWork &W, int K) {
     }
     const size_t nd = static_cast<size_t>(h->n_dof) * K;
     for (DevBuf<double> *v : {&W.B, &W.X, &W.R, &W.Z, &W.P, &W.Q}) v->alloc(nd);
-    W.partial.alloc(static_cast<size_t>(mdot_blocks(h->n_dof)) * 3 * K);
-    W.dots.alloc(3 * K);
-    W.coef.alloc(static_cast<size_t>(MultiWork::SLOTS) * 2 * MULTI_MAX_K);
-    if (!W.h_coef)
-        AMG_HIP(hipHostMalloc(reinterpret_cast<void **>(&W.h_coef),
-                              MultiWork::SLOTS * 2 * MULTI_MAX_K * sizeof(double)));
-    if (!W.h_dots) AMG_HIP(hipHostMalloc(reinterpret_cast<void **>(&W.h_dots), 3 * MULTI_MAX_K * sizeof(double)));
+    W.partial.alloc(static_cast<size_t>(mdot_blocks(h->n_dof)) * 2 * K);
+    if (!W.h_dots)
+        AMG_HIP(hipHostMalloc(reinterpret_cast<void **>(&W.h_dots), 2 * MULTI_MAX_K * sizeof(double),
+                              hipHostMallocCoherent));
 }
 
 // y = A x on the finest level (FP64), K columns
@@ -266,37 +253,13 @@ static void mapply(amg_ctx *h, int K, const double *x, double *y) {
     launch_mrow(L.mode, M_SPMV, MK_F64, K, a, h->stream);
 }
 
-// dots of up to 3 pairs over the K columns, read back to the host (the
-// synchronisation also completes every coefficient copy issued before)
-static std::vector<double> mdots(amg_ctx *h, MultiWork &W, int np, const double *a0, const double *b0,
-                                 const double *a1 = nullptr, const double *b1 = nullptr,
-                                 const double *a2 = nullptr, const double *b2 = nullptr) {
-    const double *A[3] = {a0, a1, a2}, *B[3] = {b0, b1, b2};
-    launch_mdot(np, W.K, h->n_dof, A, B, W.partial.p, W.dots.p, h->stream);
-    AMG_HIP(hipMemcpyAsync(W.h_dots, W.dots.p, static_cast<size_t>(np) * W.K * sizeof(double),
-                           hipMemcpyDeviceToHost, h->stream));
-    AMG_HIP(hipStreamSynchronize(h->stream));
-    W.used = 0;
-    return std::vector<double>(W.h_dots, W.h_dots + np * W.K);
-}
+// the sums that the launches so far have left in h_dots
+static void msync(amg_ctx *h) { AMG_HIP(hipStreamSynchronize(h->stream)); }
 
-// y = cy y + cx x with per-column coefficients, staged through a pinned slot
-// (slots are reused only after a synchronisation in mdots)
-static void mcomb(amg_ctx *h, MultiWork &W, double *y, const std::vector<double> &cy, const double *x,
-                  const std::vector<double> &cx) {
-    if (W.used == MultiWork::SLOTS) {
-        AMG_HIP(hipStreamSynchronize(h->stream));
-        W.used = 0;
-    }
-    const int slot = W.used++;
-    double *c = W.h_coef + static_cast<size_t>(slot) * 2 * MULTI_MAX_K;
-    double *d = W.coef.p + static_cast<size_t>(slot) * 2 * MULTI_MAX_K;
-    for (int r = 0; r < W.K; ++r) {
-        c[r] = cy[r];
-        c[W.K + r] = cx[r];
-    }
-    AMG_HIP(hipMemcpyAsync(d, c, 2 * W.K * sizeof(double), hipMemcpyHostToDevice, h->stream));
-    launch_mlincomb(W.K, h->n_dof, y, d, x, d + W.K, h->stream);
+static std::vector<double> mnorms(amg_ctx *h, MultiWork &W, const double *v) {
+    launch_mdot(1, W.K, h->n_dof, &v, &v, W.partial.p, W.h_dots, h->stream);
+    msync(h);
+    return std::vector<double>(W.h_dots, W.h_dots + W.K);
 }
 
 int solve_multi(amg_ctx *h, int nrhs, const double *B, double *X, double tol, int maxit, amg_result *res) {
@@ -309,24 +272,42 @@ int solve_multi(amg_ctx *h, int nrhs, const double *B, double *X, double tol, in
     const int K = nrhs <= 2 ? 2 : (nrhs <= 4 ? 4 : 8);
     MultiWork &W = h->multi;
     multi_alloc(h, W, K);
-    W.used = 0;
     hipStream_t s = h->stream;
     const int64_t nd = h->n_dof;
     launch_interleave(K, nrhs, nd, B, W.B.p, true, s);
     launch_interleave(K, nrhs, nd, X, W.X.p, true, s);
     MCycle<double> c64{h, W, K};
     MCycle<float> c32{h, W, K};
-    auto prec = [&](const double *r, double *z) {
+    // z of the last preconditioner application: FP32 as a reduced-precision
+    // cycle leaves it (its copy of r is r32), else FP64
+    const double *z64 = nullptr;
+    const float *z32 = nullptr;
+    float *const r32 = h->mixed ? W.lv[0].b32.p : nullptr;
+    auto prec = [&] {
         if (h->mixed)
-            c32.precondition(r, z);
+            z32 = c32.precondition(r32, W.lv[0].x32.p);
         else
-            c64.precondition(r, z);
+            z64 = c64.precondition(W.R.p, W.Z.p);
     };
-    const std::vector<double> one(K, 1.0), zero(K, 0.0), mone(K, -1.0);
+    // sums into h_dots: dot(v) <z, v> at K; direction(r) <p, r> at K
+    double *const second = W.h_dots + K;
+    auto dot_z = [&](const double *v) {
+        if (h->mixed)
+            launch_mdot_f32(K, nd, z32, v, W.partial.p, second, s);
+        else
+            launch_mdot(1, K, nd, &z64, &v, W.partial.p, second, s);
+    };
+    auto direction = [&](const MCoef &beta, bool first, const double *r) {
+        if (h->mixed)
+            launch_mdirection<float>(K, nd, beta, first, z32, W.P.p, r, W.partial.p, second, s);
+        else
+            launch_mdirection<double>(K, nd, beta, first, z64, W.P.p, r, W.partial.p, second, s);
+    };
     // R = B - A X
     mapply(h, K, W.X.p, W.R.p);
-    mcomb(h, W, W.R.p, mone, W.B.p, one);
-    std::vector<double> rr0 = mdots(h, W, 1, W.R.p, W.R.p);
+    launch_msubtract(nd * K, W.B.p, W.R.p, s);
+    if (h->mixed) launch_to_f32(W.R.p, r32, nd * K, s);
+    std::vector<double> rr0 = mnorms(h, W, W.R.p);
     std::vector<int> status(K, AMG_NOT_CONVERGED), iters(K, 0), active(K, 0);
     for (int r = 0; r < K; ++r) {
         if (r >= nrhs || rr0[r] == 0.0) {
@@ -339,13 +320,15 @@ int solve_multi(amg_ctx *h, int nrhs, const double *B, double *X, double tol, in
     }
     auto any_active = [&]() { return std::any_of(active.begin(), active.end(), [](int a) { return a != 0; }); };
     const bool fcg = h->prm.krylov == AMG_KRYLOV_FCG;
-    std::vector<double> rz(K, 0.0), pq_prev(K, 0.0), alpha(K, 0.0), beta(K, 0.0), malpha(K, 0.0);
+    std::vector<double> rz(K, 0.0), pq_prev(K, 0.0);
+    MCoef alpha, beta;
     int it = 0;
     if (!fcg && any_active()) {
-        prec(W.R.p, W.Z.p);
-        const std::vector<double> d = mdots(h, W, 1, W.R.p, W.Z.p);
-        for (int r = 0; r < K; ++r) rz[r] = d[r];
-        launch_copy(W.P.p, W.Z.p, nd * K, s);
+        prec();
+        dot_z(W.R.p);
+        direction(beta, true, nullptr);
+        msync(h);
+        std::copy(second, second + K, rz.begin());
     }
     // While every running column's last relative residual is above
     // KRYLOV_AHEAD * tol, the next preconditioner application goes ahead of
@@ -355,45 +338,50 @@ int solve_multi(amg_ctx *h, int nrhs, const double *B, double *X, double tol, in
     double relmin = 1.0;
     bool ahead = false;             // z of this iteration already computed
     std::vector<double> zdot(K);    // its dot, read with the last stopping test
+    auto z_and_dot = [&](const double *v) {
+        if (ahead) return;
+        prec();
+        dot_z(v);
+        msync(h);
+        std::copy(second, second + K, zdot.begin());
+    };
     while (it < maxit && any_active()) {
         if (fcg) {
-            if (!ahead) prec(W.R.p, W.Z.p);
+            // beta = -<z, q_prev> / <p_prev, q_prev>: p = z + beta p_prev
             if (it == 0) {
-                launch_copy(W.P.p, W.Z.p, nd * K, s);
+                prec();
             } else {
-                // beta = -<z, q_prev> / <p_prev, q_prev>: p = z + beta p_prev
-                const std::vector<double> d = ahead ? zdot : mdots(h, W, 1, W.Z.p, W.Q.p);
-                for (int r = 0; r < K; ++r) beta[r] = active[r] && pq_prev[r] != 0.0 ? -d[r] / pq_prev[r] : 0.0;
-                mcomb(h, W, W.P.p, beta, W.Z.p, one);
+                z_and_dot(W.Q.p);
+                for (int r = 0; r < K; ++r) beta.c[r] = active[r] && pq_prev[r] != 0.0 ? -zdot[r] / pq_prev[r] : 0.0;
             }
+            direction(beta, it == 0, W.R.p);
         }
         mapply(h, K, W.P.p, W.Q.p);
-        const std::vector<double> d = fcg ? mdots(h, W, 2, W.P.p, W.Q.p, W.P.p, W.R.p) : mdots(h, W, 1, W.P.p, W.Q.p);
+        const double *pp = W.P.p, *qq = W.Q.p;
+        launch_mdot(1, K, nd, &pp, &qq, W.partial.p, W.h_dots, s);
+        msync(h);
         for (int r = 0; r < K; ++r) {
-            alpha[r] = 0.0;
+            alpha.c[r] = 0.0;
             if (!active[r]) continue;
-            const double pq = d[r];
+            const double pq = W.h_dots[r];
             if (!(pq > 0.0) || !std::isfinite(pq)) {
                 status[r] = (pq == pq) ? AMG_BREAKDOWN : AMG_DIVERGED;
                 active[r] = 0;
                 continue;
             }
-            alpha[r] = (fcg ? d[K + r] : rz[r]) / pq;
+            alpha.c[r] = (fcg ? second[r] : rz[r]) / pq;
             pq_prev[r] = pq;
         }
-        for (int r = 0; r < K; ++r) malpha[r] = -alpha[r];
-        mcomb(h, W, W.X.p, one, W.P.p, alpha);
-        mcomb(h, W, W.R.p, one, W.Q.p, malpha);
+        launch_mupdate(K, nd, alpha, W.P.p, W.Q.p, W.X.p, W.R.p, r32, W.partial.p, W.h_dots, s);
         ++it;
         ahead = it < maxit && relmin > KRYLOV_AHEAD * tol;
-        std::vector<double> rrv;
         if (ahead) {
-            prec(W.R.p, W.Z.p);
-            rrv = fcg ? mdots(h, W, 2, W.R.p, W.R.p, W.Z.p, W.Q.p) : mdots(h, W, 2, W.R.p, W.R.p, W.R.p, W.Z.p);
-            std::copy(rrv.begin() + K, rrv.end(), zdot.begin());
-        } else {
-            rrv = mdots(h, W, 1, W.R.p, W.R.p);
+            prec();
+            dot_z(fcg ? W.Q.p : W.R.p);
         }
+        msync(h);
+        const std::vector<double> rrv(W.h_dots, W.h_dots + K);
+        if (ahead) std::copy(second, second + K, zdot.begin());
         relmin = 1e300;
         for (int r = 0; r < K; ++r) {
             if (!active[r]) continue;
@@ -410,19 +398,18 @@ int solve_multi(amg_ctx *h, int nrhs, const double *B, double *X, double tol, in
             }
         }
         if (!fcg && it < maxit && any_active()) {
-            if (!ahead) prec(W.R.p, W.Z.p);
-            const std::vector<double> dz = ahead ? zdot : mdots(h, W, 1, W.R.p, W.Z.p);
+            z_and_dot(W.R.p);
             for (int r = 0; r < K; ++r) {
-                beta[r] = active[r] && rz[r] != 0.0 ? dz[r] / rz[r] : 0.0;
-                if (active[r]) rz[r] = dz[r];
+                beta.c[r] = active[r] && rz[r] != 0.0 ? zdot[r] / rz[r] : 0.0;
+                if (active[r]) rz[r] = zdot[r];
             }
-            mcomb(h, W, W.P.p, beta, W.Z.p, one);
+            direction(beta, false, nullptr);
         }
     }
     // true residuals
     mapply(h, K, W.X.p, W.R.p);
-    mcomb(h, W, W.R.p, mone, W.B.p, one);
-    std::vector<double> rr = mdots(h, W, 1, W.R.p, W.R.p);
+    launch_msubtract(nd * K, W.B.p, W.R.p, s);
+    std::vector<double> rr = mnorms(h, W, W.R.p);
     launch_interleave(K, nrhs, nd, W.X.p, X, false, s);
     AMG_HIP(hipStreamSynchronize(s));
     const double ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
