@@ -305,53 +305,147 @@ void launch_mdiag_solve(int mode, int kind, int K, int nrows, const int *rowid, 
 }
 
 // ---------------------------------------------------------------- dense coarse end
-// Y = M X with NC columns (M's rows ld values apart): one wavefront per row
-// of M, lane j walks columns j, j + 64, ... and keeps NC partial sums
-template <int MK, int NC>
-__global__ void __launch_bounds__(TB) k_mdense(const void *M, int m, int ld, const void *Xv, void *Yv) {
-    using T = vec_t<MK>;
+// Y = M X with NC columns (M's rows ld values apart), FP64: one wavefront per
+// row of M, lane j walks columns j, j + 64, ... and keeps NC partial sums
+template <int NC>
+__global__ void __launch_bounds__(TB) k_mdense(const double *M, int m, int ld, const double *X, double *Y) {
+    using T = double;
     const int row = blockIdx.x * (TB / 64) + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (row >= m) return;
-    const T *X = static_cast<const T *>(Xv);
     T acc[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) acc[c] = T(0);
     const int64_t base = static_cast<int64_t>(row) * ld;
     for (int j = lane; j < m; j += 64) {
-        const T v = ldv<MK>(M, base + j);
+        const T v = M[base + j];
 #pragma unroll
         for (int c = 0; c < NC; ++c) acc[c] += v * X[static_cast<int64_t>(j) * NC + c];
     }
 #pragma unroll
     for (int c = 0; c < NC; ++c) acc[c] = gsum<64>(acc[c]);
-    T *Y = static_cast<T *>(Yv);
 #pragma unroll
     for (int c = 0; c < NC; ++c)
         if (lane == c) Y[static_cast<int64_t>(row) * NC + c] = acc[c];
 }
 
+// The same with an FP32 or BF16 M (16-byte aligned, ld a multiple of 8, zeros
+// past m) and FP32 matrix instructions: a workgroup takes 16 rows and all
+// columns, its 16 wavefronts chunks of 32 of the sum. With a wavefront per row
+// every row reads all of X again (273 KB at m = 2846, 24 columns: 37 us for 16
+// MB of M); here 16 rows share it. A lane's 8 values of M are neighbours in
+// its row, so the k-th instruction of a chunk sums the columns 8 g + k of its
+// four lane groups g. Each output is a sum of 64 partial sums, as with a
+// wavefront per row (relative error against 64 bits, m = 100 to 6880, 2 to 24
+// columns: 0.7e-7 to 2.0e-7 either way). Bound by the reads of X and of M from
+// the L2: m = 2846, BF16, 24 columns 37 -> 17 us; 5217: 127 -> 50 us, 6
+// columns 39 -> 28; 6880, 8 columns 76 -> 36.
+constexpr int DW = 16;  // wavefronts
+template <int MK, int NC>
+__global__ void __launch_bounds__(64 * DW) k_mdense_mfma(const void *M, int m, int ld, const float *X, float *Y) {
+    typedef float float4_t __attribute__((ext_vector_type(4)));
+    typedef uint32_t uint4_t __attribute__((ext_vector_type(4)));
+    constexpr int CT = (NC + 15) / 16;
+    __shared__ float part[DW][CT][256];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+    const int row0 = blockIdx.x * 16, row = row0 + r < m ? row0 + r : m - 1;
+    const int64_t base = static_cast<int64_t>(row) * ld;
+    float4_t acc[CT][4];
+#pragma unroll
+    for (int t = 0; t < CT; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[t][q] = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 32 * w; k0 < m; k0 += 32 * DW) {
+        const int k = k0 + 8 * g;
+        float a[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a[u] = 0.f;
+        if (k < ld) {
+            if constexpr (MK == MK_BF16) {
+                const uint4_t v = *reinterpret_cast<const uint4_t *>(static_cast<const uint16_t *>(M) + base + k);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    a[2 * u] = __uint_as_float(v[u] << 16);
+                    a[2 * u + 1] = __uint_as_float(v[u] & 0xffff0000u);
+                }
+            } else {
+                const float4_t *v = reinterpret_cast<const float4_t *>(static_cast<const float *>(M) + base + k);
+                const float4_t lo = v[0], hi = v[1];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    a[u] = lo[u];
+                    a[4 + u] = hi[u];
+                }
+            }
+        }
+        float b[CT][8];
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int c = 16 * t + r;
+                b[t][u] = k + u < m && c < NC ? X[static_cast<int64_t>(k + u) * NC + c] : 0.f;
+            }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int t = 0; t < CT; ++t)
+                acc[t][u % 4] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], b[t][u], acc[t][u % 4], 0, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < CT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            part[w][t][16 * (4 * g + i) + r] = (acc[t][0][i] + acc[t][1][i]) + (acc[t][2][i] + acc[t][3][i]);
+    __syncthreads();
+    for (int o = threadIdx.x; o < CT * 256; o += 64 * DW) {
+        const int t = o >> 8, e = o & 255, i = row0 + (e >> 4), c = 16 * t + (e & 15);
+        if (i >= m || c >= NC) continue;
+        float v[DW];
+#pragma unroll
+        for (int u = 0; u < DW; ++u) v[u] = part[u][t][e];
+#pragma unroll
+        for (int h = DW / 2; h > 0; h /= 2)
+#pragma unroll
+            for (int u = 0; u < h; ++u) v[u] += v[u + h];
+        Y[static_cast<int64_t>(i) * NC + c] = v[0];
+    }
+}
+
 template <int MK>
-static void mdense_nc(const void *M, int m, int ld, int nc, const void *X, void *Y, hipStream_t s) {
+static void mdense_mfma(const void *M, int m, int ld, int nc, const float *X, float *Y, hipStream_t s) {
+    const int nb = ceil_div(m, 16);
+    switch (nc) {
+        case 2: k_mdense_mfma<MK, 2><<<nb, 64 * DW, 0, s>>>(M, m, ld, X, Y); break;
+        case 4: k_mdense_mfma<MK, 4><<<nb, 64 * DW, 0, s>>>(M, m, ld, X, Y); break;
+        case 6: k_mdense_mfma<MK, 6><<<nb, 64 * DW, 0, s>>>(M, m, ld, X, Y); break;
+        case 8: k_mdense_mfma<MK, 8><<<nb, 64 * DW, 0, s>>>(M, m, ld, X, Y); break;
+        case 12: k_mdense_mfma<MK, 12><<<nb, 64 * DW, 0, s>>>(M, m, ld, X, Y); break;
+        case 24: k_mdense_mfma<MK, 24><<<nb, 64 * DW, 0, s>>>(M, m, ld, X, Y); break;
+        default: throw Error(AMG_EINVAL, "multi dense kernel: unsupported column count");
+    }
+}
+
+static void mdense_f64(const double *M, int m, int ld, int nc, const double *X, double *Y, hipStream_t s) {
     const int nb = ceil_div(m, TB / 64);
     switch (nc) {
-        case 2: k_mdense<MK, 2><<<nb, TB, 0, s>>>(M, m, ld, X, Y); break;
-        case 4: k_mdense<MK, 4><<<nb, TB, 0, s>>>(M, m, ld, X, Y); break;
-        case 6: k_mdense<MK, 6><<<nb, TB, 0, s>>>(M, m, ld, X, Y); break;
-        case 8: k_mdense<MK, 8><<<nb, TB, 0, s>>>(M, m, ld, X, Y); break;
-        case 12: k_mdense<MK, 12><<<nb, TB, 0, s>>>(M, m, ld, X, Y); break;
-        case 24: k_mdense<MK, 24><<<nb, TB, 0, s>>>(M, m, ld, X, Y); break;
+        case 2: k_mdense<2><<<nb, TB, 0, s>>>(M, m, ld, X, Y); break;
+        case 4: k_mdense<4><<<nb, TB, 0, s>>>(M, m, ld, X, Y); break;
+        case 6: k_mdense<6><<<nb, TB, 0, s>>>(M, m, ld, X, Y); break;
+        case 8: k_mdense<8><<<nb, TB, 0, s>>>(M, m, ld, X, Y); break;
+        case 12: k_mdense<12><<<nb, TB, 0, s>>>(M, m, ld, X, Y); break;
+        case 24: k_mdense<24><<<nb, TB, 0, s>>>(M, m, ld, X, Y); break;
         default: throw Error(AMG_EINVAL, "multi dense kernel: unsupported column count");
     }
 }
 
 void launch_mdense(int mkind, const void *M, int m, int ld, int nc, const void *X, void *Y, hipStream_t s) {
     if (m <= 0) return;
-    AMG_REQUIRE(ld >= m, AMG_EINVAL, "multi dense kernel: row stride below m");
+    AMG_REQUIRE(ld >= m && (mkind == MK_F64 || ld % 8 == 0), AMG_EINVAL, "multi dense kernel: row stride");
     switch (mkind) {
-        case MK_F64: mdense_nc<MK_F64>(M, m, ld, nc, X, Y, s); break;
-        case MK_F32: mdense_nc<MK_F32>(M, m, ld, nc, X, Y, s); break;
-        default: mdense_nc<MK_BF16>(M, m, ld, nc, X, Y, s); break;
+        case MK_F64: mdense_f64(static_cast<const double *>(M), m, ld, nc, static_cast<const double *>(X), static_cast<double *>(Y), s); break;
+        case MK_F32: mdense_mfma<MK_F32>(M, m, ld, nc, static_cast<const float *>(X), static_cast<float *>(Y), s); break;
+        default: mdense_mfma<MK_BF16>(M, m, ld, nc, static_cast<const float *>(X), static_cast<float *>(Y), s); break;
     }
     AMG_CHECK_LAUNCH();
 }
