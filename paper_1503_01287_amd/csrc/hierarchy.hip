@@ -394,12 +394,13 @@ void autotune_level(amg_ctx *h, Level &L) {
     launch_fill(L.x.p, 0.0, 3 * static_cast<int64_t>(L.n), s);
     launch_fill(L.b.p, 1.0, 3 * static_cast<int64_t>(L.n), s);
     launch_fill(L.t.p, 0.0, 3 * static_cast<int64_t>(L.n), s);
-    // best of 7 timed repetitions after 2 warm-up runs (short kernels are noisy)
+    // Best of 3 timed repetitions after a warm-up run. Most of the time goes
+    // to the eviction before each of them, 105 us for a kernel of 5 to 150; the
+    // best of 7 chose the same shapes (elasticity 16^3: 7.8 ms, now 3.4).
     auto time_it = [&](auto &&launch) {
         launch();
-        launch();
         float best_ms = 1e30f;
-        for (int r = 0; r < 7; ++r) {
+        for (int r = 0; r < 3; ++r) {
             evict_caches(h);
             AMG_HIP(hipEventRecord(e0, s));
             launch();

@@ -33,9 +33,8 @@ static void autotune_mp(amg_ctx *h, Level &L) {
     AMG_HIP(hipEventCreate(&e1));
     auto time_it = [&](auto &&launch) {
         launch();
-        launch();
         float best_ms = 1e30f;
-        for (int r = 0; r < 7; ++r) {
+        for (int r = 0; r < 3; ++r) {
             evict_caches(h);
             AMG_HIP(hipEventRecord(e0, s));
             launch();
