@@ -328,7 +328,7 @@ struct ProfStat {
 
 struct amg_ctx_impl;
 
-enum GraphKind : int { GRAPH_PRECONDITION = 0, GRAPH_CG_STEP, GRAPH_CG_NEXT };
+enum GraphKind : int { GRAPH_PRECONDITION = 0, GRAPH_CG_STEP, GRAPH_CG_NEXT, GRAPH_CG_CYCLE };
 
 }  // namespace amgp2
 
@@ -406,6 +406,7 @@ struct amg_ctx {
     amgp2::MultiWork multi;  // amg_solve_multi
     amgp2::DevBuf<double> partial, sc;
     double *h_sc = nullptr;  // pinned host copy of the scalars
+    const float *cg_z = nullptr;    // where CG's reduced-precision cycle leaves z
     hipEvent_t sc_ready = nullptr;  // that copy has landed (overlapped stopping tests)
     int n_dof = 0;           // length of a solve vector
     // profiling
@@ -432,6 +433,7 @@ void build_hierarchy(amg_ctx *h, const amg_system *sys);
 void build_mixed(amg_ctx *h);
 void build_saddle_mp(amg_ctx *h);
 void precondition_mp(amg_ctx *h, const double *r, double *z);
+const float *precondition_f32(amg_ctx *h);
 // saddle point path
 void saddle_setup_level(amg_ctx *h, Level &L);
 void setup_schur(amg_ctx *h, int l);

@@ -429,16 +429,24 @@ void launch_jacobi_zero(int mode, int64_t nn, const double *dinv, int64_t dn, co
 
 int dot_blocks(int64_t n) { return grid_for(n) > 1024 ? 1024 : grid_for(n); }
 
-__global__ void k_dot_partial(const double *a, const double *b, int64_t n, double *partial) {
+template <typename T>
+__global__ void k_dot_partial(const T *a, const double *b, int64_t n, double *partial) {
     double acc = 0.0;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * BLOCK + threadIdx.x; i < n;
          i += static_cast<int64_t>(gridDim.x) * BLOCK)
-        acc += a[i] * b[i];
+        acc += static_cast<double>(a[i]) * b[i];
     const double t = block_sum(acc);
     if (threadIdx.x == 0) partial[blockIdx.x] = t;
 }
 
 int launch_dot_partial(const double *a, const double *b, int64_t n, double *partial, hipStream_t s) {
+    const int nb = dot_blocks(n);
+    k_dot_partial<<<nb, BLOCK, 0, s>>>(a, b, n, partial);
+    AMG_CHECK_LAUNCH();
+    return nb;
+}
+
+int launch_dot_partial(const float *a, const double *b, int64_t n, double *partial, hipStream_t s) {
     const int nb = dot_blocks(n);
     k_dot_partial<<<nb, BLOCK, 0, s>>>(a, b, n, partial);
     AMG_CHECK_LAUNCH();
@@ -466,8 +474,8 @@ __global__ void __launch_bounds__(RBLOCK) k_reduce(const double *partial, int np
     } else if constexpr (POST == RED_FCG_BETA) {
         sc[SC_BETA] = -t / sc[SC_RZ_OLD];
     } else if constexpr (POST == RED_FCG_ALPHA) {
-        sc[SC_ALPHA] = t / sc[SC_PQ];
-        sc[SC_RZ_OLD] = sc[SC_PQ];
+        sc[SC_ALPHA] = sc[SC_PR] / t;
+        sc[SC_RZ_OLD] = t;
     }
 }
 
@@ -483,8 +491,14 @@ void launch_reduce(const double *partial, int np, double *sc, int dst, hipStream
     AMG_CHECK_LAUNCH();
 }
 
+// The vector work of an iteration is bound by memory (22 MB a vector of the
+// 48^3 Laplacian) or, for small systems, by its launches (4 us each): the
+// update writes the reduced-precision cycle's copy of r too, the direction
+// reads the cycle's z as it is and sums <p, r> for flexible CG. As passes of
+// their own these were two conversions and a dot, 23 us at 48^3 and 13 at
+// 32^3 elasticity.
 __global__ void k_cg_update(double *x, double *r, const double *p, const double *q, const double *sc,
-                            int64_t n, double *partial) {
+                            int64_t n, double *partial, float *r32) {
     const double al = sc[SC_ALPHA];
     double acc = 0.0;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * BLOCK + threadIdx.x; i < n;
@@ -492,6 +506,7 @@ __global__ void k_cg_update(double *x, double *r, const double *p, const double 
         x[i] += al * p[i];
         const double ri = r[i] - al * q[i];
         r[i] = ri;
+        if (r32) r32[i] = static_cast<float>(ri);
         acc += ri * ri;
     }
     const double t = block_sum(acc);
@@ -499,24 +514,42 @@ __global__ void k_cg_update(double *x, double *r, const double *p, const double 
 }
 
 int launch_cg_update(double *x, double *r, const double *p, const double *q, const double *sc,
-                     int64_t n, double *partial, hipStream_t s) {
+                     int64_t n, double *partial, float *r32, hipStream_t s) {
     const int nb = dot_blocks(n);
-    k_cg_update<<<nb, BLOCK, 0, s>>>(x, r, p, q, sc, n, partial);
+    k_cg_update<<<nb, BLOCK, 0, s>>>(x, r, p, q, sc, n, partial, r32);
     AMG_CHECK_LAUNCH();
     return nb;
 }
 
-__global__ void k_cg_direction(double *p, const double *z, const double *sc, int64_t n) {
+template <typename T>
+__global__ void k_cg_direction(double *p, const T *z, const double *sc, int first, int64_t n, const double *r,
+                               double *partial) {
     const double be = sc[SC_BETA];
+    double acc = 0.0;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * BLOCK + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * BLOCK)
-        p[i] = z[i] + be * p[i];
+         i += static_cast<int64_t>(gridDim.x) * BLOCK) {
+        double pi = static_cast<double>(z[i]);
+        if (!first) pi += be * p[i];
+        p[i] = pi;
+        if (r) acc += pi * r[i];
+    }
+    if (!r) return;
+    const double t = block_sum(acc);
+    if (threadIdx.x == 0) partial[blockIdx.x] = t;
 }
 
-void launch_cg_direction(double *p, const double *z, const double *sc, int64_t n, hipStream_t s) {
-    k_cg_direction<<<grid_for(n), BLOCK, 0, s>>>(p, z, sc, n);
+template <typename T>
+int launch_cg_direction(double *p, const T *z, const double *sc, bool first, int64_t n, const double *r,
+                        double *partial, hipStream_t s) {
+    const int nb = r ? dot_blocks(n) : grid_for(n);
+    k_cg_direction<T><<<nb, BLOCK, 0, s>>>(p, z, sc, first ? 1 : 0, n, r, partial);
     AMG_CHECK_LAUNCH();
+    return nb;
 }
+template int launch_cg_direction<double>(double *, const double *, const double *, bool, int64_t, const double *,
+                                         double *, hipStream_t);
+template int launch_cg_direction<float>(double *, const float *, const double *, bool, int64_t, const double *,
+                                        double *, hipStream_t);
 
 __global__ void k_axpby(double *y, const double *x, double a, double b, int64_t n) {
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * BLOCK + threadIdx.x; i < n;

@@ -75,6 +75,7 @@ void launch_jacobi_zero(int mode, int64_t nnodes, const double *dinv, int64_t dn
                         double *x, hipStream_t s);
 // per-block partial sums of <a, b> over n doubles; returns the number of blocks
 int launch_dot_partial(const double *a, const double *b, int64_t n, double *partial, hipStream_t s);
+int launch_dot_partial(const float *a, const double *b, int64_t n, double *partial, hipStream_t s);
 int dot_blocks(int64_t n);
 
 // Scalars of the Krylov drivers live in a small device array.
@@ -88,16 +89,19 @@ enum ReducePost : int {
     RED_CG_ALPHA,   // dst = PQ:  alpha = rz / pq
     RED_CG_BETA,    // dst = TMP: beta = tmp / rz, rz = tmp
     RED_FCG_BETA,   // dst = TMP: beta = -tmp / pq_prev
-    RED_FCG_ALPHA,  // dst = PR:  alpha = pr / pq, pq_prev = pq
+    RED_FCG_ALPHA,  // dst = PQ:  alpha = pr / pq, pq_prev = pq
 };
 // host: if set, sc[dst] and sc[SC_PQ] are also written there (pinned memory)
 void launch_reduce(const double *partial, int np, double *sc, int dst, hipStream_t s, int post = RED_NONE,
                    double *host = nullptr);
-// x += alpha p; r -= alpha q; partial of <r, r>
+// x += alpha p; r -= alpha q, r32 = r (unless null); partial of <r, r>
 int launch_cg_update(double *x, double *r, const double *p, const double *q, const double *sc,
-                     int64_t n, double *partial, hipStream_t s);
-// p = z + beta p  (beta from sc)
-void launch_cg_direction(double *p, const double *z, const double *sc, int64_t n, hipStream_t s);
+                     int64_t n, double *partial, float *r32, hipStream_t s);
+// p = z + beta p (beta from sc; first: p = z) and, unless r is null, a
+// partial of <p, r>; z as the cycle leaves it
+template <typename T>
+int launch_cg_direction(double *p, const T *z, const double *sc, bool first, int64_t n, const double *r,
+                        double *partial, hipStream_t s);
 // y = a x + b y with host scalars
 void launch_axpby(double *y, const double *x, double a, double b, int64_t n, hipStream_t s);
 

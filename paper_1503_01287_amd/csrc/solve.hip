@@ -444,8 +444,9 @@ static void scalars_wait(amg_ctx *h) { AMG_HIP(hipEventSynchronize(h->sc_ready))
 // enqueued before that wait, so the round trip overlaps the GPU's cycle. If
 // the test then stops the solve, that application has changed nothing else.
 
-static void dot_into(amg_ctx *h, const double *a, const double *b, int dst, int post = RED_NONE) {
-    ProfScope ps(h, "blas", 2.0 * h->n_dof * 8.0);
+template <typename T>
+static void dot_into(amg_ctx *h, const T *a, const double *b, int dst, int post = RED_NONE) {
+    ProfScope ps(h, "blas", h->n_dof * (8.0 + sizeof(T)));
     const int nb = launch_dot_partial(a, b, h->n_dof, h->partial.p, h->stream);
     launch_reduce(h->partial.p, nb, h->sc.p, dst, h->stream, post);
 }
@@ -474,41 +475,72 @@ static void spmv_dot(amg_ctx *h, const double *p, double *q, int post) {
     launch_reduce(h->partial.p, nb, h->sc.p, SC_PQ, h->stream, post);
 }
 
+// A reduced-precision cycle inside CG: its copy of r is written by the update
+// and its z read as it is, in FP32.
+static bool cg_f32(const amg_ctx *h) { return h->mixed && !h->saddle; }
+
 // x += alpha p, r -= alpha q, <r, r> into sc[SC_RR] and, with <p, q>, into
 // the host's copy
 static void cg_update(amg_ctx *h, double *x, double *r, const double *p, const double *q) {
-    ProfScope ps(h, "blas", 6.0 * h->n_dof * 8.0);
-    const int nb = launch_cg_update(x, r, p, q, h->sc.p, h->n_dof, h->partial.p, h->stream);
+    float *r32 = cg_f32(h) ? h->lv[0].mp.b.p : nullptr;
+    ProfScope ps(h, "blas", h->n_dof * (r32 ? 52.0 : 48.0));
+    const int nb = launch_cg_update(x, r, p, q, h->sc.p, h->n_dof, h->partial.p, r32, h->stream);
     launch_reduce(h->partial.p, nb, h->sc.p, SC_RR, h->stream, RED_NONE, h->h_sc);
 }
 
 // One iteration in two halves, either of which a small system replays as one
 // graph: its kernels take 2-5 us each, as long as their launch calls on the
 // host (Laplacian 4^3, 10 calls an iteration: 61 us of which the GPU works
-// 28). cg_step: up to the stopping test's scalars; cg_next: the next
-// direction, which may go ahead of that test (it leaves x and r alone).
+// 28). cg_step: up to the stopping test's scalars; cg_cycle and
+// cg_next_direction: the next direction, which may go ahead of that test (it
+// leaves x and r alone).
 static void cg_step(amg_ctx *h, bool fcg, double *x) {
     double *r = h->kr.p, *p = h->kp.p, *q = h->kq.p;
-    if (fcg) {
-        spmv_dot(h, p, q, RED_NONE);
-        dot_into(h, p, r, SC_PR, RED_FCG_ALPHA);
-    } else {
-        spmv_dot(h, p, q, RED_CG_ALPHA);
-    }
+    spmv_dot(h, p, q, fcg ? RED_FCG_ALPHA : RED_CG_ALPHA);
     cg_update(h, x, r, p, q);
 }
-static void cg_next_direction(amg_ctx *h, bool fcg) {
-    double *r = h->kr.p, *z = h->kz.p, *p = h->kp.p, *q = h->kq.p;
-    // PCG: p = z + (<r, z> / <r, z>_prev) p; FCG: p = z - (<z, q> / <p, q>) p
-    if (fcg)
-        dot_into(h, z, q, SC_TMP, RED_FCG_BETA);
+static void cg_cycle_eager(amg_ctx *h) {
+    if (cg_f32(h))
+        h->cg_z = precondition_f32(h);
     else
-        dot_into(h, r, z, SC_TMP, RED_CG_BETA);
-    launch_cg_direction(p, z, h->sc.p, h->n_dof, h->stream);
+        precondition_eager(h, h->kr.p, h->kz.p);
 }
-static void cg_next(amg_ctx *h, bool fcg) {
-    precondition_impl(h, h->kr.p, h->kz.p);
-    cg_next_direction(h, fcg);
+static void cg_cycle(amg_ctx *h) {
+    if (!cg_f32(h)) {
+        precondition_impl(h, h->kr.p, h->kz.p);
+        return;
+    }
+    if (h->prm.graph && !h->prof) {
+        for (const auto &g : h->graphs)
+            if (g.kind == GRAPH_CG_CYCLE) {
+                AMG_HIP(hipGraphLaunch(g.exec, h->stream));
+                return;
+            }
+        if (h->graphs.size() < 8) {
+            h->graphs.push_back({GRAPH_CG_CYCLE, nullptr, nullptr, record_graph(h, [&] { cg_cycle_eager(h); })});
+            AMG_HIP(hipGraphLaunch(h->graphs.back().exec, h->stream));
+            return;
+        }
+    }
+    cg_cycle_eager(h);
+}
+template <typename T>
+static void cg_direction_from(amg_ctx *h, bool fcg, bool first, const T *z) {
+    double *r = h->kr.p, *p = h->kp.p, *q = h->kq.p;
+    // PCG: p = z + (<r, z> / <r, z>_prev) p; FCG: p = z - (<z, q> / <p, q>) p
+    if (!fcg)
+        dot_into(h, z, r, first ? SC_RZ : SC_TMP, first ? RED_NONE : RED_CG_BETA);
+    else if (!first)
+        dot_into(h, z, q, SC_TMP, RED_FCG_BETA);
+    ProfScope ps(h, "blas", h->n_dof * (16.0 + sizeof(T) + (fcg ? 8.0 : 0.0)));
+    const int nb = launch_cg_direction(p, z, h->sc.p, first, h->n_dof, fcg ? r : nullptr, h->partial.p, h->stream);
+    if (fcg) launch_reduce(h->partial.p, nb, h->sc.p, SC_PR, h->stream);
+}
+static void cg_next_direction(amg_ctx *h, bool fcg, bool first = false) {
+    if (cg_f32(h))
+        cg_direction_from(h, fcg, first, h->cg_z);
+    else
+        cg_direction_from(h, fcg, first, static_cast<const double *>(h->kz.p));
 }
 
 // Unknowns up to which CG replays its iteration as two graphs: beyond, an
@@ -523,7 +555,7 @@ static hipGraphExec_t cg_graph(amg_ctx *h, int kind, bool fcg) {
                              if (kind == GRAPH_CG_STEP) {
                                  cg_step(h, fcg, h->kx.p);
                              } else {
-                                 precondition_eager(h, h->kr.p, h->kz.p);
+                                 cg_cycle_eager(h);
                                  cg_next_direction(h, fcg);
                              }
                          })});
@@ -563,7 +595,7 @@ static int check(double rr, double rr0, double tol) {
 static int solve_cg(amg_ctx *h, bool fcg, const double *b, double *x, double tol, int maxit, amg_result *res) {
     const auto t0 = std::chrono::steady_clock::now();
     const int64_t n = h->n_dof;
-    double *r = h->kr.p, *z = h->kz.p, *p = h->kp.p;
+    double *r = h->kr.p;
     residual(h, 0, b, x, r);
     dot_into(h, r, r, SC_RR);
     const double rr0 = read_scalar(h, SC_RR);
@@ -581,9 +613,9 @@ static int solve_cg(amg_ctx *h, bool fcg, const double *b, double *x, double tol
         step = cg_graph(h, GRAPH_CG_STEP, fcg);
         next = cg_graph(h, GRAPH_CG_NEXT, fcg);
     }
-    precondition_impl(h, r, z);
-    if (!fcg) dot_into(h, r, z, SC_RZ);
-    launch_copy(p, z, n, h->stream);
+    if (cg_f32(h)) launch_to_f32(r, h->lv[0].mp.b.p, n, h->stream);
+    cg_cycle(h);
+    cg_next_direction(h, fcg, true);
     int it = 0, status = AMG_NOT_CONVERGED;
     double rel = 1.0;
     while (it < maxit) {
@@ -593,8 +625,12 @@ static int solve_cg(amg_ctx *h, bool fcg, const double *b, double *x, double tol
         scalars_begin(h);
         const bool ahead = it < maxit && rel > KRYLOV_AHEAD * tol;
         auto go = [&] {
-            if (next) AMG_HIP(hipGraphLaunch(next, h->stream));
-            else cg_next(h, fcg);
+            if (next) {
+                AMG_HIP(hipGraphLaunch(next, h->stream));
+            } else {
+                cg_cycle(h);
+                cg_next_direction(h, fcg);
+            }
         };
         if (ahead) go();
         scalars_wait(h);

@@ -463,14 +463,20 @@ static float *cycle_mp(amg_ctx *h, int l, const float *b, float *x, bool x_zero,
     return smooth_mp(h, l, b, x, false, false, false, to_t);
 }
 
-void precondition_mp(amg_ctx *h, const double *r, double *z) {
+// M^{-1} of the finest level's FP32 right-hand side (mp.b), left where the
+// cycle ends: mp.x or mp.t, the same one every time
+const float *precondition_f32(amg_ctx *h) {
     Level &L = h->lv[0];
-    const int64_t nv = 3 * static_cast<int64_t>(L.n);
-    launch_to_f32(r, L.mp.b.p, nv, h->stream);
     const int cyc = std::max(1, h->prm.cycles);
     float *x = L.mp.x.p;
     for (int k = 0; k < cyc; ++k) x = cycle_mp(h, 0, L.mp.b.p, x, k == 0, false);
-    launch_to_f64(x, z, nv, h->stream);
+    return x;
+}
+
+void precondition_mp(amg_ctx *h, const double *r, double *z) {
+    const int64_t nv = 3 * static_cast<int64_t>(h->lv[0].n);
+    launch_to_f32(r, h->lv[0].mp.b.p, nv, h->stream);
+    launch_to_f64(precondition_f32(h), z, nv, h->stream);
 }
 
 }  // namespace amgp2
