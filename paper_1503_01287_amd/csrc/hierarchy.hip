@@ -256,7 +256,7 @@ void SweepData::build(const std::vector<int> &cp, const std::vector<int> &rowid,
     }
     places = bs[nc];
     for (int t = 0; t < SWEEP_TILE_SIZES; ++t) {
-        const int tr = (SWEEP_THREADS / 64) << t;
+        const int tr = (SWEEP_THREADS_MIN / 64) << t;
         int at = 0;
         for (int c = 0; c <= nc; ++c) {
             tp.push_back(at);
@@ -273,7 +273,7 @@ void SweepData::build(const std::vector<int> &cp, const std::vector<int> &rowid,
 
 void SweepData::fill(SweepArgs &a, const SweepShape &q, const SweepBuf &buf) const {
     int t = 0;
-    while (t < SWEEP_TILE_SIZES && (SWEEP_THREADS / 64) << t != q.tile_rows()) ++t;
+    while (t < SWEEP_TILE_SIZES && (SWEEP_THREADS_MIN / 64) << t != q.tile_rows()) ++t;
     AMG_REQUIRE(t < SWEEP_TILE_SIZES && buf.ctl.n > 0, AMG_EINVAL, "sweep: bad tile size or no buffers");
     a.ncolors = ncolors;
     a.ntiles = ntiles[t];
@@ -294,11 +294,21 @@ void SweepData::fill(SweepArgs &a, const SweepShape &q, const SweepBuf &buf) con
 // (32), 32^3 level 0 FP32 141 (16) / 147 (32). Workgroups: enough for five
 // colours, since those further ahead only poll (16^3 level 1 BF16: 60 us with
 // 5 colours' worth, 64 with 3, 70 with 256 workgroups), at most one to a CU.
+// Threads: half as many, two workgroups to a CU, where a colour is few tiles:
+// a tile's rows then wait for fewer others at its end; but tickets cost 13 ns
+// each, one after the other (1024 / 512 threads, tiles of 1024 a colour:
+// elasticity 16^3 level 1 BF16, 6, 60 / 54; 9^3 level 0 FP64, 15, 41 / 33; 21^3
+// level 1 FP64, 25, 77 / 66; 24^3 level 1 FP64, 33, 85 / 86; 16^3 level 0 FP32,
+// 40, 43 / 49; 32^3 level 1 BF16, 68, 73 / 89; 21^3 level 0 FP64, 87 / 95).
 SweepShape sweep_shape(int64_t nnz, int nrows, int ncolors, bool fp64_blocks) {
     SweepShape q;
     q.G = std::max(8, lanes_for(fp64_blocks ? nnz : nnz / 2, nrows));
-    const int per_colour = nrows / std::max(1, ncolors) / q.tile_rows() + 1;
-    q.grid = std::min(256, std::max(24, 5 * per_colour));
+    int per_colour = nrows / std::max(1, ncolors) / q.tile_rows() + 1;
+    if (per_colour <= 28) {
+        q.threads = SWEEP_THREADS_MIN;
+        per_colour = nrows / std::max(1, ncolors) / q.tile_rows() + 1;
+    }
+    q.grid = std::min(256 * 2 * SWEEP_THREADS_MIN / q.threads, std::max(24, 5 * per_colour));
     return q;
 }
 

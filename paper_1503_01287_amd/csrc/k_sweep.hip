@@ -41,7 +41,6 @@ namespace amgp2 {
 
 namespace {
 
-constexpr int NT = SWEEP_THREADS;
 constexpr unsigned SPIN_MAX = 1u << 21;  // a second or two of polls
 
 template <int KIND>
@@ -135,7 +134,7 @@ __device__ __forceinline__ void accumulate(const V *e, const V *x, V *s) {
 
 }  // namespace
 
-template <int MODE, int KIND, int G>
+template <int MODE, int KIND, int G, int NT>
 __global__ void __launch_bounds__(NT, 4) k_sweep(const SweepArgs a) {
     using V = typename ValueType<KIND>::V;
     constexpr int NV = MODE == SWEEP_SCALAR1 ? 1 : 3;   // components
@@ -442,28 +441,31 @@ void launch_split_rows(int np, int nrows, const int *order, const int *place, co
 }
 
 template <int MODE, int KIND, int G>
-static void launch_g(const SweepArgs &a, int grid, int later_rows, hipStream_t s) {
+static void launch_g(const SweepArgs &a, const SweepShape &q, int later_rows, hipStream_t s) {
+    const int grid = a.ntiles < q.grid ? a.ntiles : q.grid;
     if (later_rows > 0)
         k_later<MODE, KIND, G><<<ceil_div(static_cast<int64_t>(later_rows) * G, 256), 256, 0, s>>>(a, later_rows);
+    else if (q.threads == SWEEP_THREADS_MIN)
+        k_sweep<MODE, KIND, G, SWEEP_THREADS_MIN><<<grid, SWEEP_THREADS_MIN, 0, s>>>(a);
     else
-        k_sweep<MODE, KIND, G><<<grid, NT, 0, s>>>(a);
+        k_sweep<MODE, KIND, G, 2 * SWEEP_THREADS_MIN><<<grid, 2 * SWEEP_THREADS_MIN, 0, s>>>(a);
     AMG_CHECK_LAUNCH();
 }
 
 template <int MODE, int KIND>
-static void launch_k(int G, const SweepArgs &a, int grid, int later_rows, hipStream_t s) {
-    switch (G) {
-        case 8: launch_g<MODE, KIND, 8>(a, grid, later_rows, s); break;
-        case 16: launch_g<MODE, KIND, 16>(a, grid, later_rows, s); break;
-        case 32: launch_g<MODE, KIND, 32>(a, grid, later_rows, s); break;
-        case 64: launch_g<MODE, KIND, 64>(a, grid, later_rows, s); break;
+static void launch_k(const SweepArgs &a, const SweepShape &q, int later_rows, hipStream_t s) {
+    switch (q.G) {
+        case 8: launch_g<MODE, KIND, 8>(a, q, later_rows, s); break;
+        case 16: launch_g<MODE, KIND, 16>(a, q, later_rows, s); break;
+        case 32: launch_g<MODE, KIND, 32>(a, q, later_rows, s); break;
+        case 64: launch_g<MODE, KIND, 64>(a, q, later_rows, s); break;
         default: throw Error(AMG_EINVAL, "sweep kernel: 8, 16, 32 or 64 lanes per row");
     }
 }
 
-static void launch_any(int mode, int kind, int G, const SweepArgs &a, int grid, int later_rows, hipStream_t s) {
+static void launch_any(int mode, int kind, const SweepShape &q, const SweepArgs &a, int later_rows, hipStream_t s) {
 #define AMG_SWEEP_CASE(M, K) \
-    if (mode == M && kind == K) return launch_k<M, K>(G, a, grid, later_rows, s);
+    if (mode == M && kind == K) return launch_k<M, K>(a, q, later_rows, s);
     AMG_SWEEP_CASE(SWEEP_BLOCK, SWEEP_F64)
     AMG_SWEEP_CASE(SWEEP_BLOCK, SWEEP_F32)
     AMG_SWEEP_CASE(SWEEP_BLOCK, SWEEP_BF16)
@@ -481,11 +483,11 @@ void launch_sweep(int mode, int kind, const SweepShape &q, const SweepArgs &a, h
     AMG_REQUIRE(a.ncolors >= 1 && a.ncolors <= SWEEP_MAX_COLOURS, AMG_EINVAL, "sweep kernel: too many colours");
     AMG_REQUIRE(a.x_zero || a.x_old != a.x, AMG_EINVAL, "sweep kernel: the old iterate needs a buffer of its own");
     AMG_REQUIRE(a.forward || (!a.x_zero && !a.part), AMG_EINVAL, "sweep kernel: forward from zero or with a residual");
-    launch_any(mode, kind, q.G, a, a.ntiles < q.grid ? a.ntiles : q.grid, 0, s);
+    launch_any(mode, kind, q, a, 0, s);
 }
 
 void launch_later(int mode, int kind, int nrows, const SweepShape &q, const SweepArgs &a, hipStream_t s) {
-    if (nrows > 0) launch_any(mode, kind, q.G, a, 0, nrows, s);
+    if (nrows > 0) launch_any(mode, kind, q, a, nrows, s);
 }
 
 }  // namespace amgp2

@@ -12,7 +12,7 @@ namespace amgp2 {
 enum SweepMode : int { SWEEP_BLOCK = 3, SWEEP_SCALAR3 = 1, SWEEP_SCALAR1 = 0 };
 enum SweepKind : int { SWEEP_F64 = 0, SWEEP_F32 = 1, SWEEP_BF16 = 2 };
 
-constexpr int SWEEP_THREADS = 1024;    // threads of a workgroup
+constexpr int SWEEP_THREADS_MIN = 512;  // threads of a workgroup: these, or twice as many
 constexpr int SWEEP_MAX_COLOURS = 1023;
 constexpr int SWEEP_PAD = 32;         // a colour's range of the swept vector starts at a multiple of this many nodes
 // control words of a level's sweeps: ticket, exits, buffer in turn, given up
@@ -44,12 +44,12 @@ struct SweepArgs {
     int *ctl = nullptr;             // SWEEP_CTL_INTS words of this level, zero before the first launch
 };
 
-// G lanes per row (8, 16, 32, 64), at most `grid` workgroups
+// G lanes per row (8, 16, 32, 64), at most `grid` workgroups of `threads`
 struct SweepShape {
-    int G = 16, grid = 256;
-    int tile_rows() const { return SWEEP_THREADS / G; }
+    int G = 16, grid = 256, threads = 2 * SWEEP_THREADS_MIN;
+    int tile_rows() const { return threads / G; }
 };
-constexpr int SWEEP_TILE_SIZES = 4;  // tiles of (SWEEP_THREADS / 64) << t rows
+constexpr int SWEEP_TILE_SIZES = 5;  // tiles of (SWEEP_THREADS_MIN / 64) << t rows
 
 // "absent" into both buffers of xg (n values in all, of the sweep's precision)
 void launch_sweep_absent(int kind, void *xg, int64_t n, hipStream_t s);
