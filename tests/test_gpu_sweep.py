@@ -81,6 +81,24 @@ def test_cycle(problem, n, smoother, nu, precision):
         one.smooth(0, r, t, k % 2 == 0)
 
 
+@pytest.mark.parametrize("precision", ["FP64", "FP32", "MIXED"])
+@pytest.mark.parametrize("problem,n", [("elasticity", 11), ("elasticity", 14), ("laplace", 17)])
+def test_both_workgroup_sizes(problem, n, precision):
+    """Finest levels of 20 to 60 tiles a colour, on either side of the change
+    from 512 to 1024 threads, with last tiles partly filled."""
+    sysm = MAKE[problem](n)
+    kw = dict(smoother="GS-1-1", precision=precision, krylov="FCG", autotune=False)
+    one, per = amg.AMGSolver(sysm, **kw), amg.AMGSolver(sysm, **kw)
+    by_colour(per, precision)
+    r = dev(np.random.default_rng(n).standard_normal(sysm.dofs))
+    z, w = torch.zeros_like(r), torch.zeros_like(r)
+    for _ in range(3):
+        one.precondition(r, z)
+        per.precondition(r, w)
+        assert relmax(z, w) < TOL[precision]
+        r = r.roll(1)
+
+
 @pytest.mark.parametrize("value", [float("nan"), float("inf")])
 @pytest.mark.parametrize("precision", ["FP64", "MIXED"])
 def test_bad_right_hand_side_ends(value, precision):
