@@ -431,6 +431,15 @@ int amg_get_level_info(amg_handle h, int32_t level, amg_level_info *info) {
         info->trip_gs = h->mixed ? L.mp.tripg : L.tripg;
         info->lanes64_A = L.G;
         info->trip64_A = L.trip;
+        // (the kernels that run: an operator in tiles has a shape of its own)
+        if (L.tiles.v64.n > 0 && !L.by_rows) {
+            info->lanes64_A = TILE_LANES;
+            info->trip64_A = TILE_TRIP;
+        }
+        if (h->mixed ? L.tiles.v32.n > 0 && !L.mp.by_rows : L.tiles.v64.n > 0 && !L.by_rows) {
+            info->lanes_A = TILE_LANES;
+            info->trip_A = TILE_TRIP;
+        }
         const int fs = h->dense_start >= 0 ? h->dense_start
                                              : h->saddle_tail_from;
         info->fused = (fs >= 0 && level >= fs) ? 1 : 0;

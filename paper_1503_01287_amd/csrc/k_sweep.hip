@@ -29,10 +29,10 @@
 // is smaller than the chip, the tiles' loads where it is larger. us per sweep
 // (mean of one from zero and one from an iterate), one launch per colour ->
 // this kernel, elasticity:
-//   16^3 level 0 (35,937 rows, 14 colours)  FP64  92 -> 52   FP32  81 -> 45
-//   16^3 level 1 ( 5,217 rows, 29 colours)  FP64 178 -> 73   BF16 173 -> 62
-//   32^3 level 0 (274,625 rows)             FP64 217 -> 248  FP32 147 -> 147
-//   32^3 level 1 ( 39,233 rows)             FP64 200 -> 108  BF16 156 -> 73
+//   16^3 level 0 (35,937 rows, 14 colours)  FP64  92 -> 48   FP32  81 -> 43
+//   16^3 level 1 ( 5,217 rows, 29 colours)  FP64 178 -> 58   BF16 173 -> 54
+//   32^3 level 0 (274,625 rows)             FP64 217 -> 236  FP32 147 -> 149
+//   32^3 level 1 ( 39,233 rows)             FP64 200 -> 101  BF16 156 -> 70
 // (with `part`, which saves half of the residual's pass after the sweep).
 #include "common.h"
 #include "sweep.h"
@@ -88,12 +88,12 @@ __device__ __forceinline__ double absent_value(double) { return __longlong_as_do
 // buffer's descriptor covers one half of xg)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int AUX_SC1 = 16;  // the scope bit of device-scope accesses
-template <int NV>
+template <int NV, int AUX = AUX_SC1>
 __device__ __forceinline__ void gather(__amdgpu_buffer_rsrc_t xg, int j, float *v) {
     if constexpr (NV == 1) {
-        v[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xg, 4 * j, 0, AUX_SC1));
+        v[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xg, 4 * j, 0, AUX));
     } else {
-        const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(xg, 16 * j, 0, AUX_SC1);
+        const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(xg, 16 * j, 0, AUX);
         v[0] = __uint_as_float(q.x);
         v[1] = __uint_as_float(q.y);
         v[2] = __uint_as_float(q.z);
@@ -102,15 +102,15 @@ __device__ __forceinline__ void gather(__amdgpu_buffer_rsrc_t xg, int j, float *
 __device__ __forceinline__ double from_words(uint32_t lo, uint32_t hi) {
     return __longlong_as_double(static_cast<long long>(static_cast<uint64_t>(hi) << 32 | lo));
 }
-template <int NV>
+template <int NV, int AUX = AUX_SC1>
 __device__ __forceinline__ void gather(__amdgpu_buffer_rsrc_t xg, int j, double *v) {
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     if constexpr (NV == 1) {
-        const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(xg, 8 * j, 0, AUX_SC1);
+        const u32x2 q = __builtin_amdgcn_raw_buffer_load_b64(xg, 8 * j, 0, AUX);
         v[0] = from_words(q.x, q.y);
     } else {
-        const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(xg, 32 * j, 0, AUX_SC1);
-        const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(xg, 32 * j + 16, 0, AUX_SC1);
+        const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(xg, 32 * j, 0, AUX);
+        const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(xg, 32 * j + 16, 0, AUX);
         v[0] = from_words(q.x, q.y);
         v[1] = from_words(q.z, q.w);
         v[2] = from_words(w.x, w.y);
@@ -264,22 +264,45 @@ __global__ void __launch_bounds__(NT, 4) k_sweep(const SweepArgs a) {
                     }
                 }
             }
+            // Most neighbours were swept a while ago: an ordinary load finds
+            // them, in the L2 for its XCD's other rows (device-scope loads
+            // pass by it: 21^3 level 0 FP64 87 -> 81 us, 32^3 level 1 BF16
+            // 73 -> 70). Never an earlier sweep's: the launch before this one
+            // filled the buffer with "absent". The others are waited for at
+            // device scope.
             V xv[U][NV];
-            bool there = false;
+            bool got[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (jn[u] >= 0) gather<NV, 0>(xgr, jn[u], xv[u]);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                got[u] = true;
+                if (jn[u] >= 0) {
+#pragma unroll
+                    for (int p = 0; p < NV; ++p) got[u] = got[u] && !absent(xv[u][p]);
+                }
+            }
             unsigned n = 0;
             for (;;) {
+                bool there = true;
+#pragma unroll
+                for (int u = 0; u < U; ++u) there = there && got[u];
                 if (!there) {
                     asm volatile("" ::: "memory");  // a new load every time
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (!got[u]) gather<NV>(xgr, jn[u], xv[u]);
                     there = true;
 #pragma unroll
-                    for (int u = 0; u < U; ++u)
-                        if (jn[u] >= 0) gather<NV>(xgr, jn[u], xv[u]);
+                    for (int u = 0; u < U; ++u) {
+                        if (!got[u]) {
+                            got[u] = true;
 #pragma unroll
-                    for (int u = 0; u < U; ++u)
-                        if (jn[u] >= 0) {
-#pragma unroll
-                            for (int p = 0; p < NV; ++p) there = there && !absent(xv[u][p]);
+                            for (int p = 0; p < NV; ++p) got[u] = got[u] && !absent(xv[u][p]);
                         }
+                        there = there && got[u];
+                    }
                 }
                 if (__all(there)) break;
                 if (bad) break;

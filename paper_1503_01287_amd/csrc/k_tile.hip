@@ -35,12 +35,12 @@ __device__ __forceinline__ T once(const T *p) {
 }
 
 // Lane h of a row takes its entries h, h + 2, ..., four sums each (entry k in
-// the sums k mod 8 of the row), U = 4 entries a trip with the next trip's
+// the sums k mod 8 of the row), U entries a trip with the next trip's
 // loads in flight.
 template <int KIND, int OP, bool STREAM>
 __global__ void __launch_bounds__(NT) k_tile(const TileArgs a) {
     using X = typename TileType<KIND>::T;
-    constexpr int U = 4;
+    constexpr int U = TILE_TRIP;
     extern __shared__ __align__(16) unsigned char smem[];
     X *xs = reinterpret_cast<X *>(smem);
     // XCD k (every eighth workgroup) takes the k-th eighth of the tiles, so

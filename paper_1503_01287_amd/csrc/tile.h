@@ -12,8 +12,9 @@ namespace amgp2 {
 
 constexpr int TILE_ROWS = 256;
 constexpr int TILE_LANES = 2;     // lanes per row
+constexpr int TILE_TRIP = 4;      // entries per lane and trip
 constexpr int TILE_SLICE = 64 / TILE_LANES;  // rows whose entries are stored step by step
-constexpr int TILE_AHEAD = 4 * 64;  // places that are read past the last entry's (never used)
+constexpr int TILE_AHEAD = TILE_TRIP * 64;  // places that are read past the last entry's (never used)
 constexpr int TILE_LIST = 2048;   // most nodes of x that a tile may read
 
 enum TileKind : int { TILE_F64 = 0, TILE_F32 = 1 };
