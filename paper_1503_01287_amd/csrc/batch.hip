@@ -1036,38 +1036,38 @@ int solve_pcg_batched(amg_ctx *h, const double *b, double *x, double tol, int ma
     hipStream_t s = h->stream;
     const ChunkView t = h->b_chunks.view();
     double *r = h->kr.p, *z = h->kz.p, *pv = h->kp.p, *q = h->kq.p;
-    DevBuf<double> partial(static_cast<size_t>(2) * std::max(1, t.n)), hb(static_cast<size_t>(2) * ns), da(ns),
-        dm(ns), dbeta(ns), dones(ns);
-    std::vector<double> hv(static_cast<size_t>(2) * ns), r0(ns), rz(ns), alpha(ns, 0.0), malpha(ns, 0.0),
-        beta(ns, 0.0), ones(ns, 1.0), pq(ns);
+    DevBuf<double> partial(static_cast<size_t>(2) * std::max(1, t.n));
+    // Dots and step lengths live in pinned host memory that the kernels write
+    // and read themselves: a copy each way cost some 10 us of the stream's
+    // time, five of them per iteration. Each array is written by one side
+    // only after a synchronisation past the other's last access.
+    const size_t npin = static_cast<size_t>(4) * ns;
+    if (h->sg_pin_n < npin) {
+        if (h->sg_pin) AMG_HIP(hipHostFree(h->sg_pin));
+        h->sg_pin = nullptr;
+        h->sg_pin_n = 0;
+        AMG_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->sg_pin), npin * sizeof(double), hipHostMallocCoherent));
+        h->sg_pin_n = npin;
+    }
+    double *hv = h->sg_pin, *alpha = hv + 2 * ns, *beta = hv + 3 * ns;
+    std::vector<double> r0(ns), rz(ns), pq(ns);
     std::vector<int> status(ns, AMG_NOT_CONVERGED), iters(ns, 0);
     std::vector<char> active(ns, 0);
-    // k = 1: <a, c> per system; k = 2: <a, a> and <a, c>
-    auto dots = [&](const double *a, const double *c, int k) {
-        if (k == 1)
-            launch_seg_multidot(a, 0, 1, c, t, partial.p, s);
-        else
-            launch_seg_multidot2(a, 0, 1, a, c, t, partial.p, s);
-        launch_seg_reduce(partial.p, t.n, k, ns, h->b_c0.p, h->b_c1.p, h->b_c2.p, h->b_c3.p, hb.p, k, s);
-        AMG_HIP(hipMemcpyAsync(hv.data(), hb.p, static_cast<size_t>(k) * ns * sizeof(double), hipMemcpyDeviceToHost,
-                               s));
+    // hv[i * k + j] = the sums of partial's rows j < k, waited for
+    auto reduce = [&](int k, double *out) {
+        launch_seg_reduce(partial.p, t.n, k, ns, h->b_c0.p, h->b_c1.p, h->b_c2.p, h->b_c3.p, out, k, s);
+    };
+    auto read = [&](int k) {
+        reduce(k, hv);
         AMG_HIP(hipStreamSynchronize(s));
     };
-    // <v, a> and <v, c> per system
-    auto dots_pair = [&](const double *v, const double *a, const double *c) {
-        launch_seg_multidot2(v, 0, 1, a, c, t, partial.p, s);
-        launch_seg_reduce(partial.p, t.n, 2, ns, h->b_c0.p, h->b_c1.p, h->b_c2.p, h->b_c3.p, hb.p, 2, s);
-        AMG_HIP(hipMemcpyAsync(hv.data(), hb.p, 2 * static_cast<size_t>(ns) * sizeof(double), hipMemcpyDeviceToHost,
-                               s));
-        AMG_HIP(hipStreamSynchronize(s));
-    };
-    auto put = [&](DevBuf<double> &d, const std::vector<double> &v) {
-        AMG_HIP(hipMemcpyAsync(d.p, v.data(), ns * sizeof(double), hipMemcpyHostToDevice, s));
+    auto dots = [&](const double *a, const double *c) {  // <a, c> per system
+        launch_seg_multidot(a, 0, 1, c, t, partial.p, s);
+        read(1);
     };
     auto any_active = [&] { return std::any_of(active.begin(), active.end(), [](char c) { return c != 0; }); };
-    put(dones, ones);
     system_residual(h, b, x, r);
-    dots(r, r, 1);
+    dots(r, r);
     for (int i = 0; i < ns; ++i) {
         r0[i] = std::sqrt(hv[i]);
         if (!(r0[i] == r0[i])) status[i] = AMG_DIVERGED;
@@ -1080,22 +1080,19 @@ int solve_pcg_batched(amg_ctx *h, const double *b, double *x, double tol, int ma
     // the stopping test's read, and <z, q_prev> comes back in that read
     double relmin = 1.0;
     bool ahead = false;
-    std::vector<double> zq(ns);
     for (int it = 0; flexible && any_active() && it < maxit; ++it) {
         if (!ahead) precondition(h, r, z);
         if (it == 0) {
             launch_copy(pv, z, n, s);
         } else {
-            if (ahead)
-                std::copy(zq.begin(), zq.end(), hv.begin());
-            else
-                dots(z, q, 1);  // <z, q_prev>
-            for (int i = 0; i < ns; ++i) beta[i] = active[i] && pq[i] > 0.0 ? -hv[i] / pq[i] : 0.0;
-            put(dbeta, beta);
-            launch_seg_axpby(z, pv, dones.p, dbeta.p, t, s);  // p = z + beta p
+            if (!ahead) dots(z, q);  // <z, q_prev>
+            const double *zq = ahead ? hv + ns : hv;
+            for (int i = 0; i < ns; ++i) beta[i] = active[i] && pq[i] > 0.0 ? -zq[i] / pq[i] : 0.0;
+            launch_seg_cg_direction(z, beta, pv, t, s);
         }
         apply_level(h, 0, pv, q);
-        dots_pair(pv, q, r);  // <p, q>, <p, r>
+        launch_seg_multidot2(pv, 0, 1, q, r, t, partial.p, s);  // <p, q>, <p, r>
+        read(2);
         for (int i = 0; i < ns; ++i) {
             pq[i] = hv[2 * i];
             alpha[i] = 0.0;
@@ -1108,25 +1105,17 @@ int solve_pcg_batched(amg_ctx *h, const double *b, double *x, double tol, int ma
             alpha[i] = hv[2 * i + 1] / pq[i];
             ++iters[i];
         }
-        for (int i = 0; i < ns; ++i) malpha[i] = -alpha[i];
-        put(da, alpha);
-        put(dm, malpha);
-        launch_seg_axpby(pv, x, da.p, dones.p, t, s);  // x += alpha p
-        launch_seg_axpby(q, r, dm.p, dones.p, t, s);   // r -= alpha q
+        launch_seg_cg_update(pv, q, alpha, x, r, partial.p, t, s);
         ahead = it + 1 < maxit && relmin > KRYLOV_AHEAD * tol;
         if (ahead) {
-            // <r, r> into hb[0, ns), then z and <z, q> into hb[ns, 2 ns): one read
-            launch_seg_multidot(r, 0, 1, r, t, partial.p, s);
-            launch_seg_reduce(partial.p, t.n, 1, ns, h->b_c0.p, h->b_c1.p, h->b_c2.p, h->b_c3.p, hb.p, 1, s);
+            // <r, r> into hv[0, ns), then z and <z, q> into hv[ns, 2 ns): one wait
+            reduce(1, hv);
             precondition(h, r, z);
             launch_seg_multidot(z, 0, 1, q, t, partial.p, s);
-            launch_seg_reduce(partial.p, t.n, 1, ns, h->b_c0.p, h->b_c1.p, h->b_c2.p, h->b_c3.p, hb.p + ns, 1, s);
-            AMG_HIP(hipMemcpyAsync(hv.data(), hb.p, 2 * static_cast<size_t>(ns) * sizeof(double),
-                                   hipMemcpyDeviceToHost, s));
+            reduce(1, hv + ns);
             AMG_HIP(hipStreamSynchronize(s));
-            std::copy(hv.begin() + ns, hv.begin() + 2 * ns, zq.begin());
         } else {
-            dots(r, r, 1);
+            read(1);  // <r, r>
         }
         relmin = 1e300;
         for (int i = 0; i < ns; ++i) {
@@ -1146,13 +1135,13 @@ int solve_pcg_batched(amg_ctx *h, const double *b, double *x, double tol, int ma
     if (!flexible && any_active()) {
         precondition(h, r, z);
         launch_copy(pv, z, n, s);
-        dots(r, z, 1);
+        dots(r, z);
         for (int i = 0; i < ns; ++i) rz[i] = hv[i];
     }
     int it = 0;
     while (!flexible && any_active() && it < maxit) {
         apply_level(h, 0, pv, q);
-        dots(pv, q, 1);
+        dots(pv, q);
         for (int i = 0; i < ns; ++i) {
             pq[i] = hv[i];
             alpha[i] = 0.0;
@@ -1165,14 +1154,11 @@ int solve_pcg_batched(amg_ctx *h, const double *b, double *x, double tol, int ma
             alpha[i] = rz[i] / pq[i];
             ++iters[i];
         }
-        for (int i = 0; i < ns; ++i) malpha[i] = -alpha[i];
-        put(da, alpha);
-        put(dm, malpha);
-        launch_seg_axpby(pv, x, da.p, dones.p, t, s);  // x += alpha p
-        launch_seg_axpby(q, r, dm.p, dones.p, t, s);   // r -= alpha q
+        launch_seg_cg_update(pv, q, alpha, x, r, partial.p, t, s);
         ++it;
         precondition(h, r, z);
-        dots(r, z, 2);
+        launch_seg_multidot(r, 0, 1, z, t, partial.p + t.n, s);
+        read(2);  // <r, r>, <r, z>
         for (int i = 0; i < ns; ++i) {
             beta[i] = 0.0;
             if (!active[i]) continue;
@@ -1188,12 +1174,11 @@ int solve_pcg_batched(amg_ctx *h, const double *b, double *x, double tol, int ma
                 rz[i] = hv[2 * i + 1];
             }
         }
-        put(dbeta, beta);
-        launch_seg_axpby(z, pv, dones.p, dbeta.p, t, s);  // p = z + beta p
+        launch_seg_cg_direction(z, beta, pv, t, s);
     }
     // the true residual of every system
     system_residual(h, b, x, h->kw.p);
-    dots(h->kw.p, h->kw.p, 1);
+    dots(h->kw.p, h->kw.p);
     const double ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     int worst = AMG_OK;
     for (int j = 0; j < ns; ++j) {

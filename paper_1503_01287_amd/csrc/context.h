@@ -380,6 +380,9 @@ struct amg_ctx {
     // that the next step's preconditioner can be enqueued before the wait)
     double *gm_hpin = nullptr;
     size_t gm_hpin_n = 0;
+    // a batch's CG: pinned dots and step lengths of its systems
+    double *sg_pin = nullptr;
+    size_t sg_pin_n = 0;
     // batch of independent saddle systems merged level by level (nsys > 0):
     // merged position q holds caller system b_order[q]; systems are ordered
     // by decreasing depth so that those still coarsening on a level lead it
