@@ -328,7 +328,7 @@ struct ProfStat {
 
 struct amg_ctx_impl;
 
-enum GraphKind : int { GRAPH_PRECONDITION = 0, GRAPH_CG_STEP, GRAPH_CG_NEXT, GRAPH_CG_CYCLE };
+enum GraphKind : int { GRAPH_PRECONDITION = 0, GRAPH_CG_STEP, GRAPH_CG_NEXT, GRAPH_CYCLE_F32 };
 
 }  // namespace amgp2
 
@@ -409,7 +409,7 @@ struct amg_ctx {
     amgp2::MultiWork multi;  // amg_solve_multi
     amgp2::DevBuf<double> partial, sc;
     double *h_sc = nullptr;  // pinned host copy of the scalars
-    const float *cg_z = nullptr;    // where CG's reduced-precision cycle leaves z
+    const float *cg_z = nullptr;    // where the reduced-precision cycle leaves z
     hipEvent_t sc_ready = nullptr;  // that copy has landed (overlapped stopping tests)
     int n_dof = 0;           // length of a solve vector
     // profiling
@@ -483,6 +483,8 @@ void group_schur_rows(SchurLevel &q, hipStream_t s);
 // FP32 copy of the assembled coarse-end operator (reduced-precision cycle)
 void refresh_tail_f32(amg_ctx *h);
 void saddle_precondition(amg_ctx *h, const double *r, double *z);
+// the reduced-precision cycle from mp.b of the finest level; the buffer it ends in
+const float *saddle_precondition_f32(amg_ctx *h);
 void system_matvec(amg_ctx *h, const double *x, double *y);
 void system_residual(amg_ctx *h, const double *b, const double *x, double *r);
 int solve_fgmres(amg_ctx *h, const double *b, double *x, double tol, int maxit, amg_result *res);

@@ -638,18 +638,23 @@ static void saddle_cycle(amg_ctx *h, int l, const T *b, T *x, bool x_zero) {
     for (int k = 0; k < p.post; ++k) saddle_step<T>(h, l, b, x, false);
 }
 
+const float *saddle_precondition_f32(amg_ctx *h) {
+    Level &L0 = h->lv[0];
+    const int cyc = std::max(1, h->prm.cycles);
+    for (int k = 0; k < cyc; ++k) saddle_cycle<float>(h, 0, L0.mp.b.p, L0.mp.x.p, k == 0);
+    return L0.mp.x.p;
+}
+
 // z = M^{-1} r (FP64 vectors). The reduced-precision cycle converts r to
 // FP32 on the finest level and z back to FP64; the outer FGMRES stays FP64.
 void saddle_precondition(amg_ctx *h, const double *r, double *z) {
-    const int cyc = std::max(1, h->prm.cycles);
     if (h->mixed) {
         Level &L0 = h->lv[0];
-        const int64_t n = L0.vlen();
-        launch_to_f32(r, L0.mp.b.p, n, h->stream);
-        for (int k = 0; k < cyc; ++k) saddle_cycle<float>(h, 0, L0.mp.b.p, L0.mp.x.p, k == 0);
-        launch_to_f64(L0.mp.x.p, z, n, h->stream);
+        launch_to_f32(r, L0.mp.b.p, L0.vlen(), h->stream);
+        launch_to_f64(saddle_precondition_f32(h), z, L0.vlen(), h->stream);
         return;
     }
+    const int cyc = std::max(1, h->prm.cycles);
     for (int k = 0; k < cyc; ++k) saddle_cycle<double>(h, 0, r, z, k == 0);
 }
 
