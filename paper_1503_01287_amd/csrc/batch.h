@@ -38,7 +38,7 @@ void launch_seg_reduce(const double *partial, int n, int k, int nsys, const int 
 // system s's dots of launch_multidot2 over V_0..V_{j+1} at h + s * stride
 // (2 (j + 2) values) and its gamma, d, eta written after them
 void launch_seg_dcgs2_update(double *V, int64_t ld, int j, double *h, int stride, const ChunkView &t, bool reorth,
-                             hipStream_t s);
+                             float *w32, hipStream_t s);
 // y = coef[seg] * x
 void launch_seg_scale(const double *x, double *y, const double *coef, const ChunkView &t, hipStream_t s);
 // x += a[seg] p, r -= a[seg] q and partial[c] = <r, r> over chunk c

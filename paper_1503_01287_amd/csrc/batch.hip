@@ -812,6 +812,9 @@ int solve_fgmres_batched(amg_ctx *h, const double *b, double *x, double tol, int
         hb(static_cast<size_t>(ns) * stride), coef(ns), ycoef(static_cast<size_t>(ns) * m);
     DevBuf<int> cnt(ns), want(ns);
     double *V = h->gm_V.p, *Z = h->gm_Z.p;
+    // a reduced-precision cycle's right-hand side: written by the update for
+    // the steps after the first
+    float *w32 = h->mixed ? h->lv[0].mp.b.p : nullptr;
     // per system: H rotated columns (row-major q * m + c), Hr raw columns
     // (column c at c * (m + 1)), rotations, g, pending scales eta
     const size_t hsz = static_cast<size_t>(m + 1) * m;
@@ -896,14 +899,14 @@ int solve_fgmres_batched(amg_ctx *h, const double *b, double *x, double tol, int
         for (int j = 0; j < m && any(running) && it < maxit; ++j, ++it) {
             double *vj = V + static_cast<int64_t>(j) * n, *w = V + static_cast<int64_t>(j + 1) * n;
             double *zj = Z + static_cast<int64_t>(j) * n;
-            if (!ahead) precondition_any(h, vj, zj);
+            if (!ahead) precondition_step(h, vj, zj, j > 0);
             ahead = false;
             system_matvec(h, zj, w);
             const int k = j + 2;
             launch_seg_multidot2(V, n, k, vj, w, t, partial.p, h->stream);
             launch_seg_reduce(partial.p, t.n, 2 * k, ns, h->b_c0.p, h->b_c1.p, h->b_c2.p, h->b_c3.p, hb.p, stride,
                               h->stream);
-            launch_seg_dcgs2_update(V, n, j, hb.p, stride, t, j > 0, h->stream);
+            launch_seg_dcgs2_update(V, n, j, hb.p, stride, t, j > 0, w32, h->stream);
             AMG_HIP(hipMemcpyAsync(hp, hb.p, nh * sizeof(double), hipMemcpyDeviceToHost, h->stream));
             AMG_HIP(hipEventRecord(h->sc_ready, h->stream));
             // the pending vectors u_{j+1} are final for step j + 1: their
@@ -914,7 +917,7 @@ int solve_fgmres_batched(amg_ctx *h, const double *b, double *x, double tol, int
                 for (int i = 0; i < ns; ++i)
                     if (running[i]) emin = std::min(emin, estl[i]);
                 if (j + 1 < m && it + 1 < maxit && emin > KRYLOV_AHEAD * tol) {
-                    precondition_any(h, w, Z + static_cast<int64_t>(j + 1) * n);
+                    precondition_step(h, w, Z + static_cast<int64_t>(j + 1) * n, true);
                     ahead = true;
                 }
             }

@@ -496,7 +496,7 @@ void precondition_any(amg_ctx *h, const double *r, double *z);
 // tolerance at these convergence rates); the application only writes its
 // output, so a solve that stops there loses nothing but its GPU time.
 constexpr double KRYLOV_AHEAD = 50.0;
-void precondition_staged(amg_ctx *h, const double *r, double *z);
+void precondition_step(amg_ctx *h, const double *r, double *z, bool in_b32);
 // batches
 void build_batch(amg_ctx *h, int nsys, const amg_system *sys);
 // batches of SPD systems (every n_pres = 0): the merged FP64 hierarchy and

@@ -106,7 +106,7 @@ void launch_seg_multidot2(const double *V, int64_t ld, int k, const double *a, c
 // h + seg * stride.
 template <bool REORTH>
 __global__ void __launch_bounds__(CB) k_seg_dcgs2_update(double *V, int64_t ld, int j, double *h, int stride,
-                                                         const ChunkView t) {
+                                                         const ChunkView t, float *w32) {
     const int c = blockIdx.x;
     const int64_t s0 = t.start[c];
     const int len = t.len[c];
@@ -159,7 +159,9 @@ __global__ void __launch_bounds__(CB) k_seg_dcgs2_update(double *V, int64_t ld, 
             u = (u - as[e]) * ig;
             vj[i] = u;
         }
-        w[i] = (w[i] - ac[e] - d * u) * ie;
+        const double wi = (w[i] - ac[e] - d * u) * ie;
+        w[i] = wi;
+        if (w32) w32[s0 + i] = static_cast<float>(wi);
     }
     // every chunk of the system writes the same three values; the dots
     // read above lie below them
@@ -171,12 +173,12 @@ __global__ void __launch_bounds__(CB) k_seg_dcgs2_update(double *V, int64_t ld, 
 }
 
 void launch_seg_dcgs2_update(double *V, int64_t ld, int j, double *h, int stride, const ChunkView &t, bool reorth,
-                             hipStream_t s) {
+                             float *w32, hipStream_t s) {
     if (t.n <= 0) return;
     if (reorth)
-        k_seg_dcgs2_update<true><<<t.n, CB, 0, s>>>(V, ld, j, h, stride, t);
+        k_seg_dcgs2_update<true><<<t.n, CB, 0, s>>>(V, ld, j, h, stride, t, w32);
     else
-        k_seg_dcgs2_update<false><<<t.n, CB, 0, s>>>(V, ld, j, h, stride, t);
+        k_seg_dcgs2_update<false><<<t.n, CB, 0, s>>>(V, ld, j, h, stride, t, w32);
     AMG_CHECK_LAUNCH();
 }
 

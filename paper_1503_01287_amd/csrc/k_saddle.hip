@@ -675,9 +675,12 @@ void launch_multidot_reduce(const double *partial, int nb, int k, double *h, hip
 // eta = sqrt(w . w - |c|^2 - d^2) (Pythagoras; any positive scale serves,
 // as the next step measures the new pending vector exactly, so a
 // cancelled estimate falls back to 1e-2 |w|). gamma, d and eta are written
-// to h[2k], h[2k + 1], h[2k + 2].
+// to h[2k], h[2k + 1], h[2k + 2]. With w32 the pending vector goes there too,
+// in FP32: the next reduced-precision cycle starts from it without a pass
+// that reads it back.
 template <bool REORTH>
-__global__ void __launch_bounds__(SB) k_dcgs2_update(double *V, int64_t ld, int j, double *h, int64_t n) {
+__global__ void __launch_bounds__(SB) k_dcgs2_update(double *V, int64_t ld, int j, double *h, int64_t n,
+                                                     float *w32) {
     const int k = j + 2;
     const double *dA = h, *dB = h + k;
     double ss = 0.0, sc = 0.0, cc = 0.0;
@@ -713,7 +716,9 @@ __global__ void __launch_bounds__(SB) k_dcgs2_update(double *V, int64_t ld, int 
             u = (u - as) * ig;
             vj[t] = u;
         }
-        w[t] = (w[t] - ac - d * u) * ie;
+        const double wt = (w[t] - ac - d * u) * ie;
+        w[t] = wt;
+        if (w32) w32[t] = static_cast<float>(wt);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         h[2 * k] = gam;
@@ -722,12 +727,13 @@ __global__ void __launch_bounds__(SB) k_dcgs2_update(double *V, int64_t ld, int 
     }
 }
 
-void launch_dcgs2_update(double *V, int64_t ld, int j, double *h, int64_t n, bool reorth, hipStream_t s) {
+void launch_dcgs2_update(double *V, int64_t ld, int j, double *h, int64_t n, bool reorth, float *w32,
+                         hipStream_t s) {
     if (n <= 0) return;
     if (reorth)
-        k_dcgs2_update<true><<<grid_s(n), SB, 0, s>>>(V, ld, j, h, n);
+        k_dcgs2_update<true><<<grid_s(n), SB, 0, s>>>(V, ld, j, h, n, w32);
     else
-        k_dcgs2_update<false><<<grid_s(n), SB, 0, s>>>(V, ld, j, h, n);
+        k_dcgs2_update<false><<<grid_s(n), SB, 0, s>>>(V, ld, j, h, n, w32);
     AMG_CHECK_LAUNCH();
 }
 

@@ -139,8 +139,10 @@ void launch_multidot_reduce(const double *partial, int nb, int k, double *h, hip
 // Delayed reorthogonalisation step on basis slots j (pending vector) and
 // j + 1 (new vector) from the reduced dots h[0 .. 2(j + 2)) of
 // launch_multidot2(V, ld, j + 2, V_j, V_{j+1}); writes gamma, d, eta to
-// h[2(j + 2) ..] (see k_dcgs2_update)
-void launch_dcgs2_update(double *V, int64_t ld, int j, double *h, int64_t n, bool reorth, hipStream_t s);
+// h[2(j + 2) ..] and, if w32 is given, the new vector to it in FP32 (see
+// k_dcgs2_update)
+void launch_dcgs2_update(double *V, int64_t ld, int j, double *h, int64_t n, bool reorth, float *w32,
+                         hipStream_t s);
 // x += sum_i y[i] Z_i  (y on the device)
 void launch_multi_add(const double *Z, int64_t ld, int k, const double *y, double *x, int64_t n,
                       hipStream_t s);

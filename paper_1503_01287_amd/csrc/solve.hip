@@ -423,11 +423,12 @@ static void cycle_f32(amg_ctx *h) {
 // GMRES basis): through staging vectors so that one recording serves all
 // A reduced-precision cycle starts and ends in FP32 vectors of its own, so the
 // conversions stand outside its recording and no staging is needed: two
-// launches and two copies of a vector (4-12 us each) less.
-void precondition_staged(amg_ctx *h, const double *r, double *z) {
+// launches and two copies of a vector (4-12 us each) less. With in_b32 the
+// cycle's right-hand side mp.b holds r already.
+void precondition_step(amg_ctx *h, const double *r, double *z, bool in_b32) {
     if (h->mixed) {
         Level &L = h->lv[0];
-        launch_to_f32(r, L.mp.b.p, L.vlen(), h->stream);
+        if (!in_b32) launch_to_f32(r, L.mp.b.p, L.vlen(), h->stream);
         cycle_f32(h);
         launch_to_f64(h->cg_z, z, L.vlen(), h->stream);
         return;

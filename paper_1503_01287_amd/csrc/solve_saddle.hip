@@ -862,7 +862,7 @@ void system_residual(amg_ctx *h, const double *b, const double *x, double *r) {
     }
 }
 
-void precondition_any(amg_ctx *h, const double *r, double *z) { precondition_staged(h, r, z); }
+void precondition_any(amg_ctx *h, const double *r, double *z) { precondition_step(h, r, z, false); }
 
 // ---------------------------------------------------------------- FGMRES
 static double norm2(amg_ctx *h, const double *v) {
@@ -978,24 +978,27 @@ int solve_fgmres(amg_ctx *h, const double *b, double *x, double tol, int maxit, 
         bool stop = false;
         bool ahead = false;  // this step's preconditioner already enqueued
         double *hd = h->gm_h.p;
+        // a reduced-precision cycle's right-hand side: written by the update
+        // for the steps after the first
+        float *w32 = h->mixed ? h->lv[0].mp.b.p : nullptr;
         if (!h->sc_ready) AMG_HIP(hipEventCreateWithFlags(&h->sc_ready, hipEventDisableTiming));
         for (int j = 0; j < m && it + j < maxit && !stop; ++j) {
             double *vj = V + static_cast<int64_t>(j) * n, *w = V + static_cast<int64_t>(j + 1) * n;
             double *zj = Z + static_cast<int64_t>(j) * n;
-            if (!ahead) precondition_any(h, vj, zj);
+            if (!ahead) precondition_step(h, vj, zj, j > 0);
             ahead = false;
             system_matvec(h, zj, w);
             const int k = j + 2;
             int nb = launch_multidot2(V, n, k, vj, w, n, h->gm_part.p, h->stream);
             launch_multidot_reduce(h->gm_part.p, nb, 2 * k, hd, h->stream);
-            launch_dcgs2_update(V, n, j, hd, n, j > 0, h->stream);
+            launch_dcgs2_update(V, n, j, hd, n, j > 0, w32, h->stream);
             AMG_HIP(hipMemcpyAsync(hbuf, hd, (2 * k + 3) * sizeof(double), hipMemcpyDeviceToHost, h->stream));
             AMG_HIP(hipEventRecord(h->sc_ready, h->stream));
             // the pending vector u_{j+1} is final for step j + 1: its
             // preconditioner goes ahead of the host's wait while the last
             // estimate is far from the tolerance
             if (j + 1 < m && it + j + 1 < maxit && est_last > KRYLOV_AHEAD * tol) {
-                precondition_any(h, w, Z + static_cast<int64_t>(j + 1) * n);
+                precondition_step(h, w, Z + static_cast<int64_t>(j + 1) * n, true);
                 ahead = true;
             }
             AMG_HIP(hipEventSynchronize(h->sc_ready));
