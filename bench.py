@@ -207,7 +207,7 @@ CYCLE_OPS = ("gs", "resid", "jacobi", "jacobi0", "restrict", "prolong", "vanka",
 SINGLE_CLASSES = ("coarse", "dense_tail", "saddle_tail", "tail")
 
 
-SETUP_PHASES = ("upload", "coarsen", "galerkin", "omega_network", "drop_zeros", "smoother", "autotune", "coarsest",
+SETUP_PHASES = ("upload", "coarsen", "galerkin", "omega_network", "drop_zeros", "tiles", "smoother", "autotune", "coarsest",
                 "omega_bound", "schur", "schur_map", "vanka", "coarse_map", "reduced_copies", "saddle_map", "merge")
 
 

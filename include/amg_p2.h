@@ -222,7 +222,10 @@ typedef struct {
     int32_t lanes_A, lanes_gs;     /* lanes per row of the level's
                                       natural-order and colour-sweep kernels
                                       (of the reduced-precision copies when
-                                      precision is not FP64)                 */
+                                      precision is not FP64); a finest level
+                                      kept in tiles reports the tile kernel's
+                                      2 lanes and 4 entries per trip, and so
+                                      does lanes64_A                         */
     int32_t fused;                 /* 1 if a V-cycle reaching this level runs
                                       it inside the fused coarse kernel       */
     double omega;                  /* JA damping used on this level          */
@@ -472,8 +475,8 @@ int amg_profile_enable(amg_handle h, int32_t enable);
  * every stored entry and index once, every vector once).
  * Setup phases are always recorded (never cleared): "setup.<phase>" with
  * phase one of upload, coarsen (graphs, independent sets, interpolation;
- * host), galerkin (the Galerkin products), omega_network, drop_zeros,
- * smoother (diagonal inverses, colouring, colour-grouped copies, saddle
+ * host), galerkin (the Galerkin products), omega_network, drop_zeros, tiles
+ * (of a large scalar finest level), smoother (diagonal inverses, colouring, colour-grouped copies, saddle
  * scalings), autotune, coarsest (dense inverse), omega_bound, schur,
  * schur_map, vanka, coarse_map, reduced_copies, saddle_map, merge
  * (batches): calls and wall ms. A batch sets its systems up concurrently on
