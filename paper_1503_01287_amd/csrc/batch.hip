@@ -643,12 +643,7 @@ void build_batch_spd(amg_ctx *h, int nsys, const amg_system *sys) {
                 M.g_rowid.upload(rows, s);
                 M.d_cptr.upload(M.cptr, s);
                 if (M.Ag.nrows > 0) {
-                    M.sweep.build(M.cptr, rows, M.n, 4, s);
-                    M.sweep.rows.alloc(static_cast<size_t>(M.Ag.nrows));
-                    M.sweep.gcol.alloc(static_cast<size_t>(std::max<int64_t>(1, M.Ag.nnz)));
-                    launch_split_rows(M.A.np, M.Ag.nrows, M.g_rowid.p, M.sweep.place.p, M.A.rowptr.p, M.A.col.p,
-                                      M.A.val.p, M.A.nnz, M.Ag.rowptr.p, M.Ag.col.p, M.Ag.val.p, M.Ag.nnz,
-                                      M.sweep.rows.p, M.sweep.gcol.p, s);
+                    M.sweep.build(M.A, M.cptr, rows, M.g_rowid.p, M.n, 4, M.Ag, s);
                     M.shape = sweep_shape(M.Ag.nnz, M.Ag.nrows, ncol, M.mode == 3);
                     M.mp.shape = sweep_shape(M.Ag.nnz, M.Ag.nrows, ncol, false);
                 }

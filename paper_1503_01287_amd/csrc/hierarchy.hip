@@ -245,7 +245,8 @@ void SweepBuf::build(int kind, int64_t nodes, int stride, hipStream_t s) {
     launch_sweep_absent(kind, xg.p, 2 * half, s);
 }
 
-void SweepData::build(const std::vector<int> &cp, const std::vector<int> &rowid, int n, int stride, hipStream_t s) {
+void SweepData::build(const DMat &A, const std::vector<int> &cp, const std::vector<int> &rowid, const int *d_rowid,
+                      int n, int stride, DMat &Ag, hipStream_t s) {
     const int nc = static_cast<int>(cp.size()) - 1;
     ncolors = nc;
     std::vector<int> bs(nc + 1, 0), pl(std::max(1, n), -1), tp;
@@ -268,7 +269,14 @@ void SweepData::build(const std::vector<int> &cp, const std::vector<int> &rowid,
     cptr.upload(cp, s);
     base.upload(bs, s);
     tpre.upload(tp, s);
-    f64.build(SWEEP_F64, places, stride, s);
+    rows.alloc(static_cast<size_t>(Ag.nrows));
+    gcol.alloc(static_cast<size_t>(std::max<int64_t>(1, Ag.nnz)));
+    DevBuf<int> coupled(1);
+    coupled.zero(s);
+    launch_split_rows(A.np, Ag.nrows, d_rowid, place.p, base.p, nc, A.rowptr.p, A.col.p, A.val.p, A.nnz, Ag.rowptr.p,
+                      Ag.col.p, Ag.val.p, Ag.nnz, rows.p, gcol.p, coupled.p, s);
+    apart = coupled.download(s)[0] == 0;
+    if (usable()) f64.build(SWEEP_F64, places, stride, s);
 }
 
 void SweepData::fill(SweepArgs &a, const SweepShape &q, const SweepBuf &buf) const {
@@ -349,11 +357,7 @@ static void setup_smoother(amg_ctx *h, Level &L) {
     L.Ag.val.alloc(static_cast<size_t>(L.A.nnz) * L.A.np);
     L.g_rowid.upload(order, s);
     L.d_cptr.upload(L.cptr, s);
-    L.sweep.build(L.cptr, order, L.n, 4, s);
-    L.sweep.rows.alloc(static_cast<size_t>(L.n));
-    L.sweep.gcol.alloc(static_cast<size_t>(L.A.nnz));
-    launch_split_rows(L.A.np, L.n, L.g_rowid.p, L.sweep.place.p, L.A.rowptr.p, L.A.col.p, L.A.val.p, L.A.nnz,
-                      L.Ag.rowptr.p, L.Ag.col.p, L.Ag.val.p, L.Ag.nnz, L.sweep.rows.p, L.sweep.gcol.p, s);
+    L.sweep.build(L.A, L.cptr, order, L.g_rowid.p, L.n, 4, L.Ag, s);
     AMG_HIP(hipStreamSynchronize(s));
     L.Gg = L.G;
     L.shape = sweep_shape(L.Ag.nnz, L.Ag.nrows, ncol, L.mode == 3);
@@ -386,11 +390,7 @@ void group_schur_rows(SchurLevel &q, hipStream_t s) {
     q.Sg.rowptr.upload(grp, s);
     q.Sg.col.alloc(std::max<int64_t>(1, q.Sg.nnz));
     q.Sg.val.alloc(std::max<int64_t>(1, q.Sg.nnz));
-    q.sweep.build(q.cptr, order, q.S.nrows, 1, s);
-    q.sweep.rows.alloc(static_cast<size_t>(m));
-    q.sweep.gcol.alloc(static_cast<size_t>(std::max<int64_t>(1, q.Sg.nnz)));
-    launch_split_rows(1, m, q.rowid.p, q.sweep.place.p, q.S.rowptr.p, q.S.col.p, q.S.val.p, q.S.nnz, q.Sg.rowptr.p,
-                      q.Sg.col.p, q.Sg.val.p, q.Sg.nnz, q.sweep.rows.p, q.sweep.gcol.p, s);
+    q.sweep.build(q.S, q.cptr, order, q.rowid.p, q.S.nrows, 1, q.Sg, s);
     AMG_HIP(hipStreamSynchronize(s));
     q.shape = sweep_shape(q.Sg.nnz, m, static_cast<int>(q.cptr.size()) - 1, false);
 }

@@ -19,8 +19,9 @@
 // sweep uses the one that the control words name, fills the other with the
 // payload for the next sweep, and the last workgroup out turns them over.
 //
-// Progress: a row depends only on rows of smaller tickets, and a ticket is
-// taken by a running workgroup, so the smallest unfinished ticket never
+// Progress: a row depends only on rows of smaller tickets (setup makes sure
+// that no two rows of a colour are coupled), and a ticket is taken by a running
+// workgroup, so the smallest unfinished ticket never
 // waits, whatever part of the grid is resident. The wait is bounded all the
 // same; past the bound the row becomes NaN, which the Krylov loops report as
 // divergence.
@@ -424,16 +425,24 @@ void launch_sweep_absent(int kind, void *xg, int64_t n, hipStream_t s) {
 // entries (earlier colours, the diagonal, later colours) by the ballot's
 // prefix count, in their order.
 __global__ void __launch_bounds__(256) k_split_rows(int np, int nrows, const int *order, const int *place,
-                                                    const int *rowptr, const int *col, const double *val, int64_t nnz,
-                                                    const int *g_rowptr, int *g_col, double *g_val, int64_t g_nnz,
-                                                    int4 *rows, int *gcol) {
+                                                    const int *base, int ncolors, const int *rowptr, const int *col,
+                                                    const double *val, int64_t nnz, const int *g_rowptr, int *g_col,
+                                                    double *g_val, int64_t g_nnz, int4 *rows, int *gcol, int *coupled) {
     const int g = blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (g >= nrows) return;
     const int i = order[g], src = rowptr[i], end = rowptr[i + 1];
     const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     const int mine = place[i];
+    int c = 0, over = ncolors;  // the row's colour: the last one with base[c] <= mine
+    while (over - c > 1) {
+        const int mid = (c + over) >> 1;
+        if (base[mid] <= mine) c = mid;
+        else over = mid;
+    }
+    const int first = base[c], last = base[c + 1] - 1;
     int dst = g_rowptr[g], diag = dst;
+    bool bad = false;
     for (int cls = 0; cls < 3; ++cls) {
         if (cls == 1) diag = dst;
         for (int k0 = src; k0 < end; k0 += 64) {
@@ -441,6 +450,7 @@ __global__ void __launch_bounds__(256) k_split_rows(int np, int nrows, const int
             const int j = k < end ? col[k] : -1;
             const int pj = j >= 0 ? place[j] : 0;
             const bool take = j >= 0 && (j == i ? cls == 1 : (pj < mine ? cls == 0 : cls == 2));
+            bad |= j >= 0 && j != i && (pj < 0 || (pj >= first && pj <= last));
             const uint64_t mask = __ballot(take);
             if (take) {
                 const int at = dst + __popcll(mask & below);
@@ -450,16 +460,18 @@ __global__ void __launch_bounds__(256) k_split_rows(int np, int nrows, const int
             }
             dst += __popcll(mask);
         }
+        if (cls == 1) bad |= dst != diag + 1;
     }
+    if (bad) atomicOr(coupled, 1);
     if (lane == 0) rows[g] = make_int4(g_rowptr[g], diag, dst, i);
 }
 
-void launch_split_rows(int np, int nrows, const int *order, const int *place, const int *rowptr, const int *col,
-                       const double *val, int64_t nnz, const int *g_rowptr, int *g_col, double *g_val,
-                       int64_t g_nnz, int4 *rows, int *gcol, hipStream_t s) {
+void launch_split_rows(int np, int nrows, const int *order, const int *place, const int *base, int ncolors,
+                       const int *rowptr, const int *col, const double *val, int64_t nnz, const int *g_rowptr,
+                       int *g_col, double *g_val, int64_t g_nnz, int4 *rows, int *gcol, int *coupled, hipStream_t s) {
     if (nrows <= 0) return;
-    k_split_rows<<<ceil_div(nrows, 4), 256, 0, s>>>(np, nrows, order, place, rowptr, col, val, nnz, g_rowptr, g_col,
-                                                    g_val, g_nnz, rows, gcol);
+    k_split_rows<<<ceil_div(nrows, 4), 256, 0, s>>>(np, nrows, order, place, base, ncolors, rowptr, col, val, nnz,
+                                                    g_rowptr, g_col, g_val, g_nnz, rows, gcol, coupled);
     AMG_CHECK_LAUNCH();
 }
 

@@ -58,11 +58,13 @@ void launch_sweep(int mode, int kind, const SweepShape &q, const SweepArgs &a, h
 // after a forward sweep with the same arguments
 void launch_later(int mode, int kind, int nrows, const SweepShape &q, const SweepArgs &a, hipStream_t s);
 
-// place[i]: node i's place in xg. Rows order[g] gathered into the grouped
-// copy with their entries split as SweepArgs wants them (a stable partition
-// by the columns' places); rows, gcol written with it.
-void launch_split_rows(int np, int nrows, const int *order, const int *place, const int *rowptr, const int *col,
-                       const double *val, int64_t nnz, const int *g_rowptr, int *g_col, double *g_val,
-                       int64_t g_nnz, int4 *rows, int *gcol, hipStream_t s);
+// place[i]: node i's place in xg; base[c]: first place of colour c. Rows
+// order[g] gathered into the grouped copy with their entries split as
+// SweepArgs wants them (a stable partition by the columns' places); rows, gcol
+// written with it. coupled |= 1 where a row has an entry of its own colour
+// beside one diagonal, or of a node that is not swept.
+void launch_split_rows(int np, int nrows, const int *order, const int *place, const int *base, int ncolors,
+                       const int *rowptr, const int *col, const double *val, int64_t nnz, const int *g_rowptr,
+                       int *g_col, double *g_val, int64_t g_nnz, int4 *rows, int *gcol, int *coupled, hipStream_t s);
 
 }  // namespace amgp2
