@@ -100,6 +100,7 @@ struct SweepBuf {
 struct SweepData {
     int ncolors = 0;                   // 0: none
     int64_t places = 0;                // places in xg
+    int stride = 4;                    // values per place
     bool apart = false;                // no row is coupled with another of its colour
     DevBuf<int> place;                 // per node: its place in xg (-1: not swept)
     DevBuf<int> cptr, base;            // grouped rows of a colour; its first place in xg
@@ -110,14 +111,16 @@ struct SweepData {
     SweepBuf f64, f32;
     // tables of the colours cptr over the nodes rowid[0 .. cptr.back()) of n (on
     // the device d_rowid), those rows of A grouped into Ag (its sizes and row
-    // pointers given) and, if usable, the FP64 buffers; stride: values per place
+    // pointers given) and, if usable, the FP64 buffers
     void build(const DMat &A, const std::vector<int> &cptr, const std::vector<int> &rowid, const int *d_rowid, int n,
-               int stride, DMat &Ag, hipStream_t s);
+               int values, DMat &Ag, hipStream_t s);
     // A row waits for every coupled row of an earlier colour, so the rows of
     // one colour must not be coupled. The greedy colouring looks at a row's own
     // entries: with (i, j) stored and (j, i) not, i < j may share a colour.
     // Such levels run a launch per colour.
-    bool usable() const { return apart && ncolors > 0 && ncolors <= SWEEP_MAX_COLOURS; }
+    bool usable() const {
+        return apart && ncolors > 0 && ncolors <= SWEEP_MAX_COLOURS && sweep_half_fits(places, stride);
+    }
     void fill(SweepArgs &a, const SweepShape &q, const SweepBuf &buf) const;
 };
 

@@ -246,9 +246,10 @@ void SweepBuf::build(int kind, int64_t nodes, int stride, hipStream_t s) {
 }
 
 void SweepData::build(const DMat &A, const std::vector<int> &cp, const std::vector<int> &rowid, const int *d_rowid,
-                      int n, int stride, DMat &Ag, hipStream_t s) {
+                      int n, int values, DMat &Ag, hipStream_t s) {
     const int nc = static_cast<int>(cp.size()) - 1;
     ncolors = nc;
+    stride = values;
     std::vector<int> bs(nc + 1, 0), pl(std::max(1, n), -1), tp;
     for (int c = 0; c < nc; ++c) {
         const int rows = cp[c + 1] - cp[c];

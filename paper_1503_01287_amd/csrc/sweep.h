@@ -49,6 +49,12 @@ struct SweepShape {
     int G = 16, grid = 256, threads = 2 * SWEEP_THREADS_MIN;
     int tile_rows() const { return threads / G; }
 };
+// Swept values are read at 32-bit byte offsets through a buffer descriptor of
+// one half of xg: whether `places` of `stride` FP64 values stay below 2 GiB.
+// (Past it an offset wraps, and a load past the descriptor's size returns 0,
+// which is not "absent".)
+constexpr bool sweep_half_fits(int64_t places, int stride) { return places * stride * 8 < (int64_t(1) << 31); }
+
 constexpr int SWEEP_TILE_SIZES = 5;  // tiles of (SWEEP_THREADS_MIN / 64) << t rows
 
 // "absent" into both buffers of xg (n values in all, of the sweep's precision)
