@@ -351,7 +351,12 @@ __global__ void __launch_bounds__(NT, 4) k_sweep(const SweepArgs a) {
             }
         }
     }
-    // the last workgroup out readies the control words for the next sweep
+    // The last workgroup out readies the control words for the next sweep. A
+    // workgroup counts itself out when all its wavefronts are done: one that
+    // still waited could give up after the flag was cleared, and the next sweep
+    // would find it set. (A wavefront that gives up has read the flag back, so
+    // its store is done by then.)
+    __syncthreads();
     if (tid == 0 && atomicAdd(exits, 1) == static_cast<int>(gridDim.x) - 1) {
         agent_store(ticket, 0);
         agent_store(exits, 0);

@@ -738,7 +738,12 @@ __global__ void __launch_bounds__(64 * SWEEP_WAVES, 4) k_vanka_sweep(const Vanka
             // (part is written again only past the loop's barrier)
         }
     }
-    // the last workgroup out readies the control words for the next sweep
+    // The last workgroup out readies the control words for the next sweep. A
+    // workgroup counts itself out when all its wavefronts are done: one that
+    // still waited could give up after the flag was cleared, and the next sweep
+    // would find it set. (A wavefront that gives up has read the flag back, so
+    // its store is done by then.)
+    __syncthreads();
     if (tid == 0 && atomicAdd(exits, 1) == static_cast<int>(gridDim.x) - 1) {
         agent_store(ticket, 0);
         agent_store(exits, 0);
