@@ -343,8 +343,9 @@ int amg_get_level_colors(amg_handle h, int32_t level, int32_t *colors);
  * Jacobi, operator, the outer Krylov operator on level 0), AMG_SHAPE_SWEEP
  * the FP64 colour sweeps, AMG_SHAPE_NATURAL_RP / AMG_SHAPE_SWEEP_RP the same
  * kernels of the reduced-precision copies. (All colours of a sweep run in
- * one launch by default; a level whose sweep shape is set here runs one
- * launch of that shape per colour, followed by a natural-order residual.
+ * one launch where that is possible and faster, on all but the largest
+ * levels; a level whose sweep shape is set here runs one launch of that shape
+ * per colour, followed by a natural-order residual.
  * Likewise a large scalar finest level runs its natural-order kernels in
  * tiles of rows until their shape is set here.) lanes: lanes of the 64-wide
  * wavefront per row, one of 4, 8, 16, 32, 64. trip: entries per lane and

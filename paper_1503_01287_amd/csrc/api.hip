@@ -426,7 +426,7 @@ int amg_get_level_info(amg_handle h, int32_t level, amg_level_info *info) {
         info->n_colors = L.cptr.empty() ? 0 : static_cast<int>(L.cptr.size()) - 1;
         info->is_coarsest = L.coarsest ? 1 : 0;
         info->lanes_A = h->mixed ? L.mp.G : L.G;
-        const bool one = L.sweep.usable() && !(h->mixed ? L.mp.by_colour : L.by_colour);
+        const bool one = one_launch_sweeps(h, L, h->mixed);
         info->lanes_gs = one ? (h->mixed ? L.mp.shape.G : L.shape.G) : (h->mixed ? L.mp.Gg : L.Gg);
         info->trip_A = h->mixed ? L.mp.trip : L.trip;
         info->trip_gs = h->mixed ? L.mp.tripg : L.tripg;

@@ -414,8 +414,7 @@ void build_batch(amg_ctx *h, int nsys, const amg_system *sys) {
         SetupPhase ph(h, "autotune");
         const bool reduced = p.precision != AMG_PREC_FP64;
         for (size_t l = 0; l < merged.size(); ++l)
-            if (merged[l].nA > 0 && (l == 0 || (!reduced && !sweeps_give_residual(h, merged[l]))))
-                autotune_level(h, merged[l]);
+            if (merged[l].nA > 0 && (l == 0 || !reduced)) autotune_level(h, merged[l]);
     }
 
     // level-0 layout of every system, chunk tables
@@ -644,8 +643,7 @@ void build_batch_spd(amg_ctx *h, int nsys, const amg_system *sys) {
                 M.d_cptr.upload(M.cptr, s);
                 if (M.Ag.nrows > 0) {
                     M.sweep.build(M.A, M.cptr, rows, M.g_rowid.p, M.n, 4, M.Ag, s);
-                    M.shape = sweep_shape(M.Ag.nnz, M.Ag.nrows, ncol, M.mode == 3);
-                    M.mp.shape = sweep_shape(M.Ag.nnz, M.Ag.nrows, ncol, false);
+                    choose_sweeps(h, M);
                 }
             }
         }
@@ -700,8 +698,9 @@ void build_batch_spd(amg_ctx *h, int nsys, const amg_system *sys) {
         SetupPhase ph(h, "autotune");
         const bool reduced = p.precision != AMG_PREC_FP64;
         for (size_t l = 0; l < merged.size(); ++l)
-            if (merged[l].nA > 0 && (l == 0 || (!reduced && !sweeps_give_residual(h, merged[l]))))
-                autotune_level(h, merged[l]);
+            if (merged[l].nA > 0 && (l == 0 || (!reduced && !sweeps_give_residual(h, merged[l], false))))
+                autotune_level(h, merged[l],
+                               !reduced && !merged[l].cptr.empty() && !one_launch_sweeps(h, merged[l], false));
     }
     // level-0 layout of every system (velocity ranges only), chunk tables
     h->nsys = nsys;

@@ -247,7 +247,7 @@ struct Level {
     DevBuf<int> g_rowid;      // node of grouped row g
     SweepData sweep;
     SweepShape shape;         // of its one-launch sweeps
-    bool by_colour = false;   // one launch per colour instead (a forced launch shape)
+    bool by_colour = false;   // one launch per colour instead (sweep_by_colour, or a forced launch shape)
     TileData tiles;           // of A (a large scalar finest level)
     bool by_rows = false;     // the row kernels instead (a forced launch shape)
     DevBuf<int> d_cptr;       // cptr on the device (tail kernel)
@@ -474,12 +474,20 @@ void setup_tail(amg_ctx *h);
 // lanes per row for a row kernel from the mean entries per row (4..64)
 int lanes_for(int64_t nnz, int nrows);
 // setup-time tuner of a level's FP64 natural-order kernels (lanes, loop form)
-void autotune_level(amg_ctx *h, Level &L);
-// the level's cycle runs no natural-order residual: its one-launch
-// pre-smoothing sweeps leave all of it but the entries of later colours
-inline bool sweeps_give_residual(const amg_ctx *h, const Level &L) {
-    return h->prm.smoother == AMG_SMOOTH_GS && h->prm.pre > 0 && L.sweep.usable();
+// and, if asked, of its sweeps with a launch per colour (XCD placement too)
+void autotune_level(amg_ctx *h, Level &L, bool sweeps = false);
+// the level's Gauss-Seidel sweeps, in FP64 or in the reduced-precision cycle, take one launch
+inline bool one_launch_sweeps(const amg_ctx *h, const Level &L, bool mp) {
+    return h->prm.smoother == AMG_SMOOTH_GS && L.sweep.usable() && !(mp ? L.mp.by_colour : L.by_colour);
 }
+// its cycle runs no natural-order residual: the one-launch pre-smoothing
+// sweeps leave all of it but the entries of later colours
+inline bool sweeps_give_residual(const amg_ctx *h, const Level &L, bool mp) {
+    return h->prm.pre > 0 && one_launch_sweeps(h, L, mp);
+}
+// the shape of the one-launch sweeps of a level whose rows are grouped, and
+// which of its sweeps run a launch per colour
+void choose_sweeps(const amg_ctx *h, Level &L);
 // first level covered by the SPD hierarchy's assembled coarse end, or -1
 int dense_tail_level(const amg_ctx *h);
 // evict the GPU caches before a tuner's timed run: inside a cycle a level's

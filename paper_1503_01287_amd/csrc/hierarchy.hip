@@ -321,6 +321,14 @@ SweepShape sweep_shape(int64_t nnz, int nrows, int ncolors, bool fp64_blocks) {
     return q;
 }
 
+void choose_sweeps(const amg_ctx *h, Level &L) {
+    const int nc = static_cast<int>(L.cptr.size()) - 1;
+    L.shape = sweep_shape(L.Ag.nnz, L.Ag.nrows, nc, L.mode == 3);
+    L.mp.shape = sweep_shape(L.Ag.nnz, L.Ag.nrows, nc, false);
+    L.by_colour = sweep_by_colour(L.mode, true, L.Ag.nnz, L.Ag.nrows, nc, h->prm.pre, h->prm.post);
+    L.mp.by_colour = sweep_by_colour(L.mode, false, L.Ag.nnz, L.Ag.nrows, nc, h->prm.pre, h->prm.post);
+}
+
 static void setup_smoother(amg_ctx *h, Level &L) {
     hipStream_t s = h->stream;
     const int nb = L.mode == 3 ? 9 : 1;
@@ -361,8 +369,7 @@ static void setup_smoother(amg_ctx *h, Level &L) {
     L.sweep.build(L.A, L.cptr, order, L.g_rowid.p, L.n, 4, L.Ag, s);
     AMG_HIP(hipStreamSynchronize(s));
     L.Gg = L.G;
-    L.shape = sweep_shape(L.Ag.nnz, L.Ag.nrows, ncol, L.mode == 3);
-    L.mp.shape = sweep_shape(L.Ag.nnz, L.Ag.nrows, ncol, false);
+    choose_sweeps(h, L);
 }
 
 // Autotuner: lanes per row for the level's row kernels, measured with HIP
@@ -396,7 +403,7 @@ void group_schur_rows(SchurLevel &q, hipStream_t s) {
     q.shape = sweep_shape(q.Sg.nnz, m, static_cast<int>(q.cptr.size()) - 1, false);
 }
 
-void autotune_level(amg_ctx *h, Level &L) {
+void autotune_level(amg_ctx *h, Level &L, bool sweeps) {
     hipStream_t s = h->stream;
     const int cand[] = {8, 16, 32, 64};
     hipEvent_t e0, e1;
@@ -442,9 +449,9 @@ void autotune_level(amg_ctx *h, Level &L) {
                     bestT = T;
                 }
             }
-        return std::make_pair(bestG, bestT);
+        return std::make_tuple(bestG, bestT, best);
     };
-    std::tie(L.G, L.trip) = pick(L.G, [&](int G, int P) {
+    std::tie(L.G, L.trip, std::ignore) = pick(L.G, [&](int G, int P) {
         RowArgs a;
         a.nrows = L.n;
         a.rowptr = L.A.rowptr.p;
@@ -457,6 +464,35 @@ void autotune_level(amg_ctx *h, Level &L) {
         a.trip = P;
         return time_it([&] { launch_row(L.mode, OP_RESID, G, a, s); });
     });
+    if (sweeps) {
+        // a whole forward sweep, colour by colour, as the smoother runs it,
+        // with round-robin or per-XCD contiguous workgroup placement
+        auto sweep_time = [&](int G, int P, int xcd) {
+            return time_it([&] {
+                for (size_t c = 0; c + 1 < L.cptr.size(); ++c) {
+                    if (L.cptr[c + 1] == L.cptr[c]) continue;
+                    RowArgs a;
+                    a.nrows = L.cptr[c + 1] - L.cptr[c];
+                    a.rowptr = L.Ag.rowptr.p + L.cptr[c];
+                    a.col = L.Ag.col.p;
+                    a.val = L.Ag.val.p;
+                    a.nnz = L.Ag.nnz;
+                    a.rowid = L.g_rowid.p + L.cptr[c];
+                    a.x = L.t.p;
+                    a.b = L.b.p;
+                    a.y = L.t.p;
+                    a.dinv = L.dinv.p;
+                    a.dinv_n = L.n;
+                    a.xcd_chunks = xcd;
+                    a.trip = P;
+                    launch_row(L.mode, OP_GS, G, a, s);
+                }
+            });
+        };
+        float rr_ms = 0.f;
+        std::tie(L.Gg, L.tripg, rr_ms) = pick(L.Gg, [&](int G, int P) { return sweep_time(G, P, 0); });
+        L.gs_xcd = sweep_time(L.Gg, L.tripg, 1) < 0.95f * rr_ms ? 1 : 0;
+    }
     if (L.n_pres > 0 && L.B.nnz > 0) {
         // saddle levels: lanes of the B (1x3, pressure rows) and B^T (3x1,
         // velocity rows) kernels, same rule (heuristic kept unless >= 5% slower)
@@ -1383,11 +1419,11 @@ void build_hierarchy(amg_ctx *h, const amg_system *sys) {
                 setup_smoother(h, L);
                 if (h->saddle) saddle_setup_level(h, L);
             }
-            const bool used = l == 0 || (!reduced && (tail_from < 0 || static_cast<int>(l) < tail_from) &&
-                                         !sweeps_give_residual(h, L));
-            if (p.autotune && used && L.tiles.v64.n == 0) {  // (tiles have no shapes to choose)
+            const bool in_cycle = !reduced && (tail_from < 0 || static_cast<int>(l) < tail_from);
+            if (p.autotune && (l == 0 || (in_cycle && !sweeps_give_residual(h, L, false))) &&
+                L.tiles.v64.n == 0) {  // (tiles have no shapes to choose)
                 SetupPhase ph(h, "autotune");
-                autotune_level(h, L);
+                autotune_level(h, L, in_cycle && !L.cptr.empty() && !one_launch_sweeps(h, L, false));
             }
         }
     }

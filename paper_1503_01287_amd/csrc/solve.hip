@@ -156,10 +156,6 @@ static void jacobi_step(amg_ctx *h, int l, const double *b, double *x, bool zero
     launch_copy(x, L.t.p, 3 * static_cast<int64_t>(L.nA), h->stream);
 }
 
-static bool one_launch_sweeps(const amg_ctx *h, const Level &L) {
-    return h->prm.smoother == AMG_SMOOTH_GS && L.sweep.usable() && !L.by_colour;
-}
-
 // One block Gauss-Seidel sweep by colours. x_zero: x is zero on entry (and
 // its buffer holds the zeros), so the first colour's rows see only zero
 // neighbours: x_i = D_i^{-1} b_i without reading their matrix rows.
@@ -185,7 +181,7 @@ static SweepArgs sweep_args(Level &L, const double *b, double *x, bool forward, 
 static void gs_sweep(amg_ctx *h, int l, const double *b, double *x, bool forward, bool x_zero, bool in_t,
                      double *part) {
     Level &L = h->lv[l];
-    if (one_launch_sweeps(h, L)) {
+    if (one_launch_sweeps(h, L, false)) {
         if (!x_zero && !in_t) launch_copy(L.t.p, x, 3 * static_cast<int64_t>(L.nA), h->stream);
         const double rows = L.Ag.nrows;
         ProfScope ps(h, tag("gs", l), row_bytes(L.Ag, x_zero ? L.Ag.nnz / 2 : L.Ag.nnz, L.Ag.nrows) +
@@ -235,7 +231,7 @@ static void smooth_from(amg_ctx *h, int l, const double *b, double *x, bool pre,
     const int steps = pre ? p.pre : p.post;
     Level &L = h->lv[l];
     const bool need_fill =
-        zero_init && !filled && (steps == 0 || (p.smoother != AMG_SMOOTH_JA && !(pre && one_launch_sweeps(h, L))));
+        zero_init && !filled && (steps == 0 || (p.smoother != AMG_SMOOTH_JA && !(pre && one_launch_sweeps(h, L, false))));
     if (need_fill) launch_fill(x, 0.0, 3 * static_cast<int64_t>(L.nA), h->stream);
     for (int k = 0; k < steps; ++k) {
         if (p.smoother == AMG_SMOOTH_JA)
@@ -282,7 +278,7 @@ static void cycle(amg_ctx *h, int l, const double *b, double *x, bool x_zero, bo
         run_dense_tail(h, b, x);
         return;
     }
-    if (h->prm.pre > 0 && one_launch_sweeps(h, L)) {
+    if (h->prm.pre > 0 && one_launch_sweeps(h, L, false)) {
         // the last pre-smoothing sweep leaves all of the residual but the
         // entries of later colours
         smooth_from(h, l, b, x, true, x_zero, filled, false, L.r.p);
@@ -312,7 +308,7 @@ static void cycle(amg_ctx *h, int l, const double *b, double *x, bool x_zero, bo
         for (int k = 0; k < nu; ++k) cycle(h, l + 1, C.b.p, C.x.p, k == 0, k == 0);
     }
     // one-launch sweeps read their iterate from L.t: the prolongation puts it there
-    const bool to_t = h->prm.post > 0 && one_launch_sweeps(h, L);
+    const bool to_t = h->prm.post > 0 && one_launch_sweeps(h, L, false);
     {
         RowArgs a = row_args(L.P);
         a.x = C.x.p;

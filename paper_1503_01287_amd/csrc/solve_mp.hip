@@ -81,6 +81,35 @@ static void autotune_mp(amg_ctx *h, Level &L) {
         a.trip = P;
         return time_it([&] { launch_row_mp(L.mode, OP_RESID, G, M.kind, a, s); });
     });
+    if (!L.cptr.empty() && !one_launch_sweeps(h, L, true)) {
+        // a whole forward sweep, colour by colour, as the smoother runs it;
+        // then per-XCD contiguous rows for the chosen kernel
+        auto sweep_time = [&](int G, int P, int xcd) {
+            return time_it([&] {
+                for (size_t c = 0; c + 1 < L.cptr.size(); ++c) {
+                    if (L.cptr[c + 1] == L.cptr[c]) continue;
+                    RowArgsMP a;
+                    a.nrows = L.cptr[c + 1] - L.cptr[c];
+                    a.rowptr = L.Ag.rowptr.p + L.cptr[c];
+                    a.col = L.Ag.col.p;
+                    a.val = M.agval();
+                    a.rscale = M.scale.p;
+                    a.nnz = L.Ag.nnz;
+                    a.rowid = L.g_rowid.p + L.cptr[c];
+                    a.x = M.t.p;
+                    a.b = M.b.p;
+                    a.y = M.t.p;
+                    a.dinv = M.dinv.p;
+                    a.dinv_n = L.n;
+                    a.xcd_chunks = xcd;
+                    a.trip = P;
+                    launch_row_mp(L.mode, OP_GS, G, M.kind, a, s);
+                }
+            });
+        };
+        M.Gg = pick(M.Gg, M.tripg, [&](int G, int P) { return sweep_time(G, P, 0); });
+        M.xcd = sweep_time(M.Gg, M.tripg, 1) < 0.95f * sweep_time(M.Gg, M.tripg, 0) ? 1 : 0;
+    }
     AMG_HIP(hipEventDestroy(e0));
     AMG_HIP(hipEventDestroy(e1));
 }
@@ -136,7 +165,7 @@ void build_mixed(amg_ctx *h) {
         // sweeps give the residual or in tiles: those kernels do not run in
         // the cycle)
         if (h->prm.autotune && !in_tiles(L) && (h->dense_start < 0 || static_cast<int>(l) < h->dense_start) &&
-            !sweeps_give_residual(h, L))
+            !sweeps_give_residual(h, L, true))
             autotune_mp(h, L);
     }
     refresh_tail_f32(h);
@@ -282,10 +311,6 @@ static float *jacobi_mp(amg_ctx *h, int l, const float *b, float *x, bool zero) 
     return x;
 }
 
-static bool one_launch_sweeps(const amg_ctx *h, const Level &L) {
-    return h->prm.smoother == AMG_SMOOTH_GS && L.sweep.usable() && !L.mp.by_colour;
-}
-
 static SweepArgs sweep_args(Level &L, const float *b, float *x, bool forward, bool x_zero, float *part) {
     SweepArgs a;
     L.sweep.fill(a, L.mp.shape, L.sweep.f32);
@@ -309,7 +334,7 @@ static int sweep_kind(const Level &L) { return L.mp.kind == VAL_F32 ? SWEEP_F32 
 // part: see SweepArgs::part (one-launch forward sweeps)
 static void gs_mp(amg_ctx *h, int l, const float *b, float *x, bool forward, bool x_zero, bool in_t, float *part) {
     Level &L = h->lv[l];
-    if (one_launch_sweeps(h, L)) {
+    if (one_launch_sweeps(h, L, true)) {
         if (!x_zero && !in_t) launch_copy_f32(L.mp.t.p, x, 3 * static_cast<int64_t>(L.nA), h->stream);
         ProfScope ps(h, tag("gs", l), mat_bytes(L, x_zero ? L.Ag.nnz / 2 : L.Ag.nnz, L.Ag.nrows) +
                                           L.Ag.nrows * (4.0 + 12.0 + 24.0 + (L.mode == 3 ? 36.0 : 4.0)));
@@ -354,7 +379,7 @@ static float *smooth_mp(amg_ctx *h, int l, const float *b, float *x, bool pre, b
     const int steps = pre ? p.pre : p.post;
     Level &L = h->lv[l];
     if (zero_init && !filled &&
-        (steps == 0 || (p.smoother != AMG_SMOOTH_JA && !(pre && one_launch_sweeps(h, L)))))
+        (steps == 0 || (p.smoother != AMG_SMOOTH_JA && !(pre && one_launch_sweeps(h, L, true)))))
         launch_fill_f32(x, 0.f, 3 * static_cast<int64_t>(L.nA), h->stream);
     for (int k = 0; k < steps; ++k) {
         if (p.smoother == AMG_SMOOTH_JA)
@@ -412,7 +437,7 @@ static float *cycle_mp(amg_ctx *h, int l, const float *b, float *x, bool x_zero,
             launch_dense_gemv_f32(h->tail_dense32.p, h->tail_m, h->tail_ld, h->tail_nc, b, x, h->stream);
         return x;
     }
-    if (h->prm.pre > 0 && one_launch_sweeps(h, L)) {
+    if (h->prm.pre > 0 && one_launch_sweeps(h, L, true)) {
         // the last pre-smoothing sweep leaves all of the residual but the
         // entries of later colours
         x = smooth_mp(h, l, b, x, true, x_zero, filled, false, L.mp.r.p);
@@ -446,7 +471,7 @@ static float *cycle_mp(amg_ctx *h, int l, const float *b, float *x, bool x_zero,
         for (int k = 0; k < nu; ++k) e = cycle_mp(h, l + 1, C.mp.b.p, e, k == 0, k == 0);
     }
     // one-launch sweeps read their iterate from mp.t: the prolongation puts it there
-    const bool to_t = h->prm.post > 0 && one_launch_sweeps(h, L);
+    const bool to_t = h->prm.post > 0 && one_launch_sweeps(h, L, true);
     {
         RowArgsMP a;
         a.nrows = L.P.nrows;

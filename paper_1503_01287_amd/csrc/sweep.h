@@ -57,6 +57,33 @@ constexpr bool sweep_half_fits(int64_t places, int stride) { return places * str
 
 constexpr int SWEEP_TILE_SIZES = 5;  // tiles of (SWEEP_THREADS_MIN / 64) << t rows
 
+// Whether a level's sweeps run a launch per colour although one launch could
+// take them all: with many entries a colour the launches cost little (5 us
+// each), and their rows need no waits and no second copy of x (k_sweep's tiles
+// stream 15 to 30% slower). What one launch saves besides, half of a residual,
+// it saves once a cycle, after the last of `pre` sweeps, so the line lies lower
+// for more than two sweeps or none before the residual. us per cycle, one
+// launch / a launch for each of the finest level's 14 colours, at thousands of
+// entries a colour:
+//   3x3 blocks FP64   GS-1-1  361  715 / 728    538 1012 / 983   1817 2854 / 2477
+//                     GS-2-2  227  928 / 958    361 1267 / 1236  1817 5372 / 4391
+//          FP32       GS-1-1 1052 1016 / 1021  1400 1273 / 1266  1817 1600 / 1558
+//                     GS-2-2  361  791 / 841    538 1091 / 1045  1817 2905 / 2721
+//   scalar FP64       GS-1-1  538  494 / 527   1051  836 / 823   4306 2982 / 2587
+//          FP32       GS-1-1 1817 1045 / 1061  2885 1539 / 1495  4306 2193 / 2080
+//                     GS-2-2 1051 1045 / 1105  1817 1907 / 1842
+// and of level 1, 30 colours of rows of 70 entries (both levels by colour):
+//   scalar FP64       GS-1-1  476 1846 / 1872   711 2587 / 2534
+//          BF16       GS-1-1  476 1495 / 1537   711 2080 / 2050
+//   blocks FP64       GS-2-2  309 4391 / 4662
+inline bool sweep_by_colour(int mode, bool fp64, int64_t nnz, int nrows, int ncolors, int pre, int post) {
+    const bool few = pre > 0 && pre + post <= 2;
+    int64_t most = 600000;
+    if (mode == SWEEP_BLOCK) most = fp64 ? (few ? 450000 : 350000) : (few ? 1200000 : 450000);
+    else if (!fp64 && nnz <= 40 * static_cast<int64_t>(nrows)) most = few ? 2200000 : 1400000;
+    return ncolors > 0 && nnz > most * ncolors;
+}
+
 // "absent" into both buffers of xg (n values in all, of the sweep's precision)
 void launch_sweep_absent(int kind, void *xg, int64_t n, hipStream_t s);
 void launch_sweep(int mode, int kind, const SweepShape &q, const SweepArgs &a, hipStream_t s);

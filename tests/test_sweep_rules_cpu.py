@@ -35,3 +35,24 @@ def test_usable(tmp_path):
              "(q.stride = 1, q.places = (1 << 28) - 1, q.usable())": 1,
              "(q.stride = 1, q.places = 1 << 28, q.usable())": 0}
     assert ask(tmp_path, cases) == list(cases.values())
+
+
+def test_large_colours_take_a_launch_each(tmp_path):
+    """Both sides of every line, by entries a colour (finest levels: rows of 28
+    entries, 14 colours; coarse ones: 70 and 30)."""
+    def rule(mode, fp64, row, colours, entries, pre, post):
+        nnz = int(entries * 1e3) * colours
+        return f"sweep_by_colour({mode}, {fp64}, {nnz}ll, {nnz // row}, {colours}, {pre}, {post})"
+
+    cases = {}
+    for mode, fp64, row, colours, pre, post, below, above in (
+            ("SWEEP_BLOCK", "true", 28, 14, 1, 1, 361, 538), ("SWEEP_BLOCK", "true", 28, 14, 2, 2, 309, 361),
+            ("SWEEP_BLOCK", "true", 28, 14, 0, 1, 309, 361), ("SWEEP_BLOCK", "false", 28, 14, 1, 1, 1052, 1400),
+            ("SWEEP_BLOCK", "false", 28, 14, 2, 2, 361, 538), ("SWEEP_BLOCK", "false", 70, 30, 1, 1, 1052, 1400),
+            ("SWEEP_SCALAR3", "true", 28, 14, 1, 1, 538, 1051), ("SWEEP_SCALAR3", "true", 70, 30, 2, 2, 476, 711),
+            ("SWEEP_SCALAR3", "false", 28, 14, 1, 1, 1817, 2885), ("SWEEP_SCALAR3", "false", 28, 14, 2, 2, 1051, 1817),
+            ("SWEEP_SCALAR3", "false", 70, 30, 1, 1, 476, 711)):
+        cases[rule(mode, fp64, row, colours, below, pre, post)] = 0
+        cases[rule(mode, fp64, row, colours, above, pre, post)] = 1
+    cases["sweep_by_colour(SWEEP_BLOCK, true, 0, 0, 0, 1, 1)"] = 0
+    assert ask(tmp_path, cases) == list(cases.values())
