@@ -688,9 +688,10 @@ int dense_tail_level(const amg_ctx *h) {
     int64_t bytes = 0;
     for (int k = 0; k <= L; ++k) bytes += 72 * static_cast<int64_t>(h->lv[k].n);
     if (fp64 && bytes <= TAIL_LDS_MAX && h->lv[0].A.nnz <= TAIL_NNZ_MAX) return 0;
+    const int most = p.nu == 1 ? TAIL_DENSE_MAX : p.smoother == AMG_SMOOTH_GS ? TAIL_W_GS_MAX : TAIL_W_JA_MAX;
     for (int k = 1; k < L; ++k) {
         const int m = h->lv[k].mode == 3 ? 3 * h->lv[k].n : h->lv[k].n;
-        if (m <= TAIL_DENSE_MAX) return k;
+        if (m <= most) return k;
     }
     return -1;
 }

@@ -56,6 +56,18 @@ constexpr int TAIL_LDS_MAX = 64 * 1024;   // bytes of LDS a workgroup's level ve
 // launches take 90 us against 5-10 us for the product)
 constexpr int64_t TAIL_NNZ_MAX = 40000;
 constexpr int TAIL_DENSE_MAX = 9000;      // largest tail operator kept as an explicit matrix
+// The same for several visits of a level (nu > 1). Each of m columns is a whole
+// W-cycle then, so the assembly grows with m^2 and more, while the visits that
+// it saves are cheap on larger levels: setup and one solve together must not
+// take longer than without. ms of setup + solve without any map / with it
+// (W-cycles, 2-2 steps):
+//   GS  m  980 (x3) elasticity  9^3  70 + 25 / 42 + 5     JA  m  737 Laplacian  8^3  35 +  2 /  25 + 1
+//      1272 (x3)   elasticity 24^3  187 + 117 / 98 + 24      1272  Laplacian 24^3   89 + 11 /  69 + 4
+//      5217        Laplacian 16^3    97 + 32 / 213 + 4       2846  Laplacian 32^3  124 + 14 / 143 + 7
+//      2293 (x3)   elasticity 12^3   99 + 44 / 171 + 6       5217  Laplacian 16^3   57 +  5 / 180 + 3
+// (JA also assembles again when a caller sets its weights: 3, 9, 47 and 146 ms.)
+constexpr int TAIL_W_GS_MAX = 4000;
+constexpr int TAIL_W_JA_MAX = 1500;
 
 // `grid` columns from unit_base on
 void launch_tail(int mode, const TailArgs &a, int lds_bytes, int grid, hipStream_t s);
