@@ -676,6 +676,7 @@ void saddle_smooth(amg_ctx *h, int l, const double *b, double *x) { saddle_step<
 constexpr int SADDLE_TAIL_MAX = 5000;
 constexpr double SADDLE_TAIL_BYTES_MAX = 2.0e9;
 constexpr double SADDLE_TAIL_SETUP_MS = 2000.0;
+constexpr double SADDLE_TAIL_VANKA_MS = 650.0;
 
 void setup_saddle_tail(amg_ctx *h) {
     h->saddle_tail_from = -1;
@@ -733,13 +734,13 @@ void setup_saddle_tail(amg_ctx *h) {
         const float sparse_ms = time_cycle(d, false);
         const double gemv_bytes = h->mixed ? 0.5 * bytes : bytes;  // FP32 copy in FP32 cycles
         if (gemv_bytes / 5.0e9 >= 0.9 * sparse_ms) continue;
-        // (Vanka sweeps are timed by their launches per colour here: those in
-        // one launch shorten an assembly, but pay for no larger map)
-        const bool vanka = h->prm.smoother == AMG_SMOOTH_VANKA;
-        for (int k = d; vanka && k < last; ++k) h->lv[k].vanka.by_colour = true;
-        const float asm_ms = h->mixed || vanka ? time_cycle(d, true) : sparse_ms;
-        for (int k = d; vanka && k < last; ++k) h->lv[k].vanka.by_colour = false;
-        if (static_cast<double>(mmax) * asm_ms > SADDLE_TAIL_SETUP_MS) continue;
+        // A Vanka sweep takes one launch, so a map saves fewer of them: 12^3
+        // 20 ms a solve and not 25 for 296 ms of assembly, 15^3 36 and 44 for
+        // 463 (estimates 289 and 457), 16^3 31 and 39 for 874 (870, no longer
+        // worth its setup).
+        const float asm_ms = h->mixed ? time_cycle(d, true) : sparse_ms;
+        const double most = h->prm.smoother == AMG_SMOOTH_VANKA ? SADDLE_TAIL_VANKA_MS : SADDLE_TAIL_SETUP_MS;
+        if (static_cast<double>(mmax) * asm_ms > most) continue;
         // the maps' layout on level lev (one square block per system);
         // returns the largest block
         auto layout = [&](int lev, DenseSegs &T) {
