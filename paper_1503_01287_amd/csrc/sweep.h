@@ -15,7 +15,8 @@ enum SweepKind : int { SWEEP_F64 = 0, SWEEP_F32 = 1, SWEEP_BF16 = 2 };
 constexpr int SWEEP_THREADS_MIN = 512;  // threads of a workgroup: these, or twice as many
 constexpr int SWEEP_MAX_COLOURS = 1023;
 constexpr int SWEEP_PAD = 32;         // a colour's range of the swept vector starts at a multiple of this many nodes
-// control words of a level's sweeps: ticket, exits, buffer in turn, given up
+// control words of a level's sweeps: ticket, exits, sweeps so far (odd and even
+// ones take the two buffers in turn), the last sweep that gave up
 constexpr int SWEEP_CTL_INTS = 128;
 
 // Grouped rows: a row's entries with earlier colours come first, then the
