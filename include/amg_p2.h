@@ -188,8 +188,10 @@ typedef struct {
                              during amg_setup.                               */
     int32_t graph;        /* 1 (default): each preconditioner application is
                              recorded once into a HIP graph and replayed
-                             (same kernels, same order, same results); 0:
-                             launched one by one. Profiling runs unrecorded. */
+                             (same kernels, same order, same results; CG
+                             launches short cycles one by one, which is
+                             faster); 0: launched one by one. Profiling runs
+                             unrecorded.                                     */
     double vanka_omega;   /* Vanka damping of the local corrections (0.8)  */
     int32_t gs_post;      /* direction of the post-smoothing Gauss-Seidel
                              sweeps (SPD systems): 0 (default) backward under

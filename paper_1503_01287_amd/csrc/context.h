@@ -338,7 +338,7 @@ struct ProfStat {
 
 struct amg_ctx_impl;
 
-enum GraphKind : int { GRAPH_PRECONDITION = 0, GRAPH_CG_STEP, GRAPH_CG_NEXT, GRAPH_CYCLE_F32 };
+enum GraphKind : int { GRAPH_PRECONDITION = 0, GRAPH_CYCLE_F32 };
 
 }  // namespace amgp2
 
@@ -415,7 +415,6 @@ struct amg_ctx {
     amgp2::DevBuf<double> g_in, g_out;
     // Krylov workspace
     amgp2::DevBuf<double> kr, kz, kp, kq, kw;
-    amgp2::DevBuf<double> kx;  // the iterate of a solve whose iterations are replayed graphs
     amgp2::MultiWork multi;  // amg_solve_multi
     amgp2::DevBuf<double> partial, sc;
     double *h_sc = nullptr;  // pinned host copy of the scalars

@@ -514,28 +514,44 @@ static void cg_update(amg_ctx *h, double *x, double *r, const double *p, const d
     launch_reduce(h->partial.p, nb, h->sc.p, SC_RR, h->stream, RED_NONE, h->h_sc);
 }
 
-// One iteration in two halves, either of which a small system replays as one
-// graph: its kernels take 2-5 us each, as long as their launch calls on the
-// host (Laplacian 4^3, 10 calls an iteration: 61 us of which the GPU works
-// 28). cg_step: up to the stopping test's scalars; cg_cycle and
-// cg_next_direction: the next direction, which may go ahead of that test (it
-// leaves x and r alone).
+// Whether CG launches the cycle's kernels one by one although graphs are on. A
+// graph takes about 14 us of the stream until its first kernel, and its
+// kernels follow each other 2 to 3 us apart instead of 4: it pays where many
+// kernels are shorter than that (launches per colour, Jacobi steps on several
+// small levels), not for the few of a cycle of one level or one that ends in
+// the assembled map, nor for sweeps of a launch each. us per solve, graph / one
+// by one:
+//   Laplacian  4^3 GS-1-1 FP64   1249 /  683   elasticity 12^3 JA-1-1 FP64  6319 /  6019
+//             12^3 JA-1-1 FP64   1933 / 1738              12^3 GS-1-1 MIXED 4542 /  4344
+//             48^3 GS-1-1 MIXED 28489 / 28370             32^3 GS-1-1 MIXED 27317 / 27045
+//   W-cycles: Laplacian 8^3 JA-1-1 MIXED 2266 / 2712, 16^3 FP64 3319 / 3410,
+//             elasticity 12^3 GS-1-1 MIXED 23904 / 23850
+//   a launch per colour: elasticity 8^3 GS-1-1 MIXED 5149 / 5595
+// (Two graphs of the whole iteration, 0.96 to 1.05 of the time with a graph of
+// the cycle, were slower than single launches everywhere.)
+static bool cycle_launched(const amg_ctx *h) {
+    const int last = static_cast<int>(h->lv.size()) - 1, top = h->dense_start >= 0 ? h->dense_start : last;
+    if (h->prm.smoother == AMG_SMOOTH_GS) {
+        for (int l = 0; l < top; ++l)
+            if (!one_launch_sweeps(h, h->lv[l], h->mixed)) return false;
+        return true;
+    }
+    return top <= 1 || (h->dense_start >= 0 && h->prm.nu == 1);
+}
+
+// One iteration in two halves. cg_step: up to the stopping test's scalars;
+// cg_cycle and cg_next_direction: the next direction, which may go ahead of
+// that test (it leaves x and r alone).
 static void cg_step(amg_ctx *h, bool fcg, double *x) {
     double *r = h->kr.p, *p = h->kp.p, *q = h->kq.p;
     spmv_dot(h, p, q, fcg ? RED_FCG_ALPHA : RED_CG_ALPHA);
     cg_update(h, x, r, p, q);
 }
-static void cg_cycle_eager(amg_ctx *h) {
+static void cg_cycle(amg_ctx *h, bool launched) {
     if (cg_f32(h))
-        cycle_f32_eager(h);
+        launched ? cycle_f32_eager(h) : cycle_f32(h);
     else
-        precondition_eager(h, h->kr.p, h->kz.p);
-}
-static void cg_cycle(amg_ctx *h) {
-    if (cg_f32(h))
-        cycle_f32(h);
-    else
-        precondition_impl(h, h->kr.p, h->kz.p);
+        launched ? precondition_eager(h, h->kr.p, h->kz.p) : precondition_impl(h, h->kr.p, h->kz.p);
 }
 template <typename T>
 static void cg_direction_from(amg_ctx *h, bool fcg, bool first, const T *z) {
@@ -554,25 +570,6 @@ static void cg_next_direction(amg_ctx *h, bool fcg, bool first = false) {
         cg_direction_from(h, fcg, first, h->cg_z);
     else
         cg_direction_from(h, fcg, first, static_cast<const double *>(h->kz.p));
-}
-
-// Unknowns up to which CG replays its iteration as two graphs: beyond, an
-// iteration works longer on the GPU than its launch calls take (elasticity
-// 21^3, 238,521 unknowns: no difference), and the iterate's two copies count.
-constexpr int CG_GRAPH_MAX = 100000;
-
-static hipGraphExec_t cg_graph(amg_ctx *h, int kind, bool fcg) {
-    for (const auto &g : h->graphs)
-        if (g.kind == kind) return g.exec;
-    h->graphs.push_back({kind, nullptr, nullptr, record_graph(h, [&] {
-                             if (kind == GRAPH_CG_STEP) {
-                                 cg_step(h, fcg, h->kx.p);
-                             } else {
-                                 cg_cycle_eager(h);
-                                 cg_next_direction(h, fcg);
-                             }
-                         })});
-    return h->graphs.back().exec;
 }
 
 double true_relres(amg_ctx *h, const double *b, const double *x, double r0norm) {
@@ -616,34 +613,20 @@ static int solve_cg(amg_ctx *h, bool fcg, const double *b, double *x, double tol
     if (rr0 == 0.0) return finish(h, b, x, r0, 0, AMG_OK, t0, res);
     if (!(rr0 == rr0)) return finish(h, b, x, r0, 0, AMG_DIVERGED, t0, res);
     if (maxit <= 0) return finish(h, b, x, r0, 0, AMG_NOT_CONVERGED, t0, res);
-    const bool graphs = h->prm.graph && !h->prof && n <= CG_GRAPH_MAX;
-    double *xi = x;  // the iterate (recorded launches need a place of their own for it)
-    hipGraphExec_t step = nullptr, next = nullptr;
-    if (graphs) {
-        if (h->kx.n != static_cast<size_t>(n)) h->kx.alloc(static_cast<size_t>(n));
-        xi = h->kx.p;
-        launch_copy(xi, x, n, h->stream);
-        step = cg_graph(h, GRAPH_CG_STEP, fcg);
-        next = cg_graph(h, GRAPH_CG_NEXT, fcg);
-    }
+    const bool launched = cycle_launched(h);
     if (cg_f32(h)) launch_to_f32(r, h->lv[0].mp.b.p, n, h->stream);
-    cg_cycle(h);
+    cg_cycle(h, launched);
     cg_next_direction(h, fcg, true);
     int it = 0, status = AMG_NOT_CONVERGED;
     double rel = 1.0;
     while (it < maxit) {
-        if (step) AMG_HIP(hipGraphLaunch(step, h->stream));
-        else cg_step(h, fcg, xi);
+        cg_step(h, fcg, x);
         ++it;
         scalars_begin(h);
         const bool ahead = it < maxit && rel > KRYLOV_AHEAD * tol;
         auto go = [&] {
-            if (next) {
-                AMG_HIP(hipGraphLaunch(next, h->stream));
-            } else {
-                cg_cycle(h);
-                cg_next_direction(h, fcg);
-            }
+            cg_cycle(h, launched);
+            cg_next_direction(h, fcg);
         };
         if (ahead) go();
         scalars_wait(h);
@@ -654,7 +637,6 @@ static int solve_cg(amg_ctx *h, bool fcg, const double *b, double *x, double tol
         rel = std::sqrt(rr / rr0);
         if (!ahead && it < maxit) go();
     }
-    if (xi != x) launch_copy(x, xi, n, h->stream);
     return finish(h, b, x, r0, it, status, t0, res);
 }
 
