@@ -477,27 +477,19 @@ __device__ __forceinline__ void mpartials(const double *acc, double *partial) {
     }
 }
 
-template <typename T>
-struct DotPtrs {
-    const T *a[3];
-    const double *b[3];
-};
-
 // per block: sums over the dofs d = t, t + stride, ... (a fixed assignment,
 // the same in every kernel below that sums), then a fixed-order tree over the
-// block; partial[blk * np K + p K + r]
-template <int NP, int K, typename T>
-__global__ void __launch_bounds__(TB) k_mdot(DotPtrs<T> q, int64_t nd, double *partial) {
-    double acc[NP * K];
+// block; partial[blk * K + r]
+template <int K, typename T>
+__global__ void __launch_bounds__(TB) k_mdot(const T *a, const double *b, int64_t nd, double *partial) {
+    double acc[K];
 #pragma unroll
-    for (int o = 0; o < NP * K; ++o) acc[o] = 0.0;
+    for (int r = 0; r < K; ++r) acc[r] = 0.0;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * TB;
     for (int64_t d = static_cast<int64_t>(blockIdx.x) * TB + threadIdx.x; d < nd; d += stride)
 #pragma unroll
-        for (int p = 0; p < NP; ++p)
-#pragma unroll
-            for (int r = 0; r < K; ++r) acc[p * K + r] += static_cast<double>(q.a[p][d * K + r]) * q.b[p][d * K + r];
-    mpartials<NP * K>(acc, partial);
+        for (int r = 0; r < K; ++r) acc[r] += static_cast<double>(a[d * K + r]) * b[d * K + r];
+    mpartials<K>(acc, partial);
 }
 
 // out[o] = sum of partial[blk][o] over the nb blocks: one workgroup per
@@ -525,38 +517,19 @@ static void mreduce(int nb, int no, const double *partial, double *out, hipStrea
     AMG_CHECK_LAUNCH();
 }
 
-template <int NP, typename T>
-static void mdot_np(int K, int nb, const DotPtrs<T> &q, int64_t nd, double *partial, hipStream_t s) {
+template <typename T>
+void launch_mdot(int K, int64_t nd, const T *a, const double *b, double *partial, double *out, hipStream_t s) {
+    const int nb = mdot_blocks(nd);
     switch (K) {
-        case 2: k_mdot<NP, 2, T><<<nb, TB, 0, s>>>(q, nd, partial); break;
-        case 4: k_mdot<NP, 4, T><<<nb, TB, 0, s>>>(q, nd, partial); break;
-        case 8: k_mdot<NP, 8, T><<<nb, TB, 0, s>>>(q, nd, partial); break;
+        case 2: k_mdot<2><<<nb, TB, 0, s>>>(a, b, nd, partial); break;
+        case 4: k_mdot<4><<<nb, TB, 0, s>>>(a, b, nd, partial); break;
+        case 8: k_mdot<8><<<nb, TB, 0, s>>>(a, b, nd, partial); break;
         default: throw Error(AMG_EINVAL, "multi dot: K must be 2, 4 or 8");
     }
-}
-
-void launch_mdot(int np, int K, int64_t nd, const double *const *a, const double *const *b, double *partial,
-                 double *out, hipStream_t s) {
-    AMG_REQUIRE(np == 1 || np == 2, AMG_EINVAL, "multi dot: 1 or 2 pairs");
-    DotPtrs<double> q{};
-    for (int p = 0; p < np; ++p) {
-        q.a[p] = a[p];
-        q.b[p] = b[p];
-    }
-    const int nb = mdot_blocks(nd);
-    if (np == 1) mdot_np<1>(K, nb, q, nd, partial, s);
-    else mdot_np<2>(K, nb, q, nd, partial, s);
-    mreduce(nb, np * K, partial, out, s);
-}
-
-void launch_mdot_f32(int K, int64_t nd, const float *a, const double *b, double *partial, double *out, hipStream_t s) {
-    DotPtrs<float> q{};
-    q.a[0] = a;
-    q.b[0] = b;
-    const int nb = mdot_blocks(nd);
-    mdot_np<1>(K, nb, q, nd, partial, s);
     mreduce(nb, K, partial, out, s);
 }
+template void launch_mdot<double>(int, int64_t, const double *, const double *, double *, double *, hipStream_t);
+template void launch_mdot<float>(int, int64_t, const float *, const double *, double *, double *, hipStream_t);
 
 // The iteration's vector work is bound by memory (52 MB a vector of the 32^3
 // Laplacian with 8 right-hand sides), so each vector is read once per

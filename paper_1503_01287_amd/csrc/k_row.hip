@@ -656,31 +656,6 @@ void launch_diag_inverse(int mode, int n, const int *rowptr, const int *col, con
     AMG_CHECK_LAUNCH();
 }
 
-// one wavefront per grouped row
-__global__ void k_gather_rows(int np, int nrows, const int *order, const int *rowptr, const int *col,
-                              const double *val, int64_t nnz, const int *g_rowptr, int *g_col,
-                              double *g_val, int64_t g_nnz) {
-    const int g = blockIdx.x * (BLOCK / 64) + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (g >= nrows) return;
-    const int i = order[g];
-    const int src = rowptr[i], len = rowptr[i + 1] - rowptr[i];
-    const int dst = g_rowptr[g];
-    for (int q = lane; q < len; q += 64) {
-        g_col[dst + q] = col[src + q];
-        for (int p = 0; p < np; ++p) g_val[p * g_nnz + dst + q] = val[p * nnz + src + q];
-    }
-}
-
-void launch_gather_rows(int np, int nrows, const int *order, const int *rowptr, const int *col,
-                        const double *val, int64_t nnz, const int *g_rowptr, int *g_col, double *g_val,
-                        int64_t g_nnz, hipStream_t s) {
-    if (nrows <= 0) return;
-    k_gather_rows<<<ceil_div(nrows, BLOCK / 64), BLOCK, 0, s>>>(np, nrows, order, rowptr, col, val, nnz,
-                                                                 g_rowptr, g_col, g_val, g_nnz);
-    AMG_CHECK_LAUNCH();
-}
-
 // Entry k of row i is kept when it is the diagonal of a square operator or
 // one of its np planes is nonzero.
 __device__ inline bool kept_entry(int np, const double *val, int64_t nnz, int64_t k, bool diag) {

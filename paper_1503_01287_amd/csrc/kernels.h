@@ -114,11 +114,6 @@ void launch_dense_gemv(const double *M, int m, int nc, const double *X, double *
 // written as planes of stride n. Fails (flag set) if a diagonal is missing.
 void launch_diag_inverse(int mode, int n, const int *rowptr, const int *col, const double *val,
                          int64_t nnz, double *dinv, int *flag, hipStream_t s);
-// Gather rows order[g] of (rowptr, col, val; planes nnz apart) into the
-// grouped copy (g_rowptr, g_col, g_val; planes g_nnz apart).
-void launch_gather_rows(int np, int nrows, const int *order, const int *rowptr, const int *col,
-                        const double *val, int64_t nnz, const int *g_rowptr, int *g_col,
-                        double *g_val, int64_t g_nnz, hipStream_t s);
 
 // Dropping numerically zero entries (all planes zero; the diagonal of a
 // square operator is always kept): count per row, then the kept entries in

@@ -49,11 +49,10 @@ void launch_mdiag_solve(int mode, int kind, int K, int nrows, const int *rowid, 
 void launch_mdense(int mkind, const void *M, int m, int ld, int nc, const void *X, void *Y, hipStream_t s);
 // Krylov vector work on interleaved FP64 blocks of n_dof x K values
 // (sums in a fixed order, into host memory)
-// out[p * K + r] = <a_p, b_p> over right-hand side r, for the np pairs (1 or 2)
+// out[r] = <a, b> over right-hand side r
 int mdot_blocks(int64_t nd);
-void launch_mdot(int np, int K, int64_t nd, const double *const *a, const double *const *b, double *partial,
-                 double *out, hipStream_t s);
-void launch_mdot_f32(int K, int64_t nd, const float *a, const double *b, double *partial, double *out, hipStream_t s);
+template <typename T>
+void launch_mdot(int K, int64_t nd, const T *a, const double *b, double *partial, double *out, hipStream_t s);
 // a coefficient per right-hand side
 struct MCoef {
     double c[MULTI_MAX_K] = {};

@@ -233,7 +233,7 @@ static void multi_alloc(amg_ctx *h, MultiWork &W, int K) {
     }
     const size_t nd = static_cast<size_t>(h->n_dof) * K;
     for (DevBuf<double> *v : {&W.B, &W.X, &W.R, &W.Z, &W.P, &W.Q}) v->alloc(nd);
-    W.partial.alloc(static_cast<size_t>(mdot_blocks(h->n_dof)) * 2 * K);
+    W.partial.alloc(static_cast<size_t>(mdot_blocks(h->n_dof)) * K);
     if (!W.h_dots)
         AMG_HIP(hipHostMalloc(reinterpret_cast<void **>(&W.h_dots), 2 * MULTI_MAX_K * sizeof(double),
                               hipHostMallocCoherent));
@@ -257,7 +257,7 @@ static void mapply(amg_ctx *h, int K, const double *x, double *y) {
 static void msync(amg_ctx *h) { AMG_HIP(hipStreamSynchronize(h->stream)); }
 
 static std::vector<double> mnorms(amg_ctx *h, MultiWork &W, const double *v) {
-    launch_mdot(1, W.K, h->n_dof, &v, &v, W.partial.p, W.h_dots, h->stream);
+    launch_mdot(W.K, h->n_dof, v, v, W.partial.p, W.h_dots, h->stream);
     msync(h);
     return std::vector<double>(W.h_dots, W.h_dots + W.K);
 }
@@ -293,9 +293,9 @@ int solve_multi(amg_ctx *h, int nrhs, const double *B, double *X, double tol, in
     double *const second = W.h_dots + K;
     auto dot_z = [&](const double *v) {
         if (h->mixed)
-            launch_mdot_f32(K, nd, z32, v, W.partial.p, second, s);
+            launch_mdot(K, nd, z32, v, W.partial.p, second, s);
         else
-            launch_mdot(1, K, nd, &z64, &v, W.partial.p, second, s);
+            launch_mdot(K, nd, z64, v, W.partial.p, second, s);
     };
     auto direction = [&](const MCoef &beta, bool first, const double *r) {
         if (h->mixed)
@@ -357,8 +357,7 @@ int solve_multi(amg_ctx *h, int nrhs, const double *B, double *X, double tol, in
             direction(beta, it == 0, W.R.p);
         }
         mapply(h, K, W.P.p, W.Q.p);
-        const double *pp = W.P.p, *qq = W.Q.p;
-        launch_mdot(1, K, nd, &pp, &qq, W.partial.p, W.h_dots, s);
+        launch_mdot(K, nd, W.P.p, W.Q.p, W.partial.p, W.h_dots, s);
         msync(h);
         for (int r = 0; r < K; ++r) {
             alpha.c[r] = 0.0;
