@@ -667,6 +667,7 @@ int amg_set_launch_shape(amg_handle h, int32_t level, int32_t kernels, int32_t l
                             "amg_set_launch_shape: no Vanka sweep on this level");
                 AMG_REQUIRE(lanes >= 16 && (trip == 1 || trip == 2) && xcd == 0, AMG_EINVAL,
                             "amg_set_launch_shape: the Vanka residual takes 16, 32 or 64 lanes, trip 1 or 2, xcd 0");
+                if (trip == 1 && L.vanka.pbuf.n == 0) setup_vanka_chunks(h, L);
                 L.vanka.path = trip == 1 ? 2 : 3;
                 L.vanka.by_colour = true;
                 L.vanka.rg = lanes;

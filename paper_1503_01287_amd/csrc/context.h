@@ -451,6 +451,7 @@ void saddle_setup_level(amg_ctx *h, Level &L);
 void setup_schur(amg_ctx *h, int l);
 void setup_vanka(amg_ctx *h, int l);
 void setup_vanka_sweep(amg_ctx *h, int l);
+void setup_vanka_chunks(amg_ctx *h, Level &L);  // tables of path 2
 void setup_schur_dense(amg_ctx *h, int l);
 void setup_saddle_tail(amg_ctx *h);
 VankaView vanka_view(Level &L);

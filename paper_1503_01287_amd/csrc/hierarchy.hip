@@ -948,7 +948,6 @@ void setup_vanka(amg_ctx *h, int l) {
         rtot += 3 * static_cast<int64_t>(bp.rowptr[i + 1] - bp.rowptr[i]) + 1;
     }
     AMG_REQUIRE(rtot < (int64_t(1) << 31), AMG_EUNSUPPORTED, "amg_setup: too many Vanka patch unknowns");
-    std::vector<int> tpre(std::max(1, np), 0);
     std::vector<int2> rown;
     std::vector<VankaTile> tiles;
     V.rptr.assign(1, 0);
@@ -956,7 +955,6 @@ void setup_vanka(amg_ctx *h, int l) {
     for (int c = 0; c < nc; ++c) {
         for (int k = V.cptr[c]; k < V.cptr[c + 1]; ++k) {
             const int i = order[k], p0 = bp.rowptr[i], nn = bp.rowptr[i + 1] - p0, m = 3 * nn + 1;
-            tpre[k] = static_cast<int>(tiles.size()) - V.tptr[c];
             const int row = static_cast<int>(rown.size());
             for (int q = 0; q < nn; ++q) rown.push_back(make_int2(bp.col[p0 + q], static_cast<int>(roff[i]) + 3 * q));
             rown.push_back(make_int2(~i, static_cast<int>(roff[i]) + 3 * nn));
@@ -975,40 +973,50 @@ void setup_vanka(amg_ctx *h, int l) {
         V.rptr.push_back(static_cast<int>(rown.size()));
         V.tptr.push_back(static_cast<int>(tiles.size()));
     }
-    V.roff.upload(roff, s);
-    V.tpre.upload(tpre, s);
     V.rown.upload(rown, s);
     V.tile.upload(tiles, s);
     V.rowa.alloc(rown.size());
     launch_vanka_rows(view, static_cast<int>(rown.size()), V.rown.p, V.rowa.p, s);
     V.rbuf.alloc(static_cast<size_t>(std::max<int64_t>(1, rtot)));
     V.rg = L.A.nnz > 40 * static_cast<int64_t>(L.n) ? 64 : 32;
-    // three-kernel path: 64-row x cc-column tiles of the inverses and their
-    // partial sums, colour by colour
-    const int cc = V.cc;
-    std::vector<int> upre(std::max(1, np), 0);
-    std::vector<int64_t> poff(std::max(1, np), 0);
-    V.nunits.assign(nc, 0);
-    int64_t ptot = 0;
+    AMG_HIP(hipStreamSynchronize(s));
+}
+
+// What the three-kernel form of the launches per colour reads beside that
+// (only a caller asks for it): a patch's residual, the 64-row x cc-column tiles
+// of its inverse and their partial sums, colour by colour.
+void setup_vanka_chunks(amg_ctx *h, Level &L) {
+    hipStream_t s = h->stream;
+    VankaData &V = L.vanka;
+    const std::vector<int> pptr = V.pptr.download(s), order = V.order.download(s);
+    const int np = V.npatch, nc = static_cast<int>(V.cptr.size()) - 1, cc = V.cc;
+    std::vector<int64_t> roff(std::max(1, np), 0), poff(std::max(1, np), 0);
+    std::vector<int> tpre(std::max(1, np), 0), upre(std::max(1, np), 0);
+    int64_t rtot = 0, ptot = 0;
     for (int i = 0; i < np; ++i) {
-        const int64_t m = 3 * static_cast<int64_t>(bp.rowptr[i + 1] - bp.rowptr[i]) + 1;
+        const int64_t m = 3 * static_cast<int64_t>(pptr[i + 1] - pptr[i]) + 1;
+        roff[i] = rtot;
         poff[i] = ptot;
+        rtot += m;
         ptot += ((m + cc - 1) / cc) * m;
     }
+    V.nunits.assign(nc, 0);
     for (int c = 0; c < nc; ++c) {
-        int t = 0;
+        int t = 0, u = 0;
         for (int k = V.cptr[c]; k < V.cptr[c + 1]; ++k) {
-            upre[k] = t;
-            const int i = order[k];
-            const int m = 3 * (bp.rowptr[i + 1] - bp.rowptr[i]) + 1;
-            t += ((m + 63) / 64) * ((m + cc - 1) / cc);
+            const int i = order[k], m = 3 * (pptr[i + 1] - pptr[i]) + 1;
+            tpre[k] = t;
+            upre[k] = u;
+            t += (m + 63) / 64;
+            u += ((m + 63) / 64) * ((m + cc - 1) / cc);
         }
-        V.nunits[c] = t;
+        V.nunits[c] = u;
     }
+    V.roff.upload(roff, s);
+    V.tpre.upload(tpre, s);
     V.upre.upload(upre, s);
     V.poff.upload(poff, s);
     V.pbuf.alloc(static_cast<size_t>(std::max<int64_t>(1, ptot)));
-    AMG_HIP(hipStreamSynchronize(s));
 }
 
 // Tables of the one-launch sweeps, from the operators that the sweeps read
