@@ -641,10 +641,7 @@ void build_batch_spd(amg_ctx *h, int nsys, const amg_system *sys) {
                 if (rows.empty()) rows.push_back(0);
                 M.g_rowid.upload(rows, s);
                 M.d_cptr.upload(M.cptr, s);
-                if (M.Ag.nrows > 0) {
-                    M.sweep.build(M.A, M.cptr, rows, M.g_rowid.p, M.n, 4, M.Ag, s);
-                    choose_sweeps(h, M);
-                }
+                if (M.Ag.nrows > 0) M.sweep.build(M.A, M.cptr, rows, M.g_rowid.p, M.n, 4, M.Ag, s);
             }
         }
         // systems ending on this level: their coarsest inverses, as 3 n x 3 n
@@ -682,6 +679,7 @@ void build_batch_spd(amg_ctx *h, int nsys, const amg_system *sys) {
         }
         M.G = lanes_of(M.A.nnz, M.n);
         M.Gg = M.G;
+        if (M.Ag.nrows > 0) choose_sweeps(h, M);
         M.Gp = lanes_of(M.P.nnz, M.P.nrows);
         M.Gr = lanes_of(M.R.nnz, M.R.nrows);
         const size_t nv = 3 * static_cast<size_t>(std::max(1, M.n));

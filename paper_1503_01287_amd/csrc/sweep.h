@@ -66,13 +66,14 @@ constexpr int SWEEP_TILE_SIZES = 5;  // tiles of (SWEEP_THREADS_MIN / 64) << t r
 // for more than two sweeps or none before the residual. us per cycle, one
 // launch / a launch for each of the finest level's 14 colours, at thousands of
 // entries a colour:
-//   3x3 blocks FP64   GS-1-1  361  715 / 728    538 1012 / 983   1817 2854 / 2477
-//                     GS-2-2  227  928 / 958    361 1267 / 1236  1817 5372 / 4391
-//          FP32       GS-1-1 1052 1016 / 1021  1400 1273 / 1266  1817 1600 / 1558
-//                     GS-2-2  361  791 / 841    538 1091 / 1045  1817 2905 / 2721
-//   scalar FP64       GS-1-1  538  494 / 527   1051  836 / 823   4306 2982 / 2587
-//          FP32       GS-1-1 1817 1045 / 1061  2885 1539 / 1495  4306 2193 / 2080
-//                     GS-2-2 1051 1045 / 1105  1817 1907 / 1842
+//   3x3 blocks FP64   GS-1-1  361  712 / 726    538 1012 / 983   1817 2854 / 2477
+//                     GS-2-2  289 1088 / 1078   361 1264 / 1234  1817 5372 / 4391
+//          FP32       GS-1-1 1218 1129 / 1137  1400 1273 / 1266  1817 1600 / 1558
+//                     GS-2-2  361  788 / 839    538 1091 / 1045  1817 2905 / 2721
+//   scalar FP64       GS-1-1  766  628 / 645   1051  835 / 822   4306 2982 / 2587
+//                     GS-2-2  901 1260 / 1252  1051 1461 / 1413
+//          FP32       GS-1-1 1817 1043 / 1060  2310 1272 / 1202  4306 2193 / 2080
+//                     GS-2-2 1399 1347 / 1343  1817 1904 / 1798
 // and of level 1, 30 colours of rows of 70 entries (both levels by colour):
 //   scalar FP64       GS-1-1  476 1846 / 1872   711 2587 / 2534
 //          BF16       GS-1-1  476 1495 / 1537   711 2080 / 2050
@@ -80,8 +81,8 @@ constexpr int SWEEP_TILE_SIZES = 5;  // tiles of (SWEEP_THREADS_MIN / 64) << t r
 inline bool sweep_by_colour(int mode, bool fp64, int64_t nnz, int nrows, int ncolors, int pre, int post) {
     const bool few = pre > 0 && pre + post <= 2;
     int64_t most = 600000;
-    if (mode == SWEEP_BLOCK) most = fp64 ? (few ? 450000 : 350000) : (few ? 1200000 : 450000);
-    else if (!fp64 && nnz <= 40 * static_cast<int64_t>(nrows)) most = few ? 2200000 : 1400000;
+    if (mode == SWEEP_BLOCK) most = fp64 ? (few ? 450000 : 350000) : (few ? 1300000 : 450000);
+    else if (nnz <= 40 * static_cast<int64_t>(nrows)) most = fp64 ? 950000 : (few ? 2200000 : 1400000);
     return ncolors > 0 && nnz > most * ncolors;
 }
 

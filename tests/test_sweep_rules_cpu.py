@@ -47,10 +47,10 @@ def test_large_colours_take_a_launch_each(tmp_path):
     cases = {}
     for mode, fp64, row, colours, pre, post, below, above in (
             ("SWEEP_BLOCK", "true", 28, 14, 1, 1, 361, 538), ("SWEEP_BLOCK", "true", 28, 14, 2, 2, 309, 361),
-            ("SWEEP_BLOCK", "true", 28, 14, 0, 1, 309, 361), ("SWEEP_BLOCK", "false", 28, 14, 1, 1, 1052, 1400),
+            ("SWEEP_BLOCK", "true", 28, 14, 0, 1, 309, 361), ("SWEEP_BLOCK", "false", 28, 14, 1, 1, 1218, 1400),
             ("SWEEP_BLOCK", "false", 28, 14, 2, 2, 361, 538), ("SWEEP_BLOCK", "false", 70, 30, 1, 1, 1052, 1400),
-            ("SWEEP_SCALAR3", "true", 28, 14, 1, 1, 538, 1051), ("SWEEP_SCALAR3", "true", 70, 30, 2, 2, 476, 711),
-            ("SWEEP_SCALAR3", "false", 28, 14, 1, 1, 1817, 2885), ("SWEEP_SCALAR3", "false", 28, 14, 2, 2, 1051, 1817),
+            ("SWEEP_SCALAR3", "true", 28, 14, 1, 1, 901, 1051), ("SWEEP_SCALAR3", "true", 70, 30, 2, 2, 476, 711),
+            ("SWEEP_SCALAR3", "false", 28, 14, 1, 1, 1817, 2310), ("SWEEP_SCALAR3", "false", 28, 14, 2, 2, 1399, 1817),
             ("SWEEP_SCALAR3", "false", 70, 30, 1, 1, 476, 711)):
         cases[rule(mode, fp64, row, colours, below, pre, post)] = 0
         cases[rule(mode, fp64, row, colours, above, pre, post)] = 1
