@@ -34,7 +34,8 @@
 //   16^3 level 1 ( 5,217 rows, 29 colours)  FP64 178 -> 58   BF16 173 -> 54
 //   32^3 level 0 (274,625 rows)             FP64 217 -> 236  FP32 147 -> 149
 //   32^3 level 1 ( 39,233 rows)             FP64 200 -> 101  BF16 156 -> 70
-// (with `part`, which saves half of the residual's pass after the sweep).
+// (with `part`, which saves half of the residual's pass after the sweep; from
+// some 32^3 on, by precision, a launch per colour is faster: sweep_by_colour).
 #include "common.h"
 #include "sweep.h"
 
