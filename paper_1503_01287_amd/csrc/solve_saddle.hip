@@ -676,7 +676,7 @@ void saddle_smooth(amg_ctx *h, int l, const double *b, double *x) { saddle_step<
 constexpr int SADDLE_TAIL_MAX = 5000;
 constexpr double SADDLE_TAIL_BYTES_MAX = 2.0e9;
 constexpr double SADDLE_TAIL_SETUP_MS = 2000.0;
-constexpr double SADDLE_TAIL_VANKA_MS = 650.0;
+constexpr double SADDLE_TAIL_VANKA_MS = 770.0;
 
 void setup_saddle_tail(amg_ctx *h) {
     h->saddle_tail_from = -1;
@@ -734,10 +734,10 @@ void setup_saddle_tail(amg_ctx *h) {
         const float sparse_ms = time_cycle(d, false);
         const double gemv_bytes = h->mixed ? 0.5 * bytes : bytes;  // FP32 copy in FP32 cycles
         if (gemv_bytes / 5.0e9 >= 0.9 * sparse_ms) continue;
-        // A Vanka sweep takes one launch, so a map saves fewer of them: 12^3
-        // 20 ms a solve and not 25 for 296 ms of assembly, 15^3 36 and 44 for
-        // 463 (estimates 289 and 457), 16^3 31 and 39 for 874 (870, no longer
-        // worth its setup).
+        // A Vanka sweep takes one launch, so a map saves fewer of them: 7^3
+        // 7.4 ms a solve and not 13 for 680 ms of assembly, 12^3 20 and 25 for
+        // 296, 15^3 36 and 44 for 463 (estimates 679, 289 and 457), 16^3 31 and
+        // 39 for 874 (864, no longer worth its setup).
         const float asm_ms = h->mixed ? time_cycle(d, true) : sparse_ms;
         const double most = h->prm.smoother == AMG_SMOOTH_VANKA ? SADDLE_TAIL_VANKA_MS : SADDLE_TAIL_SETUP_MS;
         if (static_cast<double>(mmax) * asm_ms > most) continue;
